@@ -206,7 +206,13 @@ typedef enum {
 
 /* Launch shape of the recurrence kernel.  Every shape computes bitwise the
  * same vectors T_n; the moments differ only in the order in which per-block
- * double partial sums are added (a few ulp); the shape sets the speed.  A tile is 256/L rows with
+ * double partial sums are added (a few ulp); the shape sets the speed.
+ * One-orbital Hamiltonians of up to 6 entries per row whose rows lie near their
+ * neighbours (the builder's cell order, a sheet's natural order) run several
+ * steps per launch on tiles held in LDS, with the same vectors; the fields
+ * vectors_per_thread .. rows_per_thread and uniform_values, compact_columns then
+ * have no effect: they shape the sweep (one step per launch), which takes every
+ * other Hamiltonian.  A tile of the sweep is 256/L rows with
  * L = R_pad / vectors_per_thread threads per row (R_pad = R rounded up to a
  * power of two). */
 typedef struct {
@@ -256,7 +262,9 @@ typedef struct {
 tbk_status kpm_default_config(const tbk_ham *h, int32_t R, int32_t precision, tbk_kpm_config *cfg);
 
 /* Bytes of device workspace kpm_moments needs for (h, R, M, precision) with the
- * default launch shape (kpm_workspace_size) or a given one (cfg may be NULL). */
+ * default launch shape (kpm_workspace_size) or a given one (cfg may be NULL).
+ * This includes the lists and vectors of the steps on tiles; a buffer that is
+ * large enough for the sweep alone is accepted too, and the sweep then runs. */
 tbk_status kpm_workspace_size(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
                               int64_t *bytes);
 tbk_status kpm_workspace_size_config(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
@@ -326,16 +334,16 @@ tbk_status kpm_moments_config(const tbk_ham *h, const double *a, const double *b
  * kpm_moments_config without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  The workspace is a static device array of
- * the library, 64 MiB on each GPU it runs on, held until the process ends; this
+ * the library, 384 MiB on each GPU it runs on, held until the process ends; this
  * call makes no allocation (no hipMalloc, hipFree or allocating library
  * routine).  Every call on one GPU shares that GPU's array, which keeps the
  * last call's contents: n_start > 0 continues the run the last call on this
  * GPU left there (as kpm_moments_config continues the run its `work` holds),
  * and calls that overlap on one GPU (several host threads or streams) race.
  * Arguments, results (bit for bit those of kpm_moments_config with the same
- * cfg) and errors as kpm_moments_config, plus BUFFER_TOO_SMALL when
- * kpm_workspace_size_config for these arguments exceeds 64 MiB (e.g. up to
- * about 2.7 M rows for one complex-float vector).  The step timer does not
+ * cfg) and errors as kpm_moments_config, plus BUFFER_TOO_SMALL when the sweep's
+ * workspace for these arguments exceeds 64 MiB (it takes e.g. up to about 2.7 M
+ * rows for one complex-float vector).  The step timer does not
  * time this call.  Synchronises `stream`.
  */
 tbk_status kpm_moments_noalloc(const tbk_ham *h, const double *a, const double *b, const void *r,
@@ -391,8 +399,9 @@ tbk_status kpm_moments_batched(const tbk_ham *h, const double *a, const double *
  * step launches (the moment reductions between stretches are outside them)
  * and add the elapsed times when the call synchronises.
  * kpm_step_timer(1) enables and clears, kpm_step_timer(0) disables;
- * kpm_step_timer_read returns the milliseconds and the number of step
- * launches timed since the last read or enable, then clears them.  The pair
+ * kpm_step_timer_read returns the milliseconds and the number of recurrence
+ * steps timed since the last read or enable (one launch may advance several),
+ * then clears them.  The pair
  * form used by lsqt_vac_moments and the persistent launch are not timed.
  * Errors: INVALID_ARG (enable not 0/1, NULL).
  */

@@ -139,6 +139,7 @@ tbk_status time_shape(const tbk_ham &h, const tbk_kpm_config &cfg, int32_t R, in
     const int M = cfg.doubling ? 2 * steps + 1 : steps + 1;   // `steps` launches either way
     tbk_status st = make_plan(&h, R, M, precision, &cfg, pl);
     if (st != TBK_OK) return st;
+    pl.tile.on = false;       // the shapes are those of the sweep per step
     DevBuf work;
     TBK_HIP(work.alloc(pl.total, s));
     char *w = work.as<char>();

@@ -8,6 +8,7 @@
 #include "common.hpp"
 #include "kpm.hpp"
 #include "kpm_dev.hpp"
+#include "kpm_tile.hpp"
 
 namespace tbk {
 
@@ -25,9 +26,8 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // object (no allocation call), shared by every call on that GPU.  Host code
 // uses the device address hipGetSymbolAddress returns for the current device,
 // never the array's name (a host-side stand-in).
-constexpr size_t kScratchBytes = 64ull << 20;
 constexpr int kScratchDevices = 64;
-static __device__ __align__(256) char scratch[kScratchBytes];
+static __device__ __align__(256) char scratch[kStaticBytes];
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kScratchDevices] = {};
 
@@ -195,12 +195,33 @@ tbk_status make_plan(const tbk_ham *h, int32_t R, int32_t M, int32_t precision, 
     pl.off_raw = pl.off_l1 + align256((size_t)pl.Mr * Rout * pl.n_chunks * sizeof(double));
     pl.off_flag = pl.off_raw + align256((size_t)pl.Mr * Rout * sizeof(double));
     pl.total = pl.off_flag + 256;
+    tile_layout(h, pl, pl.total, R, 1);
     return TBK_OK;
+}
+
+tbk_status build_tiles(const tbk_ham *h, const KpmPlan &pl, int32_t precision, char *w, hipStream_t s, TileRun &run) {
+    return precision == TBK_PREC_F64 ? tile_build<double>(h, pl, 0, w, s, run)
+                                     : tile_build<float>(h, pl, 0, w, s, run);
 }
 
 tbk_status run_plan(const tbk_ham *h, const KpmPlan &pl, double a, double b, const void *r, int32_t R,
                     int32_t M, int32_t precision, char *w, double *mu, hipStream_t s, const void *start,
-                    const void *left) {
+                    const void *left, const TileRun *tiles) {
+    if (pl.tile.on) {
+        TileRun run;
+        if (tiles) run = *tiles;
+        else {
+            const tbk_status st = build_tiles(h, pl, precision, w, s, run);
+            if (st != TBK_OK) return st;
+        }
+        if (run.s > 0) {
+            if (precision == TBK_PREC_F64)
+                return run_tiled<double>(h, pl, run, a, b, static_cast<const double *>(r), R, M, w, mu, s,
+                                         static_cast<const double *>(start), static_cast<const double *>(left));
+            return run_tiled<float>(h, pl, run, a, b, static_cast<const float *>(r), R, M, w, mu, s,
+                                    static_cast<const float *>(start), static_cast<const float *>(left));
+        }
+    }
     const double *sd = static_cast<const double *>(start), *ld_ = static_cast<const double *>(left);
     const float *sf = static_cast<const float *>(start), *lf = static_cast<const float *>(left);
     if (precision == TBK_PREC_F64) {
@@ -366,7 +387,7 @@ extern "C" tbk_status kpm_workspace_size_config(const tbk_ham *h, int32_t R, int
     KpmPlan pl;
     tbk_status st = make_plan(h, R, M, precision, cfg, pl);
     if (st != TBK_OK) return st;
-    *bytes = (int64_t)pl.total;
+    *bytes = (int64_t)pl.tile.total;
     return TBK_OK;
 }
 
@@ -389,6 +410,7 @@ extern "C" tbk_status kpm_moments_config(const tbk_ham *h, const double *a, cons
     if (st != TBK_OK) return st;
     st = check_moment_args(h, pl, a, b, r, work, work_bytes, mu);
     if (st != TBK_OK) return st;
+    pl.tile.on = pl.tile.on && work_bytes >= (int64_t)pl.tile.total;
     TBK_CHECK(pl.cfg.persistent == 0, TBK_ERR_INVALID_ARG, "the persistent launch is for kpm_moments_batched");
     st = check_resume(h, pl, a[0], b[0], R, M, precision, work, as_stream(stream));
     if (st != TBK_OK) return st;
@@ -406,14 +428,14 @@ extern "C" tbk_status kpm_moments_noalloc(const tbk_ham *h, const double *a, con
     pl.n_start = n_start;
     st = check_start(pl, M);
     if (st != TBK_OK) return st;
-    TBK_CHECK(pl.total <= kScratchBytes, TBK_ERR_BUFFER_TOO_SMALL,
-              "kpm_moments_noalloc: this run needs %lld bytes of workspace, more than the %lld-byte static "
-              "workspace (use kpm_moments_config with a caller-allocated workspace)",
-              (long long)pl.total, (long long)kScratchBytes);
+    TBK_CHECK(pl.total <= kStaticSweepBytes, TBK_ERR_BUFFER_TOO_SMALL,
+              "kpm_moments_noalloc: this run's sweep needs %lld bytes, more than the %lld the static workspace "
+              "takes (use kpm_moments_config with a caller-allocated workspace)",
+              (long long)pl.total, (long long)kStaticSweepBytes);
     void *work = nullptr;
     st = scratch_address(&work);
     if (st != TBK_OK) return st;
-    st = check_moment_args(h, pl, a, b, r, work, (int64_t)kScratchBytes, mu);
+    st = check_moment_args(h, pl, a, b, r, work, (int64_t)kStaticBytes, mu);
     if (st != TBK_OK) return st;
     TBK_CHECK(pl.cfg.persistent == 0, TBK_ERR_INVALID_ARG, "the persistent launch is for kpm_moments_batched");
     st = check_resume(h, pl, a[0], b[0], R, M, precision, work, as_stream(stream));
@@ -443,6 +465,7 @@ extern "C" tbk_status kpm_moments_seeded(const tbk_ham *h, const double *a, cons
     if (st != TBK_OK) return st;
     st = check_moment_args(h, pl, a, b, nullptr, work, work_bytes, mu);
     if (st != TBK_OK) return st;
+    pl.tile.on = pl.tile.on && work_bytes >= (int64_t)pl.tile.total;
     TBK_CHECK(pl.cfg.persistent == 0, TBK_ERR_INVALID_ARG, "the persistent launch is for kpm_moments_batched");
     st = check_resume(h, pl, a[0], b[0], R, M, precision, work, as_stream(stream));
     if (st != TBK_OK) return st;

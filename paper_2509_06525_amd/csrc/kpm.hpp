@@ -11,6 +11,30 @@ namespace tbk {
 constexpr int kReduceChunk = 2048;                 // partials per first-level reduction block
 constexpr size_t kPartialBudget = 256ull << 20;    // bytes of block partials kept between reductions
 
+constexpr size_t kStaticSweepBytes = 64ull << 20;   // kpm_moments_noalloc takes runs whose sweep fits in this
+constexpr size_t kStaticBytes = 384ull << 20;       // its static workspace (the tiled form's lists and planes too)
+constexpr int kTileMaxS = 16;                      // most steps per launch of the tiled form (with a halo)
+
+// Layout of the tiled form (kpm_tile.hpp) behind a plan's sweep workspace.
+struct TilePlan {
+    bool on = false;            // offered for this Hamiltonian
+    int shape = 0;              // launch shape (tile_threads, tile_slots)
+    int NT = 0, K = 0, cap = 0; // threads, rows per thread, local rows a tile can hold
+    int W = 0;                  // entries per row
+    int S = 0;                  // rings listed
+    int64_t n_first = 0, n_tiles = 0, tile_rows = 0;   // tiles before halving, most after it, rows of one
+    int reduce_every = 1;       // steps whose partial sums are kept between reductions
+    size_t off_first = 0, off_fseg = 0, off_rings = 0, off_row0 = 0, off_tseg = 0, off_info = 0, off_cnt = 0, off_ext = 0, off_lcol2 = 0, off_lcol1 = 0,
+           off_val = 0, off_ons = 0, off_part = 0, off_l1 = 0, off_planes = 0, plane_bytes = 0, total = 0;
+};
+
+// Tile lists in the workspace: steps per launch (0 = not usable), no halo anywhere.
+struct TileRun {
+    int s = 0;
+    int n_tiles = 0;
+    bool closed = false;
+};
+
 struct KpmPlan {
     tbk_kpm_config cfg{};
     int Rp = 1, L = 1, VPT = 1, log2_slice = 0, n_chunks = 1, reduce_every = 1;
@@ -30,7 +54,11 @@ struct KpmPlan {
     bool seeded = false;        // start vectors generated on the device from `seed`
     uint64_t seed = 0;
     int32_t n_start = 0;        // 0: fresh run; >= 2: continue from the state kept in the workspace
+    TilePlan tile;              // tiled form; its workspace follows `total`
 };
+
+// Fills pl.tile for n_seg structures; its workspace starts at byte `base`.
+void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg);
 
 // Leading bytes of the recurrence workspace: the record of the last completed
 // run, which a later call with n_start > 0 continues.  The vectors r, T_a, T_b
@@ -104,10 +132,15 @@ tbk_status check_moment_args(const tbk_ham *h, const KpmPlan &pl, const double *
                              const void *r, void *work, int64_t work_bytes, double *mu);
 // r: start vectors in the caller's order (or NULL with pl.seeded).  With start
 // and left (row order, [rows][Rp], device) the pair form runs instead:
-// T_0 = start, mu_n = Re <left|T_n(Ht) start>, no spectrum guard.
+// T_0 = start, mu_n = Re <left|T_n(Ht) start>, no spectrum guard.  With
+// pl.tile.on the tiled form runs where the halos fit; `tiles` are lists already
+// in the workspace (build_tiles), so that several runs share them.
 tbk_status run_plan(const tbk_ham *h, const KpmPlan &pl, double a, double b, const void *r, int32_t R,
                     int32_t M, int32_t precision, char *w, double *mu, hipStream_t s,
-                    const void *start = nullptr, const void *left = nullptr);
+                    const void *start = nullptr, const void *left = nullptr, const TileRun *tiles = nullptr);
+
+// Lists the tiles of h in the workspace (pl.tile.on); run.s = 0 when their halos do not fit.
+tbk_status build_tiles(const tbk_ham *h, const KpmPlan &pl, int32_t precision, char *w, hipStream_t s, TileRun &run);
 
 // One run of the recurrence for vector type VT (double: c128, float: c64), L
 // threads per row and VPT vectors per thread; instantiated in kpm_inst_*.hip.

@@ -16,6 +16,7 @@
 #include "common.hpp"
 #include "kpm.hpp"
 #include "kpm_dev.hpp"
+#include "kpm_tile.hpp"
 
 namespace tbk {
 
@@ -326,6 +327,7 @@ struct SegPlan {
     size_t off_bpart = 0, off_boff = 0, off_bseg = 0, off_bar = 0;
     size_t off_r = 0, off_a = 0, off_b = 0, off_part = 0, off_row0 = 0, off_tseg = 0, off_toff = 0,
            off_c1f = 0, off_c1 = 0, off_shift = 0, off_flag = 0, total = 0;
+    std::vector<int32_t> first, fseg;   // tiled form: first rows (n + 1) and structures of the tiles
 };
 
 // Teams of the persistent launch: at most gmax workgroups, one team per
@@ -396,6 +398,20 @@ tbk_status make_seg_plan(const tbk_ham *h, int32_t R, int32_t M, int32_t precisi
     sp.off_shift = sp.off_c1 + a256(ve * sp.n_seg);
     sp.off_flag = sp.off_shift + a256(ve * sp.n_seg);
     sp.total = sp.off_flag + 256;
+    tile_layout(h, sp.base, sp.total, R, sp.n_seg);
+    if (sp.base.tile.on) {
+        // tiles of the tiled form: a structure that fits is one tile, others are cut evenly
+        const TilePlan &tp = sp.base.tile;
+        for (int g = 0; g < sp.n_seg; ++g) {
+            const int64_t r0 = sp.seg_rows[g], rows = sp.seg_rows[g + 1] - r0;
+            const int64_t nt = rows <= tp.cap ? 1 : ceil_div(rows, tp.tile_rows);
+            for (int64_t k = 0; k < nt; ++k) {
+                sp.first.push_back((int32_t)(r0 + rows * k / nt));
+                sp.fseg.push_back(g);
+            }
+        }
+        sp.first.push_back((int32_t)h->n_rows);
+    }
     sp.persistent = sp.base.cfg.persistent != 0;
     if (sp.persistent) {
         int dev = 0, cus = 0;
@@ -585,9 +601,135 @@ tbk_status run_seg(const tbk_ham *h, const SegPlan &sp, const double *a, const d
     return TBK_OK;
 }
 
+// First tile of each structure from the tiles' structures.
+__global__ void k_tile_offsets(const int32_t *__restrict__ tseg, int32_t n_tiles, int32_t n_seg,
+                               int64_t *__restrict__ toff) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n_tiles && (t == 0 || tseg[t] != tseg[t - 1])) toff[tseg[t]] = t;
+    if (t == 0) toff[n_seg] = n_tiles;
+}
+
+// Several steps per launch (kpm_tile.hpp): the structures' tiles side by side,
+// each with its structure's scale.  *done = false: some halo does not fit, and
+// nothing has been written but scratch.
+template <class VT>
+tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, const double *b, const VT *r, int32_t R,
+                         int32_t M, char *w, double *mu, hipStream_t s, bool *done) {
+    *done = false;
+    const KpmPlan &pl = sp.base;
+    const TilePlan &tp = pl.tile;
+    const int ns = sp.n_seg, Rp = pl.Rp;
+    const int nf = (int)sp.fseg.size();
+    int32_t *tseg = reinterpret_cast<int32_t *>(w + tp.off_tseg);
+    int64_t *toff = reinterpret_cast<int64_t *>(w + sp.off_toff);
+    VT *c1f = reinterpret_cast<VT *>(w + sp.off_c1f);
+    VT *c1 = reinterpret_cast<VT *>(w + sp.off_c1);
+    VT *shift = reinterpret_cast<VT *>(w + sp.off_shift);
+    int32_t *flag = reinterpret_cast<int32_t *>(w + sp.off_flag);
+    double *part = reinterpret_cast<double *>(w + tp.off_part);
+    const bool table = ns > 1;
+    if (table) {
+        TBK_CHECK(nf <= tp.n_first, TBK_ERR_DEVICE, "tile table exceeds its workspace");
+        TBK_HIP(hipMemcpyAsync(w + tp.off_first, sp.first.data(), sizeof(int32_t) * (nf + 1), hipMemcpyHostToDevice,
+                               s));
+        TBK_HIP(hipMemcpyAsync(w + tp.off_fseg, sp.fseg.data(), sizeof(int32_t) * nf, hipMemcpyHostToDevice, s));
+    }
+    TileRun run;
+    tbk_status st = tile_build<VT>(h, pl, table ? nf : 0, w, s, run);
+    if (st != TBK_OK) return st;
+    if (run.s == 0) return TBK_OK;
+    std::vector<VT> h1f(ns), h1(ns), hs(ns);
+    bool diag = h->has_onsite != 0;
+    for (int g = 0; g < ns; ++g) {
+        h1f[g] = (VT)(1.0 / a[g]);
+        h1[g] = (VT)(2.0 / a[g]);
+        hs[g] = (VT)b[g];
+        if (b[g] != 0.0) diag = true;
+    }
+    TileArgs<VT> ta = tile_args<VT>(h, pl, run, w, R);
+    ta.c1f = h1f[0];
+    ta.c1 = h1[0];
+    ta.shift = hs[0];
+    if (table) {
+        TBK_HIP(hipMemcpyAsync(c1f, h1f.data(), sizeof(VT) * ns, hipMemcpyHostToDevice, s));
+        TBK_HIP(hipMemcpyAsync(c1, h1.data(), sizeof(VT) * ns, hipMemcpyHostToDevice, s));
+        TBK_HIP(hipMemcpyAsync(shift, hs.data(), sizeof(VT) * ns, hipMemcpyHostToDevice, s));
+        ta.tile_seg = tseg;
+        ta.seg_c1f = c1f;
+        ta.seg_c1 = c1;
+        ta.seg_shift = shift;
+        k_tile_offsets<<<(unsigned)ceil_div(run.n_tiles, 256), 256, 0, s>>>(tseg, run.n_tiles, ns, toff);
+    } else {
+        const int64_t range[2] = {0, run.n_tiles};
+        TBK_HIP(hipMemcpyAsync(toff, range, sizeof range, hipMemcpyHostToDevice, s));
+        TBK_HIP(hipStreamSynchronize(s));      // `range` lives on this stack
+    }
+    auto plane = [&](int k) { return reinterpret_cast<VT *>(w + tp.off_planes + k * tp.plane_bytes); };
+    VT *rp = plane(4);
+    tile_start_planes<VT>(h, pl, run, r, R, w, rp, part, s);
+    TBK_HIP(hipGetLastError());
+    ta.r = rp;
+    const unsigned grid = tile_grid(run, R);
+    auto reduce = [&](int n0, int count) {
+        dim3 g(ns, count);
+        k_reduce_seg<<<g, kThreads, 0, s>>>(part, run.n_tiles, toff, Rp, R, M, n0, mu);
+    };
+    StepTimer &timer = step_timer();
+    bool open = false;
+    if (timer.on) timer.used = 0;
+    const int steps = M - 1;
+    const int groups = (int)ceil_div(steps, std::min<int64_t>(run.s, run.closed ? tp.reduce_every - 1 : kTileMaxS));
+    int batch0 = 0, at = 0, dst = 0;
+    const VT *cur = rp, *prev = rp;
+    for (int q = 0; q < groups; ++q) {
+        const int len = steps / groups + (q < steps % groups ? 1 : 0);
+        if (at + 1 + len - batch0 > tp.reduce_every) {
+            if (open) { TBK_HIP(timer.mark(s)); open = false; }
+            reduce(batch0, at + 1 - batch0);
+            batch0 = at + 1;
+        }
+        if (timer.on && !open) { TBK_HIP(timer.mark(s)); open = true; }
+        if (timer.on) timer.launches += len;
+        ta.first = at == 0;
+        ta.s = len;
+        ta.cur = cur;
+        ta.prev = prev;
+        const bool keep = q + 1 < groups;
+        ta.out_cur = keep ? plane(2 * dst) : nullptr;
+        ta.out_prev = keep ? plane(2 * dst + 1) : nullptr;
+        ta.partial = part + (int64_t)(at + 1 - batch0) * ta.pstride;
+        launch_tile_group<VT>(pl, diag, grid, s, ta);
+        cur = ta.out_cur;
+        prev = ta.out_prev;
+        at += len;
+        dst ^= 1;
+    }
+    if (open) TBK_HIP(timer.mark(s));
+    reduce(batch0, M - batch0);
+    k_fill_flag<<<1, 64, 0, s>>>(flag);
+    const int64_t rows = (int64_t)ns * R;
+    k_guard_seg<<<(unsigned)ceil_div(rows * M, 256), 256, 0, s>>>(mu, rows, M, flag);
+    TBK_HIP(hipGetLastError());
+    int32_t hflag = 0;
+    TBK_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    TBK_HIP(hipStreamSynchronize(s));
+    if (timer.on) TBK_HIP(timer.collect());
+    *done = true;
+    TBK_CHECK(hflag == 0, TBK_ERR_SPECTRUM, "a moment exceeds mu_0: some (a_s, b_s) does not bound its spectrum");
+    return TBK_OK;
+}
+
 tbk_status dispatch_seg(const tbk_ham *h, const SegPlan &sp, const double *a, const double *b, const void *r,
                         int32_t R, int32_t M, int32_t precision, char *w, double *mu, hipStream_t s) {
     const int L = sp.base.L, VPT = sp.base.VPT;
+    if (sp.base.tile.on) {
+        bool done = false;
+        const tbk_status st =
+            precision == TBK_PREC_F64
+                ? run_seg_tiled<double>(h, sp, a, b, static_cast<const double *>(r), R, M, w, mu, s, &done)
+                : run_seg_tiled<float>(h, sp, a, b, static_cast<const float *>(r), R, M, w, mu, s, &done);
+        if (st != TBK_OK || done) return st;
+    }
     if (precision == TBK_PREC_F64) {
         const double *rr = static_cast<const double *>(r);
         switch (L) {
@@ -638,7 +780,7 @@ extern "C" tbk_status kpm_workspace_size_batched(const tbk_ham *h, int32_t R, in
     SegPlan sp;
     tbk_status st = make_seg_plan(h, R, M, precision, cfg, as_stream(stream), sp);
     if (st != TBK_OK) return st;
-    *bytes = (int64_t)sp.total;
+    *bytes = (int64_t)std::max(sp.total, sp.base.tile.total);
     return TBK_OK;
 }
 
@@ -658,6 +800,7 @@ extern "C" tbk_status kpm_moments_batched(const tbk_ham *h, const double *a, con
     }
     TBK_CHECK(work_bytes >= (int64_t)sp.total, TBK_ERR_BUFFER_TOO_SMALL, "work has %lld bytes, needs %lld",
               (long long)work_bytes, (long long)sp.total);
+    sp.base.tile.on = sp.base.tile.on && work_bytes >= (int64_t)sp.base.tile.total;
     TBK_CHECK(((uintptr_t)work & 255) == 0, TBK_ERR_INVALID_ARG, "work is not 256-byte aligned");
     TBK_CHECK(h->ptr && h->col && h->val && h->onsite && h->perm, TBK_ERR_INVALID_ARG, "Hamiltonian array is NULL");
     return dispatch_seg(h, sp, a, b, r, R, M, precision, static_cast<char *>(work), mu, s);

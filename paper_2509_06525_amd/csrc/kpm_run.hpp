@@ -421,6 +421,51 @@ void launch_reduce(const KpmPlan &pl, int n0, int count, int R, double *part, do
     k_reduce_l1<<<grid, kThreads, 0, s>>>(part, pl.G, pl.Rp, R, n0, pl.n_chunks, l1);
 }
 
+// Last part of a run: chunk sums to moments, spectrum guard and state record
+// (not in the pair form, where |mu_n| <= mu_0 holds only for left = start).
+// Sums of vector v sit at the virtual vectors of k_doubling_combine for VPT.
+template <class VT>
+tbk_status finish_run(const tbk_ham *h, const KpmPlan &pl, double a, double b, int32_t R, int32_t M, char *work,
+                      double *mu, hipStream_t s, bool pair, bool dbl, int VPT, const double *l1, int n_chunks,
+                      bool timed) {
+    KpmState *state = reinterpret_cast<KpmState *>(work + pl.off_state);
+    double *mu0 = reinterpret_cast<double *>(work + pl.off_state + kStateMu0);
+    double *raw = reinterpret_cast<double *>(work + pl.off_raw);
+    int32_t *flag = reinterpret_cast<int32_t *>(work + pl.off_flag);
+    const int n0 = pl.n_start, Rv = pl.Rv, Mr = pl.Mr;
+    const int64_t nm = (int64_t)R * (M - n0);
+    if (dbl) {
+        k_reduce_l2<<<(unsigned)ceil_div((int64_t)Rv * Mr, 256), 256, 0, s>>>(l1, Rv, Mr, 0, n_chunks, raw);
+        TBK_HIP(hipGetLastError());
+        k_doubling_combine<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(raw, Mr - 1, VPT, R, M, mu);
+    } else {
+        k_reduce_l2<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(l1, R, M, n0, n_chunks, mu);
+    }
+    TBK_HIP(hipGetLastError());
+    if (pair) return TBK_OK;
+    k_fill_i32<<<1, 64, 0, s>>>(flag, 1, 0);
+    k_guard<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(mu, R, M, n0, mu0, flag);
+    KpmState rec{};
+    rec.magic = dbl ? 0 : kStateMagic;    // the doubling form keeps no state to continue from
+    rec.n_rows = h->n_rows;
+    rec.n_entries = h->n_entries;
+    rec.R = R;
+    rec.precision = sizeof(VT) == sizeof(double) ? TBK_PREC_F64 : TBK_PREC_C32;
+    rec.fmt = h->fmt;
+    rec.next_n = M;
+    rec.a = a;
+    rec.b = b;
+    k_store_state<<<1, 64, 0, s>>>(rec, state);
+    TBK_HIP(hipGetLastError());
+    int32_t hflag = 0;
+    TBK_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    TBK_HIP(hipStreamSynchronize(s));
+    if (timed) TBK_HIP(step_timer().collect());
+    TBK_CHECK(hflag == 0, TBK_ERR_SPECTRUM,
+              "a moment exceeds mu_0: the scale a = %g, shift b = %g do not bound the spectrum", a, b);
+    return TBK_OK;
+}
+
 // start/left (row order, [rows][Rp], both non-NULL) select the pair form:
 // T_0 = start and mu_n = Re <left|T_n>, without the spectrum guard.
 template <class VT, int L, int VPT, bool DBL>
@@ -428,15 +473,11 @@ tbk_status run_moments_t(const tbk_ham *h, const KpmPlan &pl, double a, double b
                          int32_t M, char *work, double *mu, hipStream_t s, const VT *start, const VT *left) {
     const bool pair = left != nullptr;
     const int n_start = pl.n_start;   // 0, or >= 2 with T_{n_start-1}, T_{n_start-2} and r in the workspace
-    KpmState *state = reinterpret_cast<KpmState *>(work + pl.off_state);
-    double *mu0 = reinterpret_cast<double *>(work + pl.off_state + kStateMu0);
     VT *r_int = reinterpret_cast<VT *>(work + pl.off_r);
     VT *TA = reinterpret_cast<VT *>(work + pl.off_a);
     VT *TB = reinterpret_cast<VT *>(work + pl.off_b);
     double *part = reinterpret_cast<double *>(work + pl.off_part);
     double *l1 = reinterpret_cast<double *>(work + pl.off_l1);
-    double *raw = reinterpret_cast<double *>(work + pl.off_raw);
-    int32_t *flag = reinterpret_cast<int32_t *>(work + pl.off_flag);
     const int Rv = pl.Rv;           // partial sums per block (per step)
     const int Mr = pl.Mr;           // reduced rows: moments (direct) or steps + 1 (doubling)
     const int Rout = DBL ? Rv : R;  // sums kept after the reduction
@@ -512,43 +553,7 @@ tbk_status run_moments_t(const tbk_ham *h, const KpmPlan &pl, double a, double b
     if (open) TBK_HIP(timer.mark(s));
     reduce(batch0, Mr - batch0);
     TBK_HIP(hipGetLastError());
-    const int64_t nm = (int64_t)R * M;
-    if constexpr (DBL) {
-        k_reduce_l2<<<(unsigned)ceil_div((int64_t)Rv * Mr, 256), 256, 0, s>>>(l1, Rv, Mr, 0, pl.n_chunks, raw);
-        TBK_HIP(hipGetLastError());
-        k_doubling_combine<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(raw, Mr - 1, VPT, R, M, mu);
-    } else {
-        const int64_t nw = (int64_t)R * (M - n_start);
-        k_reduce_l2<<<(unsigned)ceil_div(nw, 256), 256, 0, s>>>(l1, R, M, n_start, pl.n_chunks, mu);
-    }
-    TBK_HIP(hipGetLastError());
-    if (pair) return TBK_OK;     // no guard: |mu_n| <= mu_0 holds only for left = start
-    k_fill_i32<<<1, 64, 0, s>>>(flag, 1, 0);
-    if constexpr (DBL) {
-        k_guard<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(mu, R, M, 0, mu0, flag);
-    } else {
-        const int64_t nw = (int64_t)R * (M - n_start);
-        k_guard<<<(unsigned)ceil_div(nw, 256), 256, 0, s>>>(mu, R, M, n_start, mu0, flag);
-    }
-    KpmState rec{};
-    rec.magic = DBL ? 0 : kStateMagic;    // the doubling form keeps no state to continue from
-    rec.n_rows = h->n_rows;
-    rec.n_entries = h->n_entries;
-    rec.R = R;
-    rec.precision = sizeof(VT) == sizeof(double) ? TBK_PREC_F64 : TBK_PREC_C32;
-    rec.fmt = h->fmt;
-    rec.next_n = M;
-    rec.a = a;
-    rec.b = b;
-    k_store_state<<<1, 64, 0, s>>>(rec, state);
-    TBK_HIP(hipGetLastError());
-    int32_t hflag = 0;
-    TBK_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    TBK_HIP(hipStreamSynchronize(s));
-    if (timed) TBK_HIP(timer.collect());
-    TBK_CHECK(hflag == 0, TBK_ERR_SPECTRUM,
-              "a moment exceeds mu_0: the scale a = %g, shift b = %g do not bound the spectrum", a, b);
-    return TBK_OK;
+    return finish_run<VT>(h, pl, a, b, R, M, work, mu, s, pair, DBL, VPT, l1, pl.n_chunks, timed);
 }
 
 template <class VT, int L, int VPT>

@@ -1,0 +1,644 @@
+// Tiled recurrence (kpm_tile.hpp): tile lists, workspace layout and the driver
+// of a run.
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+#include "kpm_run.hpp"
+#include "kpm_tile.hpp"
+
+namespace tbk {
+namespace {
+
+constexpr int kPlanThreads = 512;
+constexpr int kHaloMax = 2048;         // halo rows a tile can list
+constexpr int kHashSize = 4096;        // open addressing, at most kHaloMax + kPlanThreads keys
+constexpr int kTileMaxW = 6;           // entries per row
+constexpr size_t kTilePartialBudget = 64ull << 20;
+
+size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+struct TileInfo {                       // what the host reads back
+    int32_t rings;                      // rings complete in every tile
+    int32_t n_tiles;                    // tiles after the split
+    unsigned long long rows[kTileMaxS + 1];   // sum over tiles of the rows within k rings
+};
+
+// first[t] = first row of tile t of n_tiles tiles of equal size over n rows;
+// clears the summary.
+__global__ void k_tile_rows(int64_t n, int32_t n_tiles, int32_t S, int32_t *__restrict__ first,
+                            TileInfo *__restrict__ info) {
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (first && t <= n_tiles) first[t] = (int32_t)((n * t) / n_tiles);
+    if (t <= kTileMaxS) info->rows[t] = 0;
+    if (t == 0) {
+        info->rings = S;
+        info->n_tiles = n_tiles;
+    }
+}
+
+// Halves the tiles whose halo does not fit (the builder orders rows in strips of
+// cells; a tile across a strip's end has two edges more than its neighbours and
+// would set the steps per launch for all of them).  One workgroup: every thread
+// counts the pieces of a run of tiles, a scan places them.  At most `most` tiles
+// result; entries past the last one hold n.
+__global__ __launch_bounds__(1024) void k_tile_split(const int32_t *__restrict__ first, const int32_t *__restrict__ rings,
+                                                     const int32_t *__restrict__ seg, int32_t n_tiles, int32_t most,
+                                                     int32_t S, int32_t n, int32_t *__restrict__ row0,
+                                                     int32_t *__restrict__ tseg, TileInfo *__restrict__ info) {
+    __shared__ int32_t sum[1024];
+    const int tid = threadIdx.x;
+    const int per = (n_tiles + 1023) / 1024;
+    const int t0 = min(tid * per, n_tiles), t1 = min(t0 + per, n_tiles);
+    auto pieces = [&](int t) { return rings[t] < S && first[t + 1] - first[t] >= 2 ? 2 : 1; };
+    int c = 0;
+    for (int t = t0; t < t1; ++t) c += pieces(t);
+    sum[tid] = c;
+    __syncthreads();
+    for (int d = 1; d < 1024; d <<= 1) {
+        const int x = tid >= d ? sum[tid - d] : 0;
+        __syncthreads();
+        sum[tid] += x;
+        __syncthreads();
+    }
+    const int total = sum[1023];
+    const bool split = total <= most;       // otherwise the tiles stay as they are
+    int q = split ? sum[tid] - c : t0;
+    for (int t = t0; t < t1; ++t) {
+        const int lo = first[t], len = first[t + 1] - lo, np = split ? pieces(t) : 1;
+        for (int k = 0; k < np; ++k, ++q) {
+            row0[q] = lo + (int)((int64_t)len * k / np);
+            if (seg) tseg[q] = seg[t];
+        }
+    }
+    const int count = split ? total : n_tiles;
+    for (int k = count + tid; k <= most; k += 1024) row0[k] = n;
+    if (tid == 0) info->n_tiles = count;
+}
+
+struct TilePlanArgs {
+    const int64_t *ptr;
+    const int32_t *col;
+    const void *val, *onsite;
+    const int32_t *row0;
+    int32_t *cnt, *ext;
+    uint32_t *lcol2;
+    uint16_t *lcol1;
+    void *tval, *tons;
+    TileInfo *info;
+    int32_t *rings;          // PROBE: complete rings of each tile
+    int32_t log2_slice, S, W, cap;
+};
+
+// Lists of one tile: breadth-first over the bonds, ring by ring.  Rows outside
+// the tile go through an LDS hash table (row -> local index) and take the next
+// local index when first met, so a ring follows the order of the rows that reach
+// it.  The order within a ring is not reproducible, the results are: every value
+// depends on its own row's entries only, and only the tile's rows are summed.
+// PROBE: only counts the rings that fit.
+template <class VT, bool PROBE>
+__global__ __launch_bounds__(kPlanThreads) void k_tile_plan(TilePlanArgs a) {
+    __shared__ int32_t keys[kHashSize];
+    __shared__ uint16_t lidx[kHashSize];
+    __shared__ int32_t list[kHaloMax];
+    __shared__ int32_t s_count, s_over;
+    const int t = blockIdx.x, tid = threadIdx.x;
+    const int row0 = a.row0[t], nr = a.row0[t + 1] - row0;
+    if (nr == 0) return;
+    const int cap_h = min(a.cap - nr, kHaloMax);
+    const int64_t smask = ((int64_t)1 << a.log2_slice) - 1, stride = smask + 1;
+    for (int i = tid; i < kHashSize; i += kPlanThreads) keys[i] = -1;
+    if (tid == 0) { s_count = 0; s_over = 0; }
+    __syncthreads();
+    int32_t *cnt = a.cnt + (int64_t)t * (a.S + 1);
+    if (!PROBE && tid == 0) cnt[0] = nr;
+    auto hash = [](int32_t c) { return (uint32_t)c * 2654435761u >> 20; };      // 12 bits
+    auto global_row = [&](int j) { return j < nr ? row0 + j : list[j - nr]; };
+    auto entries = [&](int64_t g, int64_t &base, int &w) {
+        const int64_t sl = g >> a.log2_slice;
+        const int64_t p0 = a.ptr[sl], p1 = a.ptr[sl + 1];
+        base = p0 + (g & smask);
+        w = (int)((p1 - p0) >> a.log2_slice);
+    };
+    // the first a.W (<= kTileMaxW) columns of a row, all loaded before any is used; own row past w
+    auto columns = [&](int64_t g, int64_t base, int w, int32_t (&c)[kTileMaxW]) {
+#pragma unroll
+        for (int q = 0; q < kTileMaxW; ++q) {
+            c[q] = (int32_t)g;
+            if (q < a.W && q < w) c[q] = a.col[base + q * stride];
+        }
+    };
+    int lo = 0, hi = nr, done = 0, total = 0;     // rows of the previous ring; complete rings; halo rows
+    bool closed = false;
+    for (int k = 1; k <= a.S; ++k) {
+        for (int j = lo + tid; j < hi; j += kPlanThreads) {
+            int64_t base;
+            int w;
+            int32_t cc[kTileMaxW];
+            const int64_t g = global_row(j);
+            entries(g, base, w);
+            if (w > a.W) s_over = 1;
+            columns(g, base, w, cc);
+#pragma unroll
+            for (int q = 0; q < kTileMaxW; ++q) {
+                const int32_t c = cc[q];
+                if (c == g || (uint32_t)(c - row0) < (uint32_t)nr) continue;
+                uint32_t p = hash(c);
+                while (!*(volatile int32_t *)&s_over) {
+                    const int32_t old = atomicCAS(&keys[p], -1, c);
+                    if (old == c) break;
+                    if (old == -1) {
+                        const int pos = atomicAdd(&s_count, 1);
+                        if (pos < cap_h) { list[pos] = c; lidx[p] = (uint16_t)(nr + pos); }
+                        else s_over = 1;
+                        break;
+                    }
+                    p = (p + 1) & (kHashSize - 1);
+                }
+            }
+        }
+        __syncthreads();
+        if (s_over) break;
+        const int now = s_count;
+        __syncthreads();
+        if (now == total) {             // nothing beyond: the list is closed under the bonds
+            if (!PROBE)
+                for (int q = k + tid; q <= a.S; q += kPlanThreads) cnt[q] = nr + total;
+            done = a.S;
+            closed = true;
+            break;
+        }
+        lo = nr + total;
+        hi = nr + now;
+        total = now;
+        done = k;
+        if (!PROBE && tid == 0) cnt[k] = nr + now;
+    }
+    if constexpr (PROBE) {
+        if (tid == 0) a.rings[t] = done;
+        return;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        atomicMin(&a.info->rings, done);
+        for (int k = 0; k <= done; ++k) atomicAdd(&a.info->rows[k], (unsigned long long)cnt[k]);
+    }
+    if (done == 0) return;
+    const int64_t mb = (int64_t)t * a.cap;
+    for (int i = tid; i < total; i += kPlanThreads) a.ext[mb + i] = list[i];
+    // matrix rows of every ring but the last, in local form
+    const int n_mat = closed ? nr + total : lo;
+    const VT *val = static_cast<const VT *>(a.val);
+    const VT *ons = static_cast<const VT *>(a.onsite);
+    VT *tval = static_cast<VT *>(a.tval);
+    VT *tons = static_cast<VT *>(a.tons);
+    const int NP = a.W / 2;
+    for (int j = tid; j < n_mat; j += kPlanThreads) {
+        const int64_t g = global_row(j);
+        int64_t base;
+        int w;
+        int32_t cc[kTileMaxW];
+        VT v[kTileMaxW];
+        entries(g, base, w);
+        columns(g, base, w, cc);
+#pragma unroll
+        for (int q = 0; q < kTileMaxW; ++q) {
+            v[q] = 0;
+            if (q < a.W && q < w) v[q] = val[base + q * stride];
+        }
+        uint32_t lc[kTileMaxW];
+#pragma unroll
+        for (int q = 0; q < kTileMaxW; ++q) {
+            const int32_t c = cc[q];
+            lc[q] = (uint32_t)j;
+            if (c != g) {
+                if ((uint32_t)(c - row0) < (uint32_t)nr) {
+                    lc[q] = (uint32_t)(c - row0);
+                } else {
+                    uint32_t p = hash(c);
+                    while (keys[p] != c) p = (p + 1) & (kHashSize - 1);
+                    lc[q] = lidx[p];
+                }
+            }
+            lc[q] *= (uint32_t)(2 * sizeof(VT));
+        }
+#pragma unroll
+        for (int q = 0; q < kTileMaxW; ++q) {
+            if (q >= a.W) continue;
+            tval[mb * a.W + (int64_t)q * a.cap + j] = v[q];
+            if (q == a.W - 1 && (a.W & 1)) a.lcol1[mb + j] = (uint16_t)lc[q];
+            else if (q & 1) a.lcol2[mb * NP + (int64_t)(q / 2) * a.cap + j] = lc[q - 1] | (lc[q] << 16);
+        }
+        if (ons) tons[mb + j] = ons[g];
+    }
+}
+
+// Start of a run.  MODE 0: start vectors r (caller's order, or seeded phases) to
+// row order [rows][Rp] (r_int) and planes; sums of |r|^2 per tile.  MODE 1 (pair
+// form): start and left, [rows][Rp] in row order, to planes; sums of
+// Re <left|start>.  A block per tile; thread e takes elements e, e + 256, ... of
+// the tile's [row][vector] range, all of one vector.
+template <class VT, int MODE, bool DBL>
+__global__ __launch_bounds__(kThreads) void k_tile_prepare(const VT *__restrict__ r, const VT *__restrict__ left,
+                                                           const int32_t *__restrict__ perm,
+                                                           const int32_t *__restrict__ row0, int64_t rows, int32_t R,
+                                                           int32_t Rp, int32_t seeded, uint64_t seed,
+                                                           VT *__restrict__ r_int, VT *__restrict__ plane,
+                                                           VT *__restrict__ lplane, double *__restrict__ partial) {
+    __shared__ double red[kThreads];
+    const int t = blockIdx.x;
+    const int64_t i0 = row0[t];
+    const int ne = (row0[t + 1] - row0[t]) * Rp;
+    const int v = threadIdx.x % Rp;
+    double acc = 0.0;
+    for (int e = threadIdx.x; e < ne; e += kThreads) {
+        const int64_t i = i0 + e / Rp;
+        const int64_t o = 2 * (i * Rp + v), po = 2 * ((int64_t)v * rows + i);
+        if constexpr (MODE == 0) {
+            VT re = 0, im = 0;
+            if (v < R) {
+                const int64_t src = perm ? (int64_t)perm[i] : i;
+                if (seeded) {
+                    double c, sn;
+                    seeded_phase(seed, (uint64_t)src * (uint64_t)R + (uint64_t)v, c, sn);
+                    re = (VT)c;
+                    im = (VT)sn;
+                } else {
+                    re = r[2 * (src * R + v)];
+                    im = r[2 * (src * R + v) + 1];
+                }
+            }
+            if (r_int) {
+                r_int[o] = re;
+                r_int[o + 1] = im;
+            }
+            if (plane != r_int && v < R) {
+                plane[po] = re;
+                plane[po + 1] = im;
+            }
+            acc += (double)re * (double)re + (double)im * (double)im;
+        } else if (v < R) {
+            const VT re = r[o], im = r[o + 1], lr = left[o], li = left[o + 1];
+            plane[po] = re;
+            plane[po + 1] = im;
+            lplane[po] = lr;
+            lplane[po + 1] = li;
+            acc += (double)lr * (double)re + (double)li * (double)im;
+        }
+    }
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int g = kThreads / 2; g >= Rp; g >>= 1) {
+        if ((int)threadIdx.x < g) red[threadIdx.x] += red[threadIdx.x + g];
+        __syncthreads();
+    }
+    if ((int)threadIdx.x < Rp) {
+        if constexpr (DBL) {
+            partial[(int64_t)t * 2 * Rp + 2 * v] = red[v];
+            partial[(int64_t)t * 2 * Rp + 2 * v + 1] = 0.0;
+        } else {
+            partial[(int64_t)t * Rp + v] = red[v];
+        }
+    }
+}
+
+// [rows][Rp] <-> planes [vector][rows] for the R vectors (TO: into planes; the
+// padded columns of the row form are zero).
+template <class VT, bool TO>
+__global__ __launch_bounds__(kThreads) void k_planes(VT *__restrict__ x, VT *__restrict__ plane, int64_t rows,
+                                                     int32_t R, int32_t Rp) {
+    const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (idx >= rows * Rp) return;
+    const int64_t i = idx / Rp;
+    const int v = (int)(idx % Rp);
+    const int64_t po = 2 * ((int64_t)v * rows + i);
+    if constexpr (TO) {
+        if (v < R) {
+            plane[po] = x[2 * idx];
+            plane[po + 1] = x[2 * idx + 1];
+        }
+    } else {
+        x[2 * idx] = v < R ? plane[po] : (VT)0;
+        x[2 * idx + 1] = v < R ? plane[po + 1] : (VT)0;
+    }
+}
+
+template <class VT>
+void launch_steps(const TilePlan &tp, bool diag, bool dbl, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
+    if (tp.W == 3) launch_tile_steps<VT, 3>(tp, diag, dbl, grid, s, a);
+    else if (tp.W == 4) launch_tile_steps<VT, 4>(tp, diag, dbl, grid, s, a);
+    else launch_tile_steps<VT, 6>(tp, diag, dbl, grid, s, a);
+}
+
+// Layout for rows of up to W entries from byte `base` on.
+void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int W, TilePlan &tp) {
+    tp = TilePlan{};
+    tp.W = W;
+    const int64_t n = h->n_rows, work = n * R;
+    const bool f64 = pl.elem == sizeof(double);
+    auto shape = [&](int sh) {
+        tp.shape = sh;
+        tp.NT = tile_threads(sh);
+        tp.K = tile_slots(sh, W, f64);
+        tp.cap = tile_cap(tp.NT, tp.K);
+    };
+    shape(kTileWhole);
+    if (n_seg == 1 && n <= tp.cap) {
+        tp.n_first = tp.n_tiles = 1;
+        tp.tile_rows = n;
+        tp.S = 1;
+    } else {
+        // Rows per tile and rings.  Large systems: 0.65 of the capacity (0.6 in FP64) and
+        // eight (six) rings; 4 M rows, one complex-float vector, us per step: 13.1 with 0.8
+        // and 4 rings, 9.6 with 0.65 and 8, 10.2 with 0.6 and 10 (the sweep: 36.9).  Systems
+        // with fewer tiles than CUs: smaller tiles, whose larger halo costs less than idle
+        // CUs; 30,212 rows, three vectors: 1.25 us per step with 384 rows (236 workgroups),
+        // 1.6 with 1024, the sweep 4.8.
+        if (!f64 && work < 700000) {
+            shape(kTileSmall);
+            tp.tile_rows = std::min<int64_t>(tp.cap * 8 / 15, std::max<int64_t>(256, work / 256));
+        } else {
+            shape(h->has_onsite ? kTileLargeDiag : kTileLarge);
+            if (f64) tp.tile_rows = std::min<int64_t>(tp.cap * 3 / 5, std::max<int64_t>(256, work / 400));
+            else tp.tile_rows = std::min<int64_t>(tp.cap * 13 / 20, std::max<int64_t>(tp.cap * 7 / 25, work / 512));
+        }
+        tp.S = (f64 || tp.shape == kTileSmall) && tp.tile_rows > tp.cap * 2 / 5 ? 6 : 8;
+        tp.n_first = ceil_div(n, tp.tile_rows) + (n_seg > 1 ? n_seg : 0);   // a partial tile per structure
+        tp.n_tiles = tp.n_first + tp.n_first / 8 + 8;                       // room for halved tiles
+    }
+    const size_t per_step = (size_t)tp.n_tiles * pl.Rv * sizeof(double);
+    tp.reduce_every = (int)std::min<size_t>(kTilePartialBudget / per_step, (size_t)std::min(pl.Mr, 4096));
+    tp.reduce_every = std::max(tp.reduce_every, kTileMaxS + 1);
+    const size_t rows = (size_t)tp.n_tiles * tp.cap;
+    const size_t chunks = (size_t)ceil_div(tp.n_tiles, kReduceChunk);
+    size_t o = base;
+    auto take = [&](size_t bytes) { const size_t at = o; o += align256(bytes); return at; };
+    tp.off_first = take(sizeof(int32_t) * (tp.n_first + 1));
+    tp.off_fseg = take(sizeof(int32_t) * tp.n_first);
+    tp.off_rings = take(sizeof(int32_t) * tp.n_first);
+    tp.off_row0 = take(sizeof(int32_t) * (tp.n_tiles + 1));
+    tp.off_tseg = take(sizeof(int32_t) * tp.n_tiles);
+    tp.off_info = take(sizeof(TileInfo));
+    tp.off_cnt = take(sizeof(int32_t) * tp.n_tiles * (tp.S + 1));
+    tp.off_ext = take(sizeof(int32_t) * rows);
+    tp.off_lcol2 = take(sizeof(uint32_t) * rows * (W / 2));
+    tp.off_lcol1 = take(sizeof(uint16_t) * rows * (W % 2));
+    tp.off_val = take(pl.elem * rows * W);
+    tp.off_ons = take(pl.elem * rows);
+    tp.off_part = take((size_t)tp.reduce_every * per_step);
+    tp.off_l1 = take((size_t)pl.Mr * pl.Rv * chunks * sizeof(double));
+    tp.plane_bytes = align256((size_t)n * R * 2 * pl.elem);
+    tp.off_planes = take((pl.Rp == 1 && n_seg == 1 ? 2 : 6) * tp.plane_bytes);
+    tp.total = o;
+}
+
+}  // namespace
+
+void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg) {
+    pl.tile = TilePlan{};
+    pl.tile.total = base;
+    if (pl.block || h->max_degree < 1 || h->max_degree > kTileMaxW || pl.cfg.persistent) return;
+    TilePlan other;
+    layout_width(h, pl, base, R, n_seg, h->max_degree <= 3 ? 3 : (h->max_degree <= 4 ? 4 : 6), pl.tile);
+    if (pl.tile.W <= 4) {
+        // one size for degrees up to 4, so that a workspace serves frames of either
+        layout_width(h, pl, base, R, n_seg, pl.tile.W == 3 ? 4 : 3, other);
+        pl.tile.total = std::max(pl.tile.total, other.total);
+    }
+    // runs that the static workspace takes get the same form with it as with a caller's
+    pl.tile.on = base > kStaticSweepBytes || pl.tile.total <= kStaticBytes;
+    if (!pl.tile.on) pl.tile.total = base;
+}
+
+// Tile lists of h (or of its structures, whose row0 table the caller has
+// written) and the number of steps per launch.  run.s = 0: the halos do not fit
+// (rows without locality), the sweep per step is to be used.
+template <class VT>
+tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *work, hipStream_t s, TileRun &run) {
+    const TilePlan &tp = pl.tile;
+    run = TileRun{};
+    int32_t *first = reinterpret_cast<int32_t *>(work + tp.off_first);
+    int32_t *fseg = reinterpret_cast<int32_t *>(work + tp.off_fseg);
+    int32_t *row0 = reinterpret_cast<int32_t *>(work + tp.off_row0);
+    int32_t *tseg = reinterpret_cast<int32_t *>(work + tp.off_tseg);
+    TileInfo *info = reinterpret_cast<TileInfo *>(work + tp.off_info);
+    const bool whole = tp.shape == kTileWhole;             // the whole matrix in one tile
+    const bool table = n_first > 0;               // the caller has written first and fseg
+    const int nf = table ? n_first : (int)tp.n_first;
+    k_tile_rows<<<(unsigned)ceil_div(nf + 1 + kTileMaxS, 256), 256, 0, s>>>(
+        h->n_rows, nf, tp.S, whole ? row0 : (table ? nullptr : first), info);
+    TilePlanArgs pa{};
+    pa.ptr = h->ptr;
+    pa.col = h->col;
+    pa.val = h->val;
+    pa.onsite = h->has_onsite ? h->onsite : nullptr;
+    pa.cnt = reinterpret_cast<int32_t *>(work + tp.off_cnt);
+    pa.ext = reinterpret_cast<int32_t *>(work + tp.off_ext);
+    pa.lcol2 = reinterpret_cast<uint32_t *>(work + tp.off_lcol2);
+    pa.lcol1 = reinterpret_cast<uint16_t *>(work + tp.off_lcol1);
+    pa.tval = work + tp.off_val;
+    pa.tons = work + tp.off_ons;
+    pa.info = info;
+    pa.rings = reinterpret_cast<int32_t *>(work + tp.off_rings);
+    pa.log2_slice = pl.log2_slice;
+    pa.S = tp.S;
+    pa.W = tp.W;
+    pa.cap = tp.cap;
+    if (!whole) {
+        pa.row0 = first;
+        k_tile_plan<VT, true><<<(unsigned)nf, kPlanThreads, 0, s>>>(pa);
+        k_tile_split<<<1, 1024, 0, s>>>(first, pa.rings, table ? fseg : nullptr, nf, (int)tp.n_tiles, tp.S,
+                                        (int)h->n_rows, row0, tseg, info);
+    }
+    pa.row0 = row0;
+    k_tile_plan<VT, false><<<(unsigned)(whole ? 1 : tp.n_tiles), kPlanThreads, 0, s>>>(pa);
+    TBK_HIP(hipGetLastError());
+    if (whole) {
+        run.n_tiles = 1;
+        run.closed = true;
+        run.s = INT32_MAX;
+        return TBK_OK;
+    }
+    TileInfo hi;
+    TBK_HIP(hipMemcpyAsync(&hi, info, sizeof hi, hipMemcpyDeviceToHost, s));
+    TBK_HIP(hipStreamSynchronize(s));
+    run.n_tiles = hi.n_tiles;
+    if (hi.rings >= 1 && hi.rows[hi.rings] == hi.rows[0]) {
+        run.closed = true;
+        run.s = INT32_MAX;
+        return TBK_OK;
+    }
+    if (hi.rings < 2) return TBK_OK;     // one ring saves nothing over the sweep
+    run.s = hi.rings;
+    return TBK_OK;
+}
+
+template <class VT>
+TileArgs<VT> tile_args(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, char *work, int32_t R) {
+    const TilePlan &tp = pl.tile;
+    TileArgs<VT> a{};
+    a.row0 = reinterpret_cast<const int32_t *>(work + tp.off_row0);
+    a.cnt = reinterpret_cast<const int32_t *>(work + tp.off_cnt);
+    a.ext = reinterpret_cast<const int32_t *>(work + tp.off_ext);
+    a.lcol2 = reinterpret_cast<const uint32_t *>(work + tp.off_lcol2);
+    a.lcol1 = reinterpret_cast<const uint16_t *>(work + tp.off_lcol1);
+    a.val = reinterpret_cast<const VT *>(work + tp.off_val);
+    a.ons = h->has_onsite ? reinterpret_cast<const VT *>(work + tp.off_ons) : nullptr;
+    a.rows = h->n_rows;
+    a.n_work = run.n_tiles * R;
+    a.R = R;
+    a.Rv = pl.cfg.doubling ? 2 * pl.Rp : pl.Rp;
+    a.pstride = (int64_t)run.n_tiles * a.Rv;
+    a.S1 = tp.S + 1;
+    a.cap = tp.cap;
+    a.closed = run.closed ? 1 : 0;
+    return a;
+}
+
+unsigned tile_grid(const TileRun &run, int32_t R) {
+    return (unsigned)(ceil_div((int64_t)run.n_tiles * R, xcd_grid_multiple(2)) * xcd_grid_multiple(2));
+}
+
+template <class VT>
+tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, double a, double b, const VT *r,
+                     int32_t R, int32_t M, char *work, double *mu, hipStream_t s, const VT *start, const VT *left) {
+    const TilePlan &tp = pl.tile;
+    const bool pair = left != nullptr, dbl = pl.cfg.doubling != 0;
+    const int n_start = pl.n_start;
+    const int64_t n = h->n_rows;
+    const int Rp = pl.Rp;
+    const bool direct = Rp == 1;                   // the row form is the plane
+    VT *r_int = reinterpret_cast<VT *>(work + pl.off_r);
+    VT *T[2] = {reinterpret_cast<VT *>(work + pl.off_a), reinterpret_cast<VT *>(work + pl.off_b)};
+    auto plane = [&](int k) { return reinterpret_cast<VT *>(work + tp.off_planes + k * tp.plane_bytes); };
+    // pairs of vectors (even n, odd n); with one vector the first pair is the state's own
+    VT *P[2][2] = {{direct ? T[0] : plane(0), direct ? T[1] : plane(1)},
+                   {direct ? plane(0) : plane(2), direct ? plane(1) : plane(3)}};
+    VT *rp = direct ? r_int : plane(4), *sp = rp;
+    double *part = reinterpret_cast<double *>(work + tp.off_part);
+    double *l1 = reinterpret_cast<double *>(work + tp.off_l1);
+    const int Rv = pl.Rv, Rout = dbl ? Rv : R;
+    const int n_chunks = (int)ceil_div(run.n_tiles, kReduceChunk);
+    const int32_t *row0 = reinterpret_cast<const int32_t *>(work + tp.off_row0);
+    const unsigned gt = (unsigned)run.n_tiles;
+    const unsigned ge = (unsigned)ceil_div(n * Rp, kThreads);
+
+    if (pair) {
+        if (direct) {
+            rp = const_cast<VT *>(left);
+            sp = const_cast<VT *>(start);
+            k_pair_overlap<VT, 1, 1><<<gt, kThreads, 0, s>>>(left, start, n, 1, gt, part);
+        } else {
+            sp = plane(5);
+            k_tile_prepare<VT, 1, false><<<gt, kThreads, 0, s>>>(start, left, nullptr, row0, n, R, Rp, 0, 0, nullptr,
+                                                                  sp, rp, part);
+        }
+    } else if (n_start == 0) {
+        if (dbl)
+            k_tile_prepare<VT, 0, true><<<gt, kThreads, 0, s>>>(r, nullptr, h->perm, row0, n, R, Rp,
+                                                                 pl.seeded ? 1 : 0, pl.seed, r_int, rp, nullptr, part);
+        else
+            k_tile_prepare<VT, 0, false><<<gt, kThreads, 0, s>>>(r, nullptr, h->perm, row0, n, R, Rp,
+                                                                  pl.seeded ? 1 : 0, pl.seed, r_int, rp, nullptr,
+                                                                  part);
+    } else if (!direct) {
+        k_planes<VT, true><<<ge, kThreads, 0, s>>>(r_int, rp, n, R, Rp);
+        k_planes<VT, true><<<ge, kThreads, 0, s>>>(T[0], P[0][0], n, R, Rp);
+        k_planes<VT, true><<<ge, kThreads, 0, s>>>(T[1], P[0][1], n, R, Rp);
+    }
+    TBK_HIP(hipGetLastError());
+
+    TileArgs<VT> ta = tile_args<VT>(h, pl, run, work, R);
+    ta.r = rp;
+    ta.c1f = (VT)(1.0 / a);
+    ta.c1 = (VT)(2.0 / a);
+    ta.shift = (VT)b;
+    const bool diag = h->has_onsite || b != 0.0;
+    const unsigned grid = tile_grid(run, R);
+    auto reduce = [&](int n0, int count) {
+        dim3 g(n_chunks, count);
+        k_reduce_l1<<<g, kThreads, 0, s>>>(part, run.n_tiles, Rv, Rout, n0, n_chunks, l1);
+    };
+
+    StepTimer &timer = step_timer();
+    const bool timed = timer.on && !pair;
+    bool open = false;
+    if (timed) timer.used = 0;
+    // the steps n0 + 1 .. Mr - 1, dealt evenly to `groups` launches
+    const int n0 = n_start > 0 ? n_start - 1 : 0;       // T_{n0} is the newest vector at hand
+    const int steps = pl.Mr - 1 - n0;
+    const int most = std::min<int64_t>(run.s, run.closed ? tp.reduce_every - 1 : kTileMaxS);
+    const int groups = (int)ceil_div(steps, most);
+    // a fresh run ends in pair 0; a continued one starts there
+    int dst = n_start > 0 ? 1 : (groups - 1) & 1;
+    int batch0 = n_start;          // first row index of the pending batch of partials
+    int at = n0;                   // T_at is the newest vector
+    const VT *cur = n_start > 0 ? P[0][at & 1] : sp;
+    // T_0 of a run that ended at T_1 is r (the sweep leaves no copy of it)
+    const VT *prev = n_start > 2 ? P[0][(at + 1) & 1] : (n_start == 2 ? rp : sp);
+    for (int q = 0; q < groups; ++q) {
+        const int len = steps / groups + (q < steps % groups ? 1 : 0);
+        if (at + 1 + len - batch0 > tp.reduce_every) {
+            if (open) { TBK_HIP(timer.mark(s)); open = false; }
+            reduce(batch0, at + 1 - batch0);
+            batch0 = at + 1;
+        }
+        if (timed && !open) { TBK_HIP(timer.mark(s)); open = true; }
+        if (timed) timer.launches += len;
+        ta.first = at == 0;
+        ta.s = len;
+        ta.cur = cur;
+        ta.prev = prev;
+        const int end = at + len;
+        const bool keep = q + 1 < groups || !(pair || dbl);    // the last group's vectors: only for a run to continue
+        ta.out_cur = keep ? P[dst][end & 1] : nullptr;
+        ta.out_prev = keep ? P[dst][(end + 1) & 1] : nullptr;
+        ta.partial = part + (int64_t)(at + 1 - batch0) * ta.pstride;
+        launch_steps<VT>(tp, diag, dbl, grid, s, ta);
+        cur = ta.out_cur;
+        prev = ta.out_prev;
+        at = end;
+        dst ^= 1;
+    }
+    if (open) TBK_HIP(timer.mark(s));
+    reduce(batch0, pl.Mr - batch0);
+    TBK_HIP(hipGetLastError());
+    if (!pair && !dbl) {           // the state of the run, in row order
+        for (int q = 0; q < 2; ++q) {
+            const VT *x = q ? prev : cur;          // T_at, T_{at-1}
+            VT *y = T[(at + q) & 1];
+            if (!direct) k_planes<VT, false><<<ge, kThreads, 0, s>>>(y, const_cast<VT *>(x), n, R, Rp);
+            else if (x != y)
+                TBK_HIP(hipMemcpyAsync(y, x, sizeof(VT) * 2 * (size_t)n, hipMemcpyDeviceToDevice, s));
+        }
+        TBK_HIP(hipGetLastError());
+    }
+    return finish_run<VT>(h, pl, a, b, R, M, work, mu, s, pair, dbl, 1, l1, n_chunks, timed);
+}
+
+template <class VT>
+void launch_tile_group(const KpmPlan &pl, bool diag, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
+    launch_steps<VT>(pl.tile, diag, false, grid, s, a);
+}
+
+template <class VT>
+void tile_start_planes(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, const VT *r, int32_t R, char *work,
+                       VT *rp, double *part, hipStream_t s) {
+    const int32_t *row0 = reinterpret_cast<const int32_t *>(work + pl.tile.off_row0);
+    k_tile_prepare<VT, 0, false><<<(unsigned)run.n_tiles, kThreads, 0, s>>>(
+        r, nullptr, h->perm, row0, h->n_rows, R, pl.Rp, 0, 0, nullptr, rp, nullptr, part);
+}
+
+#define TBK_TILE_INST(VT)                                                                                              \
+    template tbk_status tile_build<VT>(const tbk_ham *, const KpmPlan &, int, char *, hipStream_t, TileRun &);        \
+    template TileArgs<VT> tile_args<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, char *, int32_t);           \
+    template tbk_status run_tiled<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, double, double, const VT *,   \
+                                      int32_t, int32_t, char *, double *, hipStream_t, const VT *, const VT *);        \
+    template void launch_tile_group<VT>(const KpmPlan &, bool, unsigned, hipStream_t, const TileArgs<VT> &);           \
+    template void tile_start_planes<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, const VT *, int32_t,        \
+                                        char *, VT *, double *, hipStream_t);
+TBK_TILE_INST(float)
+TBK_TILE_INST(double)
+#undef TBK_TILE_INST
+
+}  // namespace tbk

@@ -1,0 +1,35 @@
+// Launch of the tiled recurrence kernels; included by the kpm_tile_inst_*.hip
+// translation units, each of which instantiates some (vector type, width).
+#pragma once
+
+#include "kpm_tile.hpp"
+
+namespace tbk {
+namespace {
+
+template <class VT, int W, int SHAPE, bool DIAG, bool DBL>
+void launch(unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
+    constexpr int NT = tile_threads(SHAPE), K = tile_slots(SHAPE, W, sizeof(VT) == 8);
+    k_tile_steps<VT, NT, K, W, DIAG, DBL><<<grid, NT, 0, s>>>(a);
+}
+
+template <class VT, int W, int SHAPE>
+void launch_shape(bool diag, bool dbl, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
+    if (dbl) diag ? launch<VT, W, SHAPE, true, true>(grid, s, a) : launch<VT, W, SHAPE, false, true>(grid, s, a);
+    else diag ? launch<VT, W, SHAPE, true, false>(grid, s, a) : launch<VT, W, SHAPE, false, false>(grid, s, a);
+}
+
+}  // namespace
+
+template <class VT, int W>
+void launch_tile_steps(const TilePlan &tp, bool diag, bool dbl, unsigned grid, hipStream_t s,
+                       const TileArgs<VT> &a) {
+    // large_diag differs from large where its rows per thread do
+    constexpr bool own = tile_slots(kTileLargeDiag, W, sizeof(VT) == 8) != tile_slots(kTileLarge, W, sizeof(VT) == 8);
+    if (tp.shape == kTileWhole) launch_shape<VT, W, kTileWhole>(diag, dbl, grid, s, a);
+    else if (tp.shape == kTileLargeDiag && own) launch_shape<VT, W, kTileLargeDiag>(diag, dbl, grid, s, a);
+    else if (sizeof(VT) == 4 && tp.shape == kTileSmall) launch_shape<VT, W, sizeof(VT) == 4 ? kTileSmall : kTileLarge>(diag, dbl, grid, s, a);
+    else launch_shape<VT, W, kTileLarge>(diag, dbl, grid, s, a);
+}
+
+}  // namespace tbk

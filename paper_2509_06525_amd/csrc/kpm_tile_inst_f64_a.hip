@@ -1,0 +1,7 @@
+// Instances of the tiled recurrence for complex-double vectors, rows of up to 3 entries (kpm_tile.hpp).
+#include "kpm_tile_inst.hpp"
+
+namespace tbk {
+template void launch_tile_steps<double, 3>(const TilePlan &, bool, bool, unsigned, hipStream_t,
+                                        const TileArgs<double> &);
+}  // namespace tbk

@@ -342,8 +342,10 @@ struct LsqtLayout {
     size_t off_mu = 0, total = 0;       // a batch's moments [R B][M]
 };
 
+// tiled = false leaves out the workspace of the tiled recurrence (a caller's
+// buffer may be sized for the sweep per step alone).
 tbk_status make_layout(const tbk_ham *h, int32_t R, int32_t M, int32_t precision, int32_t time_batch,
-                       const tbk_kpm_config *cfg, LsqtLayout &ly) {
+                       const tbk_kpm_config *cfg, bool tiled, LsqtLayout &ly) {
     TBK_CHECK(R >= 1 && R <= 64, TBK_ERR_INVALID_ARG, "R = %d outside [1, 64]", R);
     TBK_CHECK(time_batch >= 0, TBK_ERR_INVALID_ARG, "time_batch = %d < 0", time_batch);
     ly.B = time_batch_of(R, time_batch);
@@ -361,7 +363,8 @@ tbk_status make_layout(const tbk_ham *h, int32_t R, int32_t M, int32_t precision
     const size_t elem = precision == TBK_PREC_C32 ? sizeof(float) : sizeof(double);
     auto a256 = [](size_t x) { return (x + 255) & ~(size_t)255; };
     ly.vec = a256((size_t)h->n_rows * pad_vectors(R) * 2 * elem);
-    ly.off_vec = a256(ly.pl.total);
+    ly.pl.tile.on = ly.pl.tile.on && tiled;
+    ly.off_vec = a256(ly.pl.tile.on ? ly.pl.tile.total : ly.pl.total);
     ly.off_batch = ly.off_vec + 9 * ly.vec;
     ly.bvec = a256((size_t)h->n_rows * ly.pl.Rp * 2 * elem);
     ly.off_mu = ly.off_batch + 2 * ly.bvec;
@@ -465,6 +468,11 @@ tbk_status run_vac(const tbk_ham *h, const VT *vx, double a, double b, const VT 
     const int64_t nb_el = 2 * n * (int64_t)Rb;
     const unsigned gz = (unsigned)ceil_div(nb_el, kLsqtThreads);
     const unsigned gi = (unsigned)ceil_div(n * R, kLsqtThreads);
+    TileRun tiles;                  // listed once for the recurrences of all batches
+    if (pl.tile.on) {
+        tbk_status st = build_tiles(h, pl, precision, work, s, tiles);
+        if (st != TBK_OK) return st;
+    }
     for (int32_t j0 = 0; j0 < n_t; j0 += ly.B) {
         const int32_t nb = std::min(ly.B, n_t - j0);
         if (nb * R < Rb) {
@@ -481,7 +489,8 @@ tbk_status run_vac(const tbk_ham *h, const VT *vx, double a, double b, const VT 
                 if (st != TBK_OK) return st;
             }
         }
-        tbk_status st = run_plan(h, pl, a, b, nullptr, R * ly.B, M, precision, work, mub, s, start, left);
+        tbk_status st = run_plan(h, pl, a, b, nullptr, R * ly.B, M, precision, work, mub, s, start, left,
+                                 &tiles);
         if (st != TBK_OK) return st;
         TBK_HIP(hipMemcpyAsync(nu + (int64_t)j0 * R * M, mub, sizeof(double) * (size_t)nb * R * M,
                                hipMemcpyDeviceToDevice, s));
@@ -559,7 +568,7 @@ extern "C" tbk_status lsqt_workspace_size(const tbk_ham *h, int32_t R, int32_t M
     clear_error();
     TBK_CHECK(bytes != nullptr, TBK_ERR_INVALID_ARG, "bytes is NULL");
     LsqtLayout ly;
-    tbk_status st = make_layout(h, R, M, precision, time_batch, cfg, ly);
+    tbk_status st = make_layout(h, R, M, precision, time_batch, cfg, true, ly);
     if (st != TBK_OK) return st;
     *bytes = (int64_t)ly.total;
     return TBK_OK;
@@ -578,8 +587,12 @@ extern "C" tbk_status lsqt_vac_moments(const tbk_ham *h, const void *vx, double 
     if (n_cheb <= 0) n_cheb = default_terms(a * dt / kHbar);
     TBK_CHECK(n_cheb <= 100000, TBK_ERR_INVALID_ARG, "n_cheb = %d too large", n_cheb);
     LsqtLayout ly;
-    tbk_status st = make_layout(h, R, M, precision, time_batch, cfg, ly);
+    tbk_status st = make_layout(h, R, M, precision, time_batch, cfg, true, ly);
     if (st != TBK_OK) return st;
+    if (work_bytes < (int64_t)ly.total) {
+        st = make_layout(h, R, M, precision, time_batch, cfg, false, ly);
+        if (st != TBK_OK) return st;
+    }
     TBK_CHECK(work_bytes >= (int64_t)ly.total, TBK_ERR_BUFFER_TOO_SMALL, "work has %lld bytes, needs %lld",
               (long long)work_bytes, (long long)ly.total);
     TBK_CHECK(((uintptr_t)work & 255) == 0, TBK_ERR_INVALID_ARG, "work is not 256-byte aligned");

@@ -1,0 +1,175 @@
+"""Several recurrence steps per launch on tiles (kpm_moments, kpm_moments_batched,
+VAC) against the sweep of one step per launch, through the C ABI.
+
+Both forms form every value of T_n from the same operands in the same order, so
+the kept vectors of a run are equal bit for bit; the moments differ in the order
+of double sums over N terms: at most about 2 eps sqrt(N) of mu_0 = N apart, held
+to 1e-13 N.  The sweep runs when the workspace has room for it alone, which is
+the size reported for a persistent configuration (a form tiles are not offered
+for).  Sizes sit at the edges of a tile (one tile, just over one, a last tile of
+few rows), rows of 3 to 6 entries, both orders of rows and an order without
+locality (no tile's halo fits: the sweep runs on either workspace).
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2509_06525_amd import synth, tbkpm
+from tests import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+STATE = 1024                        # bytes of the run's record ahead of r, T_a, T_b
+
+
+def _sweep_size(H, R, M, prec, doubling=0):
+    cfg = tbkpm.with_fields(tbkpm.default_config(H, R, prec), persistent=1, doubling=doubling)
+    return tbkpm.workspace_size(H, R, M, prec, cfg)
+
+
+def _runs(H, R, M, prec, seed, doubling=0):
+    """(moments, kept vectors) of the tiled form and of the sweep."""
+    a, b = H.scale()
+    n = H.n_rows
+    r = tbkpm.random_phase(seed, n, R, prec)
+    cfg = tbkpm.with_doubling(tbkpm.default_config(H, R, prec), doubling)
+    sizes = (tbkpm.workspace_size(H, R, M, prec, cfg), _sweep_size(H, R, M, prec, doubling))
+    assert sizes[0] > sizes[1]
+    out = []
+    Rp = 1
+    while Rp < R:
+        Rp *= 2
+    vb = n * Rp * (8 if prec == "c32" else 16)
+    pitch = (vb + 255) // 256 * 256
+    for nbytes in sizes:
+        work = torch.zeros(nbytes, dtype=torch.uint8, device=G.DEV)
+        mu = tbkpm.kpm_moments(H, a, b, r, M, prec, work=work, config=cfg)
+        kept = [work[STATE + k * pitch: STATE + k * pitch + vb].clone() for k in range(3)]
+        out.append((mu, kept))
+    return out, (a, b, r)
+
+
+def _check(H, R, M, prec, seed=3, doubling=0):
+    (tiled, sweep), args = _runs(H, R, M, prec, seed, doubling)
+    assert (tiled[0] - sweep[0]).abs().max().item() <= 1e-13 * H.n_rows
+    if not doubling:
+        for k, (x, y) in enumerate(zip(tiled[1], sweep[1])):
+            assert torch.equal(x, y) or (k == 1 and M == 2)      # T_0 of a run that ends at T_1 is r alone
+    return tiled[0], args
+
+
+@pytest.mark.parametrize("nx,ny", [(4, 6), (24, 24), (31, 40), (32, 39), (35, 37), (83, 91), (250, 181)])
+@pytest.mark.parametrize("fmt,prec,slice,R", [("sell_f32", "c32", 256, 1), ("sell_f32", "c32", 16, 3),
+                                              ("sell_f64", "f64", 64, 2), ("csr_f64", "f64", 1, 1),
+                                              ("sell_f32", "c32", 1024, 8)])
+def test_tiles_equal_the_sweep_at_tile_edges(nx, ny, fmt, prec, slice, R):
+    s = synth.graphene_sheet(nx, ny, 0.05, 11)
+    _check(G.build(s, fmt=fmt, slice=slice), R, 75, prec)
+
+
+@pytest.mark.parametrize("sigma", [0.0, 0.09, 0.13, 0.16])
+@pytest.mark.parametrize("fmt,prec,R,stripes", [("sell_f32", "c32", 1, True), ("sell_f32", "c32", 5, False),
+                                                ("sell_f32", "c32", 16, True), ("sell_f64", "f64", 4, True)])
+def test_tiles_equal_the_sweep_for_every_width(sigma, fmt, prec, R, stripes):
+    """Widths 3 to 6 with and without onsite energies, large and small tiles."""
+    s = synth.hbn_stripes(190, 120, 7, sigma, 5) if stripes else synth.graphene_sheet(190, 120, sigma, 5)
+    H = G.build(s, fmt=fmt, slice=64)
+    for M in (2, 3, 66):
+        _check(H, R, M, prec)
+
+
+@pytest.mark.parametrize("fmt,prec,R,M", [("sell_f32", "c32", 1, 64), ("sell_f32", "c32", 3, 65), ("sell_f64", "f64", 2, 90)])
+@pytest.mark.parametrize("nx,ny", [(20, 30), (120, 130)])
+def test_doubling_on_tiles(fmt, prec, R, M, nx, ny):
+    s = synth.hbn_stripes(nx, ny, 5, 0.05, 9)
+    mu, (a, b, r) = _check(G.build(s, fmt=fmt, slice=32), R, M, prec, doubling=1)
+    if prec == "f64" and nx == 20:
+        csr, _ = O.hamiltonian(s.pos, s.species, s.box, s.periodic, s.onsite, s.t_pair)
+        mo, _ = O.kpm_moments(csr, a, b, r.cpu().numpy(), M)
+        assert np.abs(mu.cpu().numpy() - mo).max() <= 1e-10 * s.n
+
+
+@pytest.mark.parametrize("order", ["caller", "shuffled"])
+def test_row_orders(order):
+    """The caller's order keeps neighbours near (tiles run); a shuffled one does not,
+    and the sweep runs whatever the workspace."""
+    s = synth.graphene_sheet(100, 90, 0.05, 2)
+    if order == "shuffled":
+        p = np.random.default_rng(1).permutation(s.n)
+        s.pos, s.species = s.pos[p].copy(), s.species[p].copy()
+    H = G.build(s, fmt="sell_f64", slice=64, reorder=False)
+    mu, (a, b, r) = _check(H, 2, 50, "f64")
+    csr, _ = O.hamiltonian(s.pos, s.species, s.box, s.periodic, s.onsite, s.t_pair)
+    mo, _ = O.kpm_moments(csr, a, b, r.cpu().numpy(), 50)
+    assert np.abs(mu.cpu().numpy() - mo).max() <= 1e-10 * s.n
+
+
+@pytest.mark.parametrize("k0,k1", [(40, 81), (9, 10), (2, 67)])
+@pytest.mark.parametrize("R", [1, 3])
+def test_either_form_continues_the_other(k0, k1, R):
+    """A run split over both forms: the vectors agree bit for bit, so the second part's
+    moments are those of its own form's one-shot run."""
+    s = synth.graphene_sheet(110, 100, 0.05, 4)
+    H = G.build(s, fmt="sell_f32", slice=64)
+    a, b = H.scale()
+    r = tbkpm.random_phase(1, s.n, R, "c32")
+    big, small = tbkpm.workspace_size(H, R, k1, "c32"), _sweep_size(H, R, k1, "c32")
+    one = tbkpm.kpm_moments(H, a, b, r, k1, "c32")
+    for first, second in ((big, small), (small, big), (big, big)):
+        work = torch.zeros(big, dtype=torch.uint8, device=G.DEV)
+        mu = torch.empty((R, k0), dtype=torch.float64, device=G.DEV)
+        tbkpm.kpm_moments(H, a, b, r, k0, "c32", work=work[:first], mu=mu)
+        rest = torch.empty((R, k1), dtype=torch.float64, device=G.DEV)
+        tbkpm.kpm_moments(H, a, b, None, k1, "c32", work=work[:second], mu=rest, n_start=k0, R=R)
+        got = torch.cat([mu, rest[:, k0:]], 1)
+        assert (got - one).abs().max().item() <= 1e-13 * s.n
+        if first == second:
+            assert torch.equal(got, one)
+
+
+@pytest.mark.parametrize("fmt,prec,R", [("sell_f32", "c32", 8), ("sell_f32", "c32", 1), ("sell_f64", "f64", 3)])
+@pytest.mark.parametrize("dims", [((5, 7), (9, 8)), ((6, 8), (40, 44), (90, 80), (31, 40))])
+def test_stacked_tiles_equal_the_stacked_sweep(fmt, prec, R, dims):
+    """Structures of one tile and of several; each against its own run, too."""
+    snaps = [synth.graphene_sheet(nx, ny, 0.04 + 0.02 * k, k) for k, (nx, ny) in enumerate(dims)]
+    pos, sp, seg, boxes = synth.stack(snaps)
+    H = tbkpm.build_hamiltonian_batched(G.to_dev(pos), G.to_dev(sp), seg, boxes, (1, 1, 0), [0.0], [[-2.7]],
+                                        fmt=fmt, slice=32)
+    a, b = H.scales()
+    n, M = int(seg[-1]), 60
+    r = tbkpm.random_phase(2, n, R, prec)
+    cfg = tbkpm.default_config(H, R, prec)
+    tiled = tbkpm.kpm_moments_batched(H, a, b, r, M, prec, config=cfg)
+    full = tbkpm.workspace_size_batched(H, R, M, prec, cfg)
+    Rp = 1
+    while Rp < R:
+        Rp *= 2
+    # the sweep's size lies below the vectors' and partials' (3 vectors, <= 60 steps of tiles) and the full size
+    vec = (n * Rp * (8 if prec == "c32" else 16) + 255) // 256 * 256
+    tiles = sum(-(-s.n // (256 * cfg.vectors_per_thread // Rp)) for s in snaps)
+    sweep = 3 * vec + M * tiles * Rp * 8 + 12 * tiles + 64 * len(dims) + 8192
+    assert sweep < full
+    work = torch.zeros(sweep, dtype=torch.uint8, device=G.DEV)
+    swept = tbkpm.kpm_moments_batched(H, a, b, r, M, prec, work=work, config=cfg)
+    assert (tiled - swept).abs().max().item() <= 1e-13 * n
+    for k, s in enumerate(snaps):
+        Hk = G.build(s, fmt=fmt, slice=32)
+        mk = tbkpm.kpm_moments(Hk, a[k], b[k], r[seg[k]:seg[k + 1]].contiguous(), M, prec)
+        assert (tiled[k] - mk).abs().max().item() <= 1e-13 * s.n * (1 if prec == "f64" else 1e7)
+
+
+def test_vac_on_tiles_equals_the_sweep():
+    s = synth.graphene_sheet(70, 60, 0.05, 8)
+    H = G.build(s, fmt="sell_f64", slice=64)
+    a, b = H.scale()
+    vx = tbkpm.build_velocity(H, G.to_dev(s.pos), s.box, s.periodic, 0)
+    r = tbkpm.random_phase(5, s.n, 1, "f64")
+    M, n_t = 40, 21
+    nu = tbkpm.vac_moments(H, vx, a, b, r, M, n_t, 0.1, precision="f64")
+    # nine vector blocks, the batch's start and left vectors and its moments after the sweep's workspace
+    vec = (s.n * 16 + 255) // 256 * 256
+    small = _sweep_size(H, 16, M, "f64") + 9 * vec + 2 * 16 * vec + (16 * M * 8 + 255) // 256 * 256 + 256
+    work = torch.zeros(small, dtype=torch.uint8, device=G.DEV)
+    nu2 = tbkpm.vac_moments(H, vx, a, b, r, M, n_t, 0.1, precision="f64", work=work)
+    scale = nu.abs().max().item()
+    assert (nu - nu2).abs().max().item() <= 1e-13 * max(scale, s.n)
