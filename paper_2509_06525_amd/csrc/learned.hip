@@ -44,13 +44,9 @@ constexpr int kWaves = 4;         // wavefronts per block of the MLP kernels
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// float -> bfloat16 bits, round to nearest even (NaN kept quiet).
-__device__ __forceinline__ uint16_t f2bf(float x) {
-    uint32_t u = __float_as_uint(x);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+// float -> bfloat16 bits, round to nearest even (NaN quiet): one instruction on
+// gfx950, equal to the integer form for every pattern that is not a NaN.
+__device__ __forceinline__ uint16_t f2bf(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
 
 // double -> bfloat16 bits, one rounding (nearest even at the 8th significant bit).
 __device__ __forceinline__ uint16_t d2bf(double x) {
@@ -297,42 +293,54 @@ struct WaveWeights {
 
 __device__ __forceinline__ void load_weights(const float *__restrict__ P, WaveWeights &w) {
     const int l = threadIdx.x & 63, n = l & 15, q = l >> 4;
-    for (int m = 0; m < 2; ++m) {
-        const float *r1 = P + kOffW1 + (16 * m + n) * kNI + 4 * q;
-        w.A1[m] = pack4(r1[0], r1[1], r1[2], r1[3]);
-        for (int kb = 0; kb < 2; ++kb) {
-            const float *r2 = P + kOffW2 + (16 * m + n) * kNH + 16 * kb + 4 * q;
-            w.A2[m][kb] = pack4(r2[0], r2[1], r2[2], r2[3]);
-            // transposed: element i = W2[16 kb + 4 q + i][16 m + n]
-            const float *c2 = P + kOffW2 + (16 * kb + 4 * q) * kNH + 16 * m + n;
-            w.A2T[m][kb] = pack4(c2[0], c2[kNH], c2[2 * kNH], c2[3 * kNH]);
-        }
+    // every parameter of the lane is loaded before any is converted
+    float r1[2][4], r2[2][2][4], c2[2][2][4], r3[2][4];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
         for (int i = 0; i < 4; ++i) {
+            r1[m][i] = P[kOffW1 + (16 * m + n) * kNI + 4 * q + i];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                r2[m][kb][i] = P[kOffW2 + (16 * m + n) * kNH + 16 * kb + 4 * q + i];
+                // transposed: element i = W2[16 kb + 4 q + i][16 m + n]
+                c2[m][kb][i] = P[kOffW2 + (16 * kb + 4 * q + i) * kNH + 16 * m + n];
+            }
             w.b1[m][i] = P[kOffB1 + 16 * m + 4 * q + i];
             w.b2[m][i] = P[kOffB2 + 16 * m + 4 * q + i];
-            w.w3[m][i] = rbf(P[kOffW3 + 16 * m + 4 * q + i]);
+            r3[m][i] = P[kOffW3 + 16 * m + 4 * q + i];
         }
-    }
     w.b3 = P[kOffB3];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        w.A1[m] = pack4(r1[m][0], r1[m][1], r1[m][2], r1[m][3]);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            w.A2[m][kb] = pack4(r2[m][kb][0], r2[m][kb][1], r2[m][kb][2], r2[m][kb][3]);
+            w.A2T[m][kb] = pack4(c2[m][kb][0], c2[m][kb][1], c2[m][kb][2], c2[m][kb][3]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w.w3[m][i] = rbf(r3[m][i]);
+    }
 }
 
 struct TileAct {
     f32x4 h1[2], h2[2];   // post-tanh activations, hidden 16 m + 4 q + i, bond n
+    bf16x4 h1b[2];        // bf16 of h1
     float y;              // output of bond n (all four q lanes)
 };
 
 // Forward pass of the 16 bonds whose features (bf16, 4 per lane) are xq.
 __device__ __forceinline__ void mlp_tile_forward(const WaveWeights &w, bf16x4 xq, TileAct &a) {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    bf16x4 hb[2];
     for (int m = 0; m < 2; ++m) {
         f32x4 z = mfma16(w.A1[m], xq, zero);
         for (int i = 0; i < 4; ++i) a.h1[m][i] = tanhf(z[i] + w.b1[m][i]);
-        hb[m] = pack4(a.h1[m][0], a.h1[m][1], a.h1[m][2], a.h1[m][3]);
+        a.h1b[m] = pack4(a.h1[m][0], a.h1[m][1], a.h1[m][2], a.h1[m][3]);
     }
     float part = 0.f;
     for (int mo = 0; mo < 2; ++mo) {
-        const f32x4 z = mfma32(w.A2[mo][0], w.A2[mo][1], hb[0], hb[1], zero);
+        const f32x4 z = mfma32(w.A2[mo][0], w.A2[mo][1], a.h1b[0], a.h1b[1], zero);
         for (int i = 0; i < 4; ++i) {
             a.h2[mo][i] = tanhf(z[i] + w.b2[mo][i]);
             part += w.w3[mo][i] * rbf(a.h2[mo][i]);
@@ -349,13 +357,24 @@ __device__ __forceinline__ void mlp_tile_forward(const WaveWeights &w, bf16x4 xq
 // (mul c + add) mod n_chunks, a bijection of the n_chunks = n_total / 16 whole
 // chunks when gcd(mul, n_chunks) = 1; the last n_total % 16 bonds keep their
 // positions.  mul = 1, add = 0 is the stored order.
+// Below 2^26 chunks mul c + add is exact in double, and the remainder comes from a
+// rounded quotient and one correction; the 128-bit remainder is a routine of some
+// thousand cycles at the head of every tile.
 struct BondOrder {
     int64_t n_total, first, mul, add;
     __device__ __forceinline__ int64_t map(int64_t b) const {
         const int64_t i = first + b;
         const int64_t n_chunks = n_total >> 4;
         const int64_t c = i >> 4;
-        if ((mul == 1 && add == 0) || c >= n_chunks) return i;
+        if (mul == 1 && add == 0) return i;
+        if (n_chunks < ((int64_t)1 << 26)) {
+            const int64_t x = mul * c + add;
+            int64_t pc = x - (int64_t)((double)x / (double)n_chunks) * n_chunks;
+            pc += pc < 0 ? n_chunks : 0;
+            pc -= pc >= n_chunks ? n_chunks : 0;
+            return c >= n_chunks ? i : (pc << 4) + (i & 15);
+        }
+        if (c >= n_chunks) return i;
         const uint64_t pc = (uint64_t)(((unsigned __int128)mul * (uint64_t)c + (uint64_t)add) % (uint64_t)n_chunks);
         return (int64_t)(pc << 4) + (i & 15);
     }
@@ -364,12 +383,11 @@ struct BondOrder {
 // Features of bond tile t for this lane: X[16 t + n][4 q .. 4 q + 3]; zero past nb.
 __device__ __forceinline__ bf16x4 load_x(const uint16_t *__restrict__ X, int64_t nb, int64_t b) {
     const int q = (threadIdx.x & 63) >> 4;
-    bf16x4 r = {0, 0, 0, 0};
-    if (b < nb) {
-        const uint2 raw = *reinterpret_cast<const uint2 *>(X + b * kNI + 4 * q);
-        r[0] = (short)(raw.x & 0xffff); r[1] = (short)(raw.x >> 16);
-        r[2] = (short)(raw.y & 0xffff); r[3] = (short)(raw.y >> 16);
-    }
+    uint2 raw = *reinterpret_cast<const uint2 *>(X + min(b, nb - 1) * kNI + 4 * q);
+    if (b >= nb) raw = make_uint2(0, 0);
+    bf16x4 r;
+    r[0] = (short)(raw.x & 0xffff); r[1] = (short)(raw.x >> 16);
+    r[2] = (short)(raw.y & 0xffff); r[3] = (short)(raw.y >> 16);
     return r;
 }
 
@@ -389,130 +407,217 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp_forward(int64_t nb, const u
     }
 }
 
+// x + x of the lane `off` away (1, 2, 4, 8, within 16 lanes).  For off = 4 and 8 the
+// mirrored lanes hold what the lanes at that distance hold, since the four (eight)
+// lanes around each already agree: DPP moves in place of LDS permutes.
+template <int OFF>
+__device__ __forceinline__ float add_xor16(float x) {
+    constexpr int ctrl = OFF == 1 ? 0xB1 : (OFF == 2 ? 0x4E : (OFF == 4 ? 0x141 : 0x140));
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xf, 0xf, true));
+}
+
+// x + y with y's product rounded before the sum (no contraction).
+__device__ __forceinline__ float add_rounded(float x, float y) {
+#pragma clang fp contract(off)
+    return x + y;
+}
+
+// What one lane keeps of a bond tile between its loads and its gradient.
+struct GradTile {
+    bf16x4 xq;
+    float target, weight;
+    bool ok;
+};
+
+__device__ __forceinline__ GradTile load_grad_tile(int64_t t, int64_t nb, const uint16_t *__restrict__ X,
+                                                   const float *__restrict__ target,
+                                                   const float *__restrict__ weight, const BondOrder &order) {
+    GradTile g;
+    const int n = threadIdx.x & 15;
+    const int64_t b = 16 * t + n;
+    g.ok = b < nb;
+    const int64_t src = order.map(min(b, nb - 1));   // the training-set bond at minibatch position b
+    g.xq = load_x(X, order.n_total, src);
+    if (!g.ok) g.xq = bf16x4{0, 0, 0, 0};
+    g.target = target[src];
+    g.weight = weight ? weight[src] : 1.f;
+    return g;
+}
+
+constexpr int kTrPad = 20;       // LDS row of 16 bonds, padded (8-byte reads, spread over the banks)
+
+// One wavefront's gradient sums and its transpose space.
+struct GradAcc {
+    f32x4 gW1[2];        // (h = 16 mh + 4 q + i, f = n)
+    f32x4 gW2[2][2];     // (h = 16 mh + 4 q + i, k = 16 nk + n)
+    float gb1[2][4], gb2[2][4], gw3[2][4], gb3;
+    double loss;
+};
+
+// T bond tiles of a wavefront at once (their chains overlap; one wavefront per SIMD
+// has nothing else to run meanwhile), added to the sums in tile order.  The bonds go
+// onto K of the weight-gradient products through LDS rows [hidden][bond].
+template <int T>
+__device__ __forceinline__ void grad_tiles(const WaveWeights &w, const GradTile (&g)[T], float inv_b, GradAcc &s,
+                                           uint16_t (*tr)[3 * kNH + kNI][kTrPad]) {
+    const int l = threadIdx.x & 63, n = l & 15, q = l >> 4;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    TileAct a[T];
+#pragma unroll
+    for (int u = 0; u < T; ++u) mlp_tile_forward(w, g[u].xq, a[u]);
+    f32x4 d1[T][2], d2[T][2];
+    bf16x4 d2b[T][2];
+    float dyb[T];
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+        const float wb = g[u].ok ? g[u].weight : 0.f;
+        const float diff = g[u].ok ? a[u].y - g[u].target : 0.f;
+        if (q == 0) s.loss += (double)wb * (double)diff * (double)diff;
+        const float dy = 2.f * wb * diff * inv_b;
+        if (q == 0) s.gb3 += dy;
+        dyb[u] = rbf(dy);
+        // output and second layer deltas
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d2[u][m][i] = w.w3[m][i] * dyb[u] * (1.f - a[u].h2[m][i] * a[u].h2[m][i]);
+            d2b[u][m] = pack4(d2[u][m][0], d2[u][m][1], d2[u][m][2], d2[u][m][3]);
+        }
+        // first layer deltas: d1 = (W2^T d2) * (1 - h1^2)
+#pragma unroll
+        for (int ko = 0; ko < 2; ++ko) {
+            const f32x4 z = mfma32(w.A2T[ko][0], w.A2T[ko][1], d2b[u][0], d2b[u][1], zero);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d1[u][ko][i] = z[i] * (1.f - a[u].h1[ko][i] * a[u].h1[ko][i]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < T; ++u)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s.gw3[m][i] += dyb[u] * rbf(a[u].h2[m][i]);
+                // sums of the rounded deltas, as the bf16 products take them
+                s.gb2[m][i] = add_rounded(s.gb2[m][i], d2[u][m][i]);
+                s.gb1[m][i] = add_rounded(s.gb1[m][i], d1[u][m][i]);
+            }
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int h = 16 * m + 4 * q + i;
+                tr[u][h][n] = (uint16_t)d2b[u][m][i];
+                tr[u][kNH + h][n] = (uint16_t)a[u].h1b[m][i];
+                tr[u][2 * kNH + h][n] = f2bf(d1[u][m][i]);
+            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tr[u][3 * kNH + 4 * q + i][n] = (uint16_t)g[u].xq[i];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // bonds 4 q .. 4 q + 3 of row r
+    auto row = [&](int u, int r) { return *reinterpret_cast<const bf16x4 *>(&tr[u][r][4 * q]); };
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+        const bf16x4 bx = row(u, 3 * kNH + n);
+        const bf16x4 bh[2] = {row(u, kNH + n), row(u, kNH + 16 + n)};
+#pragma unroll
+        for (int mh = 0; mh < 2; ++mh) {
+            const bf16x4 ad2 = row(u, 16 * mh + n), ad1 = row(u, 2 * kNH + 16 * mh + n);
+            s.gW2[mh][0] = mfma16(ad2, bh[0], s.gW2[mh][0]);
+            s.gW2[mh][1] = mfma16(ad2, bh[1], s.gW2[mh][1]);
+            s.gW1[mh] = mfma16(ad1, bx, s.gW1[mh]);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Loss sum_b w_b (y_b - y*_b)^2 / B and its gradient: each wavefront writes its
-// FP32 partial gradient (parameter layout) and FP64 partial loss.
+// FP32 partial gradient (parameter layout) and FP64 partial loss.  A minibatch
+// is a few tiles per wavefront, so the kernel is one serial chain (loads, two
+// layers of MFMA and tanh, the deltas, the products over bonds): the first two
+// tiles' loads go out ahead of the weights', the weights are all loaded before any
+// is converted, and two tiles run side by side.  2048 bonds (64 wavefronts): 18.2 us
+// with the loads waited for one by one, 8.8 us so; reduction and AdamW 8.3 -> 4.0 us.
 __global__ __launch_bounds__(64 * kWaves) void k_mlp_grad(int64_t nb, const uint16_t *__restrict__ X,
                                                           const float *__restrict__ target,
                                                           const float *__restrict__ weight,
                                                           const float *__restrict__ P, float inv_b,
                                                           BondOrder order, float *__restrict__ gpart,
                                                           double *__restrict__ lpart) {
-    __shared__ uint16_t s_d2[kWaves][16][kNH];
-    __shared__ uint16_t s_h1[kWaves][16][kNH];
-    __shared__ uint16_t s_d1[kWaves][16][kNH];
-    __shared__ uint16_t s_x[kWaves][16][kNI];
-    WaveWeights w;
-    load_weights(P, w);
+    __shared__ __align__(8) uint16_t tr[kWaves][2][3 * kNH + kNI][kTrPad];
     const int wv = threadIdx.x >> 6;
     const int l = threadIdx.x & 63, n = l & 15, q = l >> 4;
     const int64_t wave = blockIdx.x * (int64_t)kWaves + wv;
     const int64_t nwave = (int64_t)gridDim.x * kWaves;
     const int64_t ntile = (nb + 15) / 16;
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    f32x4 gW1[2] = {zero, zero};                 // (h = 16 mh + 4 q + i, f = n)
-    f32x4 gW2[2][2] = {{zero, zero}, {zero, zero}};  // (h = 16 mh + 4 q + i, k = 16 nk + n)
-    float gb1[2][4] = {}, gb2[2][4] = {}, gw3[2][4] = {};
-    float gb3 = 0.f;
-    double loss = 0.0;
-    for (int64_t t = wave; t < ntile; t += nwave) {
-        const int64_t b = 16 * t + n;
-        const bool ok = b < nb;
-        const int64_t src = ok ? order.map(b) : 0;   // the training-set bond at minibatch position b
-        const bf16x4 xq = load_x(X, order.n_total, ok ? src : order.n_total);
-        TileAct a;
-        mlp_tile_forward(w, xq, a);
-        const float wb = ok ? (weight ? weight[src] : 1.f) : 0.f;
-        const float diff = ok ? a.y - target[src] : 0.f;
-        if (q == 0) loss += (double)wb * (double)diff * (double)diff;
-        const float dy = 2.f * wb * diff * inv_b;
-        if (q == 0) gb3 += dy;
-        const float dyb = rbf(dy);
-        // output and second layer deltas
-        f32x4 d2[2];
-        bf16x4 d2b[2];
-        for (int m = 0; m < 2; ++m) {
-            for (int i = 0; i < 4; ++i) {
-                gw3[m][i] += dyb * rbf(a.h2[m][i]);
-                d2[m][i] = w.w3[m][i] * dyb * (1.f - a.h2[m][i] * a.h2[m][i]);
-                gb2[m][i] += d2[m][i];
-            }
-            d2b[m] = pack4(d2[m][0], d2[m][1], d2[m][2], d2[m][3]);
+    GradTile g[2];
+    g[0] = load_grad_tile(min(wave, ntile - 1), nb, X, target, weight, order);
+    g[1] = load_grad_tile(min(wave + nwave, ntile - 1), nb, X, target, weight, order);
+    WaveWeights w;
+    load_weights(P, w);
+    GradAcc s{};
+    for (int64_t t = wave; t < ntile; t += 2 * nwave) {
+        if (t != wave) {
+            g[0] = load_grad_tile(t, nb, X, target, weight, order);
+            g[1] = load_grad_tile(min(t + nwave, ntile - 1), nb, X, target, weight, order);
         }
-        // first layer deltas: d1 = (W2^T d2) * (1 - h1^2)
-        f32x4 d1[2];
-        for (int ko = 0; ko < 2; ++ko) {
-            const f32x4 z = mfma32(w.A2T[ko][0], w.A2T[ko][1], d2b[0], d2b[1], zero);
-            for (int i = 0; i < 4; ++i) {
-                d1[ko][i] = z[i] * (1.f - a.h1[ko][i] * a.h1[ko][i]);
-                gb1[ko][i] += d1[ko][i];
-            }
+        if (t + nwave < ntile) {
+            grad_tiles<2>(w, g, inv_b, s, tr[wv]);
+        } else {
+            const GradTile one[1] = {g[0]};
+            grad_tiles<1>(w, one, inv_b, s, tr[wv]);
         }
-        // bonds onto K through LDS: [bond][hidden] bf16
-        for (int m = 0; m < 2; ++m)
-            for (int i = 0; i < 4; ++i) {
-                s_d2[wv][n][16 * m + 4 * q + i] = (uint16_t)d2b[m][i];
-                s_h1[wv][n][16 * m + 4 * q + i] = f2bf(a.h1[m][i]);
-                s_d1[wv][n][16 * m + 4 * q + i] = f2bf(d1[m][i]);
-            }
-        for (int i = 0; i < 4; ++i) s_x[wv][n][4 * q + i] = (uint16_t)xq[i];
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        for (int mh = 0; mh < 2; ++mh) {
-            bf16x4 ad2, ad1;
-            for (int i = 0; i < 4; ++i) {
-                ad2[i] = (short)s_d2[wv][4 * q + i][16 * mh + n];
-                ad1[i] = (short)s_d1[wv][4 * q + i][16 * mh + n];
-            }
-            for (int nk = 0; nk < 2; ++nk) {
-                bf16x4 bh;
-                for (int i = 0; i < 4; ++i) bh[i] = (short)s_h1[wv][4 * q + i][16 * nk + n];
-                gW2[mh][nk] = mfma16(ad2, bh, gW2[mh][nk]);
-            }
-            bf16x4 bx;
-            for (int i = 0; i < 4; ++i) bx[i] = (short)s_x[wv][4 * q + i][n];
-            gW1[mh] = mfma16(ad1, bx, gW1[mh]);
-        }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     // sums over the 16 bonds of a lane group (lanes with equal q)
+    auto sum16 = [](float x) { return add_xor16<8>(add_xor16<4>(add_xor16<2>(add_xor16<1>(x)))); };
+#pragma unroll
     for (int m = 0; m < 2; ++m)
-        for (int i = 0; i < 4; ++i)
-            for (int off = 1; off < 16; off <<= 1) {
-                gb1[m][i] += __shfl_xor(gb1[m][i], off);
-                gb2[m][i] += __shfl_xor(gb2[m][i], off);
-                gw3[m][i] += __shfl_xor(gw3[m][i], off);
-            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s.gb1[m][i] = sum16(s.gb1[m][i]);
+            s.gb2[m][i] = sum16(s.gb2[m][i]);
+            s.gw3[m][i] = sum16(s.gw3[m][i]);
+        }
     for (int off = 1; off < 64; off <<= 1) {
-        gb3 += __shfl_xor(gb3, off);
-        loss += __shfl_xor(loss, off);
+        s.gb3 += __shfl_xor(s.gb3, off);
+        s.loss += __shfl_xor(s.loss, off);
     }
     float *G = gpart + wave * kNP;
+#pragma unroll
     for (int m = 0; m < 2; ++m)
+#pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int h = 16 * m + 4 * q + i;
-            G[kOffW1 + h * kNI + n] = gW1[m][i];
-            G[kOffW2 + h * kNH + n] = gW2[m][0][i];
-            G[kOffW2 + h * kNH + 16 + n] = gW2[m][1][i];
+            G[kOffW1 + h * kNI + n] = s.gW1[m][i];
+            G[kOffW2 + h * kNH + n] = s.gW2[m][0][i];
+            G[kOffW2 + h * kNH + 16 + n] = s.gW2[m][1][i];
             if (n == 0) {
-                G[kOffB1 + h] = gb1[m][i];
-                G[kOffB2 + h] = gb2[m][i];
-                G[kOffW3 + h] = gw3[m][i];
+                G[kOffB1 + h] = s.gb1[m][i];
+                G[kOffB2 + h] = s.gb2[m][i];
+                G[kOffW3 + h] = s.gw3[m][i];
             }
         }
     if (l == 0) {
-        G[kOffB3] = gb3;
-        lpart[wave] = loss * (double)inv_b;
+        G[kOffB3] = s.gb3;
+        lpart[wave] = s.loss * (double)inv_b;
     }
 }
 
 // grad[p] = sum over the wavefront partials (FP64), loss likewise.  A block
 // serves kRedParams parameters with kRedSplit threads each: thread k of a
 // parameter sums waves k, k + kRedSplit, ... in order and the kRedSplit sums are
-// added in order (a fixed order: deterministic).  With `adam` the block then
+// added in order (a fixed order: deterministic).  The partials of a thread are
+// loaded kRedBatch at a time; the last block adds the partial losses, 64 loaded
+// by the lanes of a wavefront and added in wave order.  With `adam` a block then
 // applies the AdamW update of tbk_adamw_step to its parameters (the training
 // loop's fused step; t-dependent factors c1, c2 precomputed on the host).
-constexpr int kRedParams = 64, kRedSplit = 4;
+constexpr int kRedParams = 64, kRedSplit = 4, kRedBatch = 16;
 
 struct AdamArgs {
     float *p, *m, *v;
@@ -526,10 +631,31 @@ __global__ __launch_bounds__(kRedParams * kRedSplit) void k_grad_reduce(int64_t 
                                                                        double *__restrict__ loss, AdamArgs ad) {
     __shared__ double red[kRedSplit][kRedParams];
     const int pl = threadIdx.x % kRedParams, k = threadIdx.x / kRedParams;
+    if (blockIdx.x == gridDim.x - 1) {
+        if (loss && k == 0) {
+            double sum = 0.0;
+            for (int64_t w0 = 0; w0 < nwave; w0 += 64) {
+                const double x = w0 + pl < nwave ? lpart[w0 + pl] : 0.0;
+                const int c = (int)min((int64_t)64, nwave - w0);
+                for (int u = 0; u < c; ++u) sum += __shfl(x, u);
+            }
+            if (pl == 0) *loss = sum;
+        }
+        return;
+    }
     const int p = blockIdx.x * kRedParams + pl;
     double s = 0.0;
-    if (p < kNP)
-        for (int64_t wv = k; wv < nwave; wv += kRedSplit) s += (double)gpart[wv * kNP + p];
+    if (p < kNP) {
+        int64_t wv = k;
+        for (; wv + (kRedBatch - 1) * kRedSplit < nwave; wv += kRedBatch * kRedSplit) {
+            float x[kRedBatch];
+#pragma unroll
+            for (int u = 0; u < kRedBatch; ++u) x[u] = gpart[(wv + u * kRedSplit) * kNP + p];
+#pragma unroll
+            for (int u = 0; u < kRedBatch; ++u) s += (double)x[u];
+        }
+        for (; wv < nwave; wv += kRedSplit) s += (double)gpart[wv * kNP + p];
+    }
     red[k][pl] = s;
     __syncthreads();
     if (k == 0 && p < kNP) {
@@ -545,11 +671,6 @@ __global__ __launch_bounds__(kRedParams * kRedSplit) void k_grad_reduce(int64_t 
             const float mh = mi / ad.c1, vh = vi / ad.c2;
             ad.p[p] -= ad.lr * (mh / (sqrtf(vh) + ad.eps) + ad.wd * ad.p[p]);
         }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && loss) {
-        double l = 0.0;
-        for (int64_t wv = 0; wv < nwave; ++wv) l += lpart[wv];
-        *loss = l;
     }
 }
 
@@ -946,7 +1067,7 @@ static tbk_status loss_grad_impl(int64_t nb, const uint16_t *X, const float *tar
     double *lpart = reinterpret_cast<double *>(static_cast<char *>(work) + ((nwave * kNP * 4 + 255) / 256) * 256);
     k_mlp_grad<<<G, 64 * kWaves, 0, s>>>(nb, X, target, weight, params, 1.0f / (float)nb, order, gpart, lpart);
     TBK_HIP(hipGetLastError());
-    const unsigned rb = (kNP + kRedParams - 1) / kRedParams;
+    const unsigned rb = (kNP + kRedParams - 1) / kRedParams + 1;      // the last block: the loss
     if (adam)
         k_grad_reduce<true><<<rb, kRedParams * kRedSplit, 0, s>>>(nwave, gpart, lpart, grad, loss, *adam);
     else
