@@ -824,7 +824,9 @@ int32_t lsqt_chebyshev_terms(double a, double dt);
 /* Bytes of device workspace lsqt_vac_moments needs for the same (R, M,
  * precision, time_batch, cfg): the workspace of the recurrence of R * B vectors
  * (B = the time batch, below), six [n_rows][R_pad] vectors and, when B > 1, the
- * batch's start and left vectors and moments. */
+ * batch's start and left vectors and moments, and the lists and vectors of the
+ * form that propagates and steps on tiles.  A buffer large enough without the
+ * latter is accepted; the sweeps then run. */
 tbk_status lsqt_workspace_size(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
                                int32_t time_batch, const tbk_kpm_config *cfg, int64_t *bytes);
 

@@ -698,7 +698,7 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
         ta.out_cur = keep ? plane(2 * dst) : nullptr;
         ta.out_prev = keep ? plane(2 * dst + 1) : nullptr;
         ta.partial = part + (int64_t)(at + 1 - batch0) * ta.pstride;
-        launch_tile_group<VT>(pl, diag, grid, s, ta);
+        launch_tile_group<VT>(pl, diag, kTileDirect, grid, s, ta);
         cur = ta.out_cur;
         prev = ta.out_prev;
         at += len;

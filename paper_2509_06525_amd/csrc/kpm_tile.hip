@@ -302,6 +302,28 @@ __global__ __launch_bounds__(kThreads) void k_tile_prepare(const VT *__restrict_
     }
 }
 
+// partial[t][v] = Re <left_v|start_v> over the rows of tile t (planes); grid (tiles, R).
+template <class VT>
+__global__ __launch_bounds__(kThreads) void k_tile_overlap(const VT *__restrict__ start, const VT *__restrict__ left,
+                                                           const int32_t *__restrict__ row0, int64_t rows, int32_t Rp,
+                                                           double *__restrict__ partial) {
+    __shared__ double red[kThreads / 64];
+    const int t = blockIdx.x, v = blockIdx.y;
+    double acc = 0.0;
+    for (int64_t i = row0[t] + threadIdx.x; i < row0[t + 1]; i += kThreads) {
+        const int64_t o = 2 * ((int64_t)v * rows + i);
+        acc += (double)left[o] * (double)start[o] + (double)left[o + 1] * (double)start[o + 1];
+    }
+    acc = wave_sum(acc);
+    if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < kThreads / 64; ++w) s += red[w];
+        partial[(int64_t)t * Rp + v] = s;
+    }
+}
+
 // [rows][Rp] <-> planes [vector][rows] for the R vectors (TO: into planes; the
 // padded columns of the row form are zero).
 template <class VT, bool TO>
@@ -324,10 +346,10 @@ __global__ __launch_bounds__(kThreads) void k_planes(VT *__restrict__ x, VT *__r
 }
 
 template <class VT>
-void launch_steps(const TilePlan &tp, bool diag, bool dbl, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
-    if (tp.W == 3) launch_tile_steps<VT, 3>(tp, diag, dbl, grid, s, a);
-    else if (tp.W == 4) launch_tile_steps<VT, 4>(tp, diag, dbl, grid, s, a);
-    else launch_tile_steps<VT, 6>(tp, diag, dbl, grid, s, a);
+void launch_steps(const TilePlan &tp, bool diag, int form, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
+    if (tp.W == 3) launch_tile_steps<VT, 3>(tp, diag, form, grid, s, a);
+    else if (tp.W == 4) launch_tile_steps<VT, 4>(tp, diag, form, grid, s, a);
+    else launch_tile_steps<VT, 6>(tp, diag, form, grid, s, a);
 }
 
 // Layout for rows of up to W entries from byte `base` on.
@@ -388,7 +410,7 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
     tp.off_part = take((size_t)tp.reduce_every * per_step);
     tp.off_l1 = take((size_t)pl.Mr * pl.Rv * chunks * sizeof(double));
     tp.plane_bytes = align256((size_t)n * R * 2 * pl.elem);
-    tp.off_planes = take((pl.Rp == 1 && n_seg == 1 ? 2 : 6) * tp.plane_bytes);
+    tp.off_planes = take((pl.Rp == 1 && n_seg == 1 ? 2 : 6) * tp.plane_bytes);    // T pairs, r, start
     tp.total = o;
 }
 
@@ -501,7 +523,8 @@ unsigned tile_grid(const TileRun &run, int32_t R) {
 
 template <class VT>
 tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, double a, double b, const VT *r,
-                     int32_t R, int32_t M, char *work, double *mu, hipStream_t s, const VT *start, const VT *left) {
+                     int32_t R, int32_t M, char *work, double *mu, hipStream_t s, const VT *start, const VT *left,
+                     bool planes) {
     const TilePlan &tp = pl.tile;
     const bool pair = left != nullptr, dbl = pl.cfg.doubling != 0;
     const int n_start = pl.n_start;
@@ -524,10 +547,10 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
     const unsigned ge = (unsigned)ceil_div(n * Rp, kThreads);
 
     if (pair) {
-        if (direct) {
+        if (direct || planes) {
             rp = const_cast<VT *>(left);
             sp = const_cast<VT *>(start);
-            k_pair_overlap<VT, 1, 1><<<gt, kThreads, 0, s>>>(left, start, n, 1, gt, part);
+            k_tile_overlap<VT><<<dim3(gt, R), kThreads, 0, s>>>(start, left, row0, n, Rp, part);
         } else {
             sp = plane(5);
             k_tile_prepare<VT, 1, false><<<gt, kThreads, 0, s>>>(start, left, nullptr, row0, n, R, Rp, 0, 0, nullptr,
@@ -594,7 +617,7 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
         ta.out_cur = keep ? P[dst][end & 1] : nullptr;
         ta.out_prev = keep ? P[dst][(end + 1) & 1] : nullptr;
         ta.partial = part + (int64_t)(at + 1 - batch0) * ta.pstride;
-        launch_steps<VT>(tp, diag, dbl, grid, s, ta);
+        launch_steps<VT>(tp, diag, dbl ? kTileDoubling : kTileDirect, grid, s, ta);
         cur = ta.out_cur;
         prev = ta.out_prev;
         at = end;
@@ -617,8 +640,8 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
 }
 
 template <class VT>
-void launch_tile_group(const KpmPlan &pl, bool diag, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
-    launch_steps<VT>(pl.tile, diag, false, grid, s, a);
+void launch_tile_group(const KpmPlan &pl, bool diag, int form, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
+    launch_steps<VT>(pl.tile, diag, form, grid, s, a);
 }
 
 template <class VT>
@@ -629,12 +652,60 @@ void tile_start_planes(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, 
         r, nullptr, h->perm, row0, h->n_rows, R, pl.Rp, 0, 0, nullptr, rp, nullptr, part);
 }
 
+template <class VT>
+tbk_status propagate_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, double a, double b, int32_t R,
+                           int32_t n_cheb, const double *cre, const double *cim, double pr, double pi, char *work,
+                           hipStream_t s, const VT *phi, VT *phi_out) {
+    const TilePlan &tp = pl.tile;
+    auto plane = [&](int k) { return reinterpret_cast<VT *>(work + tp.off_planes + k * tp.plane_bytes); };
+    TileArgs<VT> ta = tile_args<VT>(h, pl, run, work, R);
+    ta.c1f = (VT)(1.0 / a);
+    ta.c1 = (VT)(2.0 / a);
+    ta.shift = (VT)b;
+    ta.c0r = cre[0];
+    ta.c0i = cim[0];
+    ta.pr = pr;
+    ta.pi = pi;
+    const bool diag = h->has_onsite || b != 0.0;
+    const unsigned grid = tile_grid(run, R);
+    const int steps = n_cheb - 1;
+    const int groups = (int)ceil_div(steps, std::min<int64_t>(run.s, kTileMaxS));
+    int at = 0, dst = 0;
+    const VT *cur = phi, *prev = phi;
+    for (int q = 0; q < groups; ++q) {
+        const int len = steps / groups + (q < steps % groups ? 1 : 0);
+        const bool last = q + 1 == groups;
+        ta.first = at == 0;
+        ta.s = len;
+        ta.cur = cur;
+        ta.prev = prev;
+        ta.out_cur = last ? nullptr : plane(2 * dst);
+        ta.out_prev = last ? nullptr : plane(2 * dst + 1);
+        ta.acc_in = plane(4);
+        ta.acc_out = last ? phi_out : plane(4);
+        for (int m = 0; m < len; ++m) {
+            ta.cr[m] = cre[at + 1 + m];
+            ta.ci[m] = cim[at + 1 + m];
+        }
+        launch_steps<VT>(tp, diag, kTilePropagate, grid, s, ta);
+        cur = ta.out_cur;
+        prev = ta.out_prev;
+        at += len;
+        dst ^= 1;
+    }
+    TBK_HIP(hipGetLastError());
+    return TBK_OK;
+}
+
 #define TBK_TILE_INST(VT)                                                                                              \
     template tbk_status tile_build<VT>(const tbk_ham *, const KpmPlan &, int, char *, hipStream_t, TileRun &);        \
     template TileArgs<VT> tile_args<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, char *, int32_t);           \
     template tbk_status run_tiled<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, double, double, const VT *,   \
-                                      int32_t, int32_t, char *, double *, hipStream_t, const VT *, const VT *);        \
-    template void launch_tile_group<VT>(const KpmPlan &, bool, unsigned, hipStream_t, const TileArgs<VT> &);           \
+                                      int32_t, int32_t, char *, double *, hipStream_t, const VT *, const VT *, bool);  \
+    template tbk_status propagate_tiled<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, double, double,         \
+                                            int32_t, int32_t, const double *, const double *, double, double, char *,  \
+                                            hipStream_t, const VT *, VT *);                                            \
+    template void launch_tile_group<VT>(const KpmPlan &, bool, int, unsigned, hipStream_t, const TileArgs<VT> &);           \
     template void tile_start_planes<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, const VT *, int32_t,        \
                                         char *, VT *, double *, hipStream_t);
 TBK_TILE_INST(float)

@@ -51,7 +51,17 @@ template <class VT> struct TileArgs {
     int32_t first;           // 1: T_n is T_0 (step 0 is T_1 = Ht T_0)
     int32_t closed;          // 1: no tile has a halo, so s is not limited by rings
     VT c1f, c1, shift;       // 1/a, 2/a, b (one structure)
+    // propagator form: acc += (cr + i ci)[m] T of step m; acc starts as (c0r + i c0i) T_0
+    // (first) or from acc_in, and leaves multiplied by pr + i pi
+    const VT *acc_in;
+    VT *acc_out;
+    double c0r, c0i, pr, pi;
+    double cr[kTileMaxS], ci[kTileMaxS];
 };
+
+// What a launch gathers beside the vectors: the sums <r|T>, the two sums of the
+// doubling identities, or the series of the propagator.
+enum TileForm { kTileDirect = 0, kTileDoubling = 1, kTilePropagate = 2 };
 
 // Sum over the wavefront; lane 63 holds it (fixed order).
 __device__ __forceinline__ double wave_sum(double x) {
@@ -72,15 +82,22 @@ __device__ __forceinline__ double wave_sum(double x) {
     return x;
 }
 
+// x y rounded before anything is added to it (no contraction).
+template <class VT> __device__ __forceinline__ VT rounded_product(VT x, VT y) {
+#pragma clang fp contract(off)
+    return x * y;
+}
+
 // Local rows a workgroup of NT threads with K rows each can hold: 128 fewer than
 // its slots, whose LDS takes the moment sums (2 KB).
 constexpr int tile_cap(int NT, int K) { return NT * K - 128; }
 constexpr int kTileFlush = 8;      // steps between two writes of the moment sums
 
-template <class VT, int NT, int K, int W, bool DIAG, bool DBL>
+template <class VT, int NT, int K, int W, bool DIAG, int FORM>
 __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
     typedef std::conditional_t<sizeof(VT) == 4, f2v, d2v> C2;
     constexpr int CAP = tile_cap(NT, K);
+    constexpr bool DBL = FORM == kTileDoubling, EVO = FORM == kTilePropagate;
     constexpr int NA = DBL ? 2 : 1;
     constexpr int NW = NT / 64;
     constexpr int NP = W / 2;
@@ -99,6 +116,7 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
     const C2 *gcur = reinterpret_cast<const C2 *>(a.cur) + plane;
     const C2 *gprev = reinterpret_cast<const C2 *>(a.prev) + plane;
     const C2 *gr = reinterpret_cast<const C2 *>(a.r) + plane;
+    const C2 *gacc = reinterpret_cast<const C2 *>(a.acc_in) + plane;
     const int32_t *ext = a.ext + (int64_t)t * a.cap - nr;
     VT c1f = a.c1f, c1 = a.c1, shift = a.shift;
     if (a.tile_seg) {
@@ -131,7 +149,10 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
             for (int p = 0; p < NP; ++p) lc[k][p] = a.lcol2[mb * NP + (int64_t)p * a.cap + j];
             if constexpr (W & 1) lc[k][NP] = a.lcol1[mb + j];
             if constexpr (DIAG) dg[k] = a.ons ? a.ons[mb + j] : (VT)0;
-            if constexpr (!DBL) rr[k] = gr[row0 + min(j, nr - 1)];
+            if constexpr (FORM == kTileDirect) rr[k] = gr[row0 + min(j, nr - 1)];
+            if constexpr (EVO) {
+                if (!a.first) rr[k] = gacc[row0 + min(j, nr - 1)];
+            }
         }
         C2 xc[K], xp[K];
 #pragma unroll
@@ -146,7 +167,13 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int j = k * NT + tid;
-            if (a.first) xp[k].x = xp[k].y = 0;
+            if (a.first) {
+                xp[k].x = xp[k].y = 0;
+                if constexpr (EVO) {
+                    rr[k].x = (VT)(a.c0r * (double)xc[k].x - a.c0i * (double)xc[k].y);
+                    rr[k].y = (VT)(a.c0r * (double)xc[k].y + a.c0i * (double)xc[k].x);
+                }
+            }
             if (j < n_all) buf[j] = xc[k];
             if (j < n_mat) buf[CAP + j] = xp[k];
         }
@@ -159,6 +186,7 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
         constexpr int DST = decltype(par)::value ? 0 : CAP;
         const int lim = a.closed ? nr : cnt[s - 1 - m];
         const VT cc = (m == 0 && a.first) ? c1f : c1;
+        const double cr = EVO ? a.cr[m] : 0.0, ci = EVO ? a.ci[m] : 0.0;
         const char *src = reinterpret_cast<const char *>(buf + SRC);
         double acc[NA];
 #pragma unroll
@@ -178,12 +206,16 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
                 C2 own;
                 if constexpr (DIAG || DBL) own = buf[SRC + j];
                 VT yr = 0, yi = 0;
+                if constexpr (DIAG && EVO) {      // first, as in k_evolve_term
+                    yr = rounded_product(dg[k], own.x);
+                    yi = rounded_product(dg[k], own.y);
+                }
 #pragma unroll
                 for (int w = 0; w < W; ++w) {
                     yr += h[k][w] * x[w].x;
                     yi += h[k][w] * x[w].y;
                 }
-                if constexpr (DIAG) {
+                if constexpr (DIAG && !EVO) {
                     yr += dg[k] * own.x;
                     yi += dg[k] * own.y;
                 }
@@ -192,7 +224,10 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
                 o.y = cc * yi - p.y;
                 buf[DST + j] = o;
                 if (j < nr) {
-                    if constexpr (DBL) {
+                    if constexpr (EVO) {
+                        rr[k].x += (VT)(cr * (double)o.x - ci * (double)o.y);
+                        rr[k].y += (VT)(cr * (double)o.y + ci * (double)o.x);
+                    } else if constexpr (DBL) {
                         acc[0] += (double)o.x * (double)o.x + (double)o.y * (double)o.y;
                         acc[1] += (double)own.x * (double)o.x + (double)own.y * (double)o.y;
                     } else {
@@ -203,6 +238,10 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
                     }
                 }
             }
+        }
+        if constexpr (EVO) {
+            __syncthreads();
+            return;
         }
 #pragma unroll
         for (int q = 0; q < NA; ++q) {
@@ -230,6 +269,21 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
     }
     if (m < s) step(std::integral_constant<int, 0>{}, m);
 
+    if constexpr (EVO) {
+        C2 *oa = reinterpret_cast<C2 *>(a.acc_out) + plane + row0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int j = k * NT + tid;
+            if (j < nr) {
+                C2 y = rr[k];
+                if (!a.out_cur) {      // the last group: the phase of the shift
+                    y.x = (VT)(a.pr * (double)rr[k].x - a.pi * (double)rr[k].y);
+                    y.y = (VT)(a.pr * (double)rr[k].y + a.pi * (double)rr[k].x);
+                }
+                oa[j] = y;
+            }
+        }
+    }
     if (a.out_cur) {
         const int cur = (s & 1) ? CAP : 0, old = CAP - cur;
         C2 *oc = reinterpret_cast<C2 *>(a.out_cur) + plane + row0;
@@ -248,7 +302,7 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
 // Launches one group of steps with the kernel of the plan's shape; instantiated
 // per vector type and width in kpm_tile_inst_*.hip.
 template <class VT, int W>
-void launch_tile_steps(const TilePlan &tp, bool diag, bool dbl, unsigned grid, hipStream_t s,
+void launch_tile_steps(const TilePlan &tp, bool diag, int form, unsigned grid, hipStream_t s,
                        const TileArgs<VT> &a);
 
 // Launch shapes (threads, rows per thread).  A row's entries stay in registers
@@ -275,13 +329,21 @@ template <class VT>
 tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *work, hipStream_t s, TileRun &run);
 template <class VT>
 TileArgs<VT> tile_args(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, char *work, int32_t R);
+// planes: start and left are planes [vector][rows] (pair form).
 template <class VT>
 tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, double a, double b, const VT *r,
-                     int32_t R, int32_t M, char *work, double *mu, hipStream_t s, const VT *start, const VT *left);
-unsigned tile_grid(const TileRun &run, int32_t R);
-// One launch of a group of steps (direct form).
+                     int32_t R, int32_t M, char *work, double *mu, hipStream_t s, const VT *start, const VT *left,
+                     bool planes = false);
+// phi_out = exp(-i b dt / hbar) sum_k c[k] T_k(Ht) phi for R vectors in planes
+// (n_cheb >= 2 terms, coefficients cre + i cim, phase pr + i pi); phi_out is not phi.
 template <class VT>
-void launch_tile_group(const KpmPlan &pl, bool diag, unsigned grid, hipStream_t s, const TileArgs<VT> &a);
+tbk_status propagate_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, double a, double b, int32_t R,
+                           int32_t n_cheb, const double *cre, const double *cim, double pr, double pi, char *work,
+                           hipStream_t s, const VT *phi, VT *phi_out);
+unsigned tile_grid(const TileRun &run, int32_t R);
+// One launch of a group of steps.
+template <class VT>
+void launch_tile_group(const KpmPlan &pl, bool diag, int form, unsigned grid, hipStream_t s, const TileArgs<VT> &a);
 // Start vectors (caller's order) to planes, and the sums of |r|^2 per tile.
 template <class VT>
 void tile_start_planes(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, const VT *r, int32_t R, char *work,

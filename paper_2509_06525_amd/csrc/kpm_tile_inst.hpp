@@ -7,29 +7,36 @@
 namespace tbk {
 namespace {
 
-template <class VT, int W, int SHAPE, bool DIAG, bool DBL>
+template <class VT, int W, int SHAPE, bool DIAG, int FORM>
 void launch(unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
     constexpr int NT = tile_threads(SHAPE), K = tile_slots(SHAPE, W, sizeof(VT) == 8);
-    k_tile_steps<VT, NT, K, W, DIAG, DBL><<<grid, NT, 0, s>>>(a);
+    k_tile_steps<VT, NT, K, W, DIAG, FORM><<<grid, NT, 0, s>>>(a);
+}
+
+template <class VT, int W, int SHAPE, int FORM>
+void launch_diag(bool diag, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
+    if (diag) launch<VT, W, SHAPE, true, FORM>(grid, s, a);
+    else launch<VT, W, SHAPE, false, FORM>(grid, s, a);
 }
 
 template <class VT, int W, int SHAPE>
-void launch_shape(bool diag, bool dbl, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
-    if (dbl) diag ? launch<VT, W, SHAPE, true, true>(grid, s, a) : launch<VT, W, SHAPE, false, true>(grid, s, a);
-    else diag ? launch<VT, W, SHAPE, true, false>(grid, s, a) : launch<VT, W, SHAPE, false, false>(grid, s, a);
+void launch_shape(bool diag, int form, unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
+    if (form == kTileDoubling) launch_diag<VT, W, SHAPE, kTileDoubling>(diag, grid, s, a);
+    else if (form == kTilePropagate) launch_diag<VT, W, SHAPE, kTilePropagate>(diag, grid, s, a);
+    else launch_diag<VT, W, SHAPE, kTileDirect>(diag, grid, s, a);
 }
 
 }  // namespace
 
 template <class VT, int W>
-void launch_tile_steps(const TilePlan &tp, bool diag, bool dbl, unsigned grid, hipStream_t s,
+void launch_tile_steps(const TilePlan &tp, bool diag, int form, unsigned grid, hipStream_t s,
                        const TileArgs<VT> &a) {
     // large_diag differs from large where its rows per thread do
     constexpr bool own = tile_slots(kTileLargeDiag, W, sizeof(VT) == 8) != tile_slots(kTileLarge, W, sizeof(VT) == 8);
-    if (tp.shape == kTileWhole) launch_shape<VT, W, kTileWhole>(diag, dbl, grid, s, a);
-    else if (tp.shape == kTileLargeDiag && own) launch_shape<VT, W, kTileLargeDiag>(diag, dbl, grid, s, a);
-    else if (sizeof(VT) == 4 && tp.shape == kTileSmall) launch_shape<VT, W, sizeof(VT) == 4 ? kTileSmall : kTileLarge>(diag, dbl, grid, s, a);
-    else launch_shape<VT, W, kTileLarge>(diag, dbl, grid, s, a);
+    if (tp.shape == kTileWhole) launch_shape<VT, W, kTileWhole>(diag, form, grid, s, a);
+    else if (tp.shape == kTileLargeDiag && own) launch_shape<VT, W, kTileLargeDiag>(diag, form, grid, s, a);
+    else if (sizeof(VT) == 4 && tp.shape == kTileSmall) launch_shape<VT, W, sizeof(VT) == 4 ? kTileSmall : kTileLarge>(diag, form, grid, s, a);
+    else launch_shape<VT, W, kTileLarge>(diag, form, grid, s, a);
 }
 
 }  // namespace tbk

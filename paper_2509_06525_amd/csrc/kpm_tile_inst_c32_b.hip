@@ -2,8 +2,8 @@
 #include "kpm_tile_inst.hpp"
 
 namespace tbk {
-template void launch_tile_steps<float, 4>(const TilePlan &, bool, bool, unsigned, hipStream_t,
+template void launch_tile_steps<float, 4>(const TilePlan &, bool, int, unsigned, hipStream_t,
                                         const TileArgs<float> &);
-template void launch_tile_steps<float, 6>(const TilePlan &, bool, bool, unsigned, hipStream_t,
+template void launch_tile_steps<float, 6>(const TilePlan &, bool, int, unsigned, hipStream_t,
                                         const TileArgs<float> &);
 }  // namespace tbk

@@ -2,6 +2,6 @@
 #include "kpm_tile_inst.hpp"
 
 namespace tbk {
-template void launch_tile_steps<double, 3>(const TilePlan &, bool, bool, unsigned, hipStream_t,
+template void launch_tile_steps<double, 3>(const TilePlan &, bool, int, unsigned, hipStream_t,
                                         const TileArgs<double> &);
 }  // namespace tbk

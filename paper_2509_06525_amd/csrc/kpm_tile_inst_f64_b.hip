@@ -2,8 +2,8 @@
 #include "kpm_tile_inst.hpp"
 
 namespace tbk {
-template void launch_tile_steps<double, 4>(const TilePlan &, bool, bool, unsigned, hipStream_t,
+template void launch_tile_steps<double, 4>(const TilePlan &, bool, int, unsigned, hipStream_t,
                                         const TileArgs<double> &);
-template void launch_tile_steps<double, 6>(const TilePlan &, bool, bool, unsigned, hipStream_t,
+template void launch_tile_steps<double, 6>(const TilePlan &, bool, int, unsigned, hipStream_t,
                                         const TileArgs<double> &);
 }  // namespace tbk

@@ -13,7 +13,10 @@
 // rule over the samples (lsqt_sigma in dos.hip).
 //
 // All vectors live in the builder's row order, [rows][R_pad] interleaved
-// complex, like the recurrence's.  The kernels here are plain SELL sweeps with
+// complex, like the recurrence's, or, for one-orbital Hamiltonians whose tiles
+// fit (kpm_tile.hpp), in planes [vector][rows]: the propagation then runs six to
+// eight terms of its series per launch, and the recurrences take their start and
+// left vectors as they lie (run_vac_tiled).  Otherwise the kernels here are plain SELL sweeps with
 // one thread per (row, vector) (for block Hamiltonians: per (orbital row,
 // vector), over the atom's blocks); the M-1 recurrence steps per time step,
 // which dominate, run in the tuned recurrence kernel, for B time steps at a
@@ -26,6 +29,7 @@
 
 #include "common.hpp"
 #include "kpm.hpp"
+#include "kpm_tile.hpp"
 
 namespace tbk {
 namespace {
@@ -340,6 +344,9 @@ struct LsqtLayout {
     size_t vec = 0, off_vec = 0;        // [rows][R_pad] vector units after the recurrence workspace
     size_t bvec = 0, off_batch = 0;     // start and left vectors of a batch, [rows][pad(R B)]
     size_t off_mu = 0, total = 0;       // a batch's moments [R B][M]
+    KpmPlan ev;                 // tiles of the propagation (2 R vectors); ev.tile.on: planes throughout
+    size_t plane2 = 0, off_phi = 0;     // two sets of 2 R planes (phi_R | phi_L)
+    size_t planeb = 0, off_start = 0;   // R B planes each: start, left
 };
 
 // tiled = false leaves out the workspace of the tiled recurrence (a caller's
@@ -368,8 +375,127 @@ tbk_status make_layout(const tbk_ham *h, int32_t R, int32_t M, int32_t precision
     ly.off_batch = ly.off_vec + 9 * ly.vec;
     ly.bvec = a256((size_t)h->n_rows * ly.pl.Rp * 2 * elem);
     ly.off_mu = ly.off_batch + 2 * ly.bvec;
+    if (ly.pl.tile.on && 2 * R <= 64) {
+        st = make_plan(h, 2 * R, 2, precision, nullptr, ly.ev);
+        if (st != TBK_OK) return st;
+        tile_layout(h, ly.ev, ly.off_vec, 2 * R, 1);
+        ly.plane2 = a256((size_t)h->n_rows * 2 * R * 2 * elem);
+        ly.planeb = a256((size_t)h->n_rows * R * ly.B * 2 * elem);
+        ly.off_phi = a256(ly.ev.tile.total);
+        ly.off_start = ly.off_phi + 2 * ly.plane2;
+        ly.off_mu = std::max(ly.off_mu, ly.off_start + 2 * ly.planeb);
+    }
     ly.total = ly.off_mu + a256((size_t)R * ly.B * M * sizeof(double));
     return TBK_OK;
+}
+
+// plane v of out = row order of r[.][v] (caller's order), grid (rows / 256, R).
+template <class VT>
+__global__ void k_permute_planes(const VT *__restrict__ r, const int32_t *__restrict__ perm, int64_t n, int32_t R,
+                                 VT *__restrict__ out) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int v = blockIdx.y;
+    if (i >= n) return;
+    const int64_t src = 2 * ((int64_t)perm[i] * R + v), dst = 2 * ((int64_t)v * n + i);
+    out[dst] = r[src];
+    out[dst + 1] = r[src + 1];
+}
+
+// Plane v of y = V x (as k_apply_velocity); with x2 also y2 = x2 (a time step's
+// start and left vectors into the batch's planes).  Grid (rows / 256, R).
+template <class VT>
+__global__ void k_velocity_planes(SellView h, const VT *__restrict__ vx, const VT *__restrict__ x, int64_t n,
+                                  VT *__restrict__ y, const VT *__restrict__ x2, VT *__restrict__ y2) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t pl = 2 * (int64_t)blockIdx.y * n;
+    if (i >= n) return;
+    int64_t base, stride;
+    int32_t w;
+    row_range(h, i, base, w, stride);
+    VT sr = 0, si = 0;
+    for (int32_t k = 0; k < w; ++k) {
+        const int64_t q = base + k * stride;
+        const VT c = vx[q];
+        const int64_t xo = pl + 2 * (int64_t)h.col[q];
+        sr += c * x[xo];
+        si += c * x[xo + 1];
+    }
+    y[pl + 2 * i] = -si;
+    y[pl + 2 * i + 1] = sr;
+    if (x2) {
+        y2[pl + 2 * i] = x2[pl + 2 * i];
+        y2[pl + 2 * i + 1] = x2[pl + 2 * i + 1];
+    }
+}
+
+tbk_status check_finite(const double *nu, int64_t m, hipStream_t s) {
+    DevBuf flag;
+    TBK_HIP(flag.alloc(sizeof(int32_t), s));
+    TBK_HIP(hipMemsetAsync(flag.as<int32_t>(), 0, sizeof(int32_t), s));
+    k_all_finite<<<(unsigned)ceil_div(m, 256), 256, 0, s>>>(nu, m, flag.as<int32_t>());
+    TBK_HIP(hipGetLastError());
+    int32_t hf = 0;
+    TBK_HIP(hipMemcpyAsync(&hf, flag.as<int32_t>(), sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    TBK_HIP(hipStreamSynchronize(s));
+    TBK_CHECK(hf == 0, TBK_ERR_SPECTRUM, "a correlation moment is not finite: (a, b) does not bound the spectrum");
+    return TBK_OK;
+}
+
+// Coefficients (2 - delta_k0) (-i)^k J_k(a dt / hbar) of the propagator and its phase.
+struct Series {
+    std::vector<double> re, im;
+    double pr, pi;
+    Series(double a, double b, double dt, int32_t n_cheb) : re(n_cheb), im(n_cheb) {
+        const double z = a * dt / kHbar;
+        for (int32_t k = 0; k < n_cheb; ++k) {
+            const double jk = (k == 0 ? 1.0 : 2.0) * ::jn(k, z);
+            const int q = k & 3;                     // (-i)^k: 1, -i, -1, i
+            re[k] = q == 0 ? jk : (q == 2 ? -jk : 0.0);
+            im[k] = q == 1 ? -jk : (q == 3 ? jk : 0.0);
+        }
+        pr = std::cos(b * dt / kHbar);
+        pi = -std::sin(b * dt / kHbar);              // exp(-i b dt / hbar)
+    }
+};
+
+// The VAC run in planes: propagation and recurrences on tiles, several terms or
+// steps per launch.  250k atoms, one vector, 32 steps of 18 terms and 256 moments:
+// the sweeps' 17 launches per propagation took 116 us, four on tiles 43 us; 9.1 -> 6.3 ms.
+template <class VT>
+tbk_status run_vac_tiled(const tbk_ham *h, const VT *vx, double a, double b, const VT *r, int32_t R, int32_t M,
+                         int32_t n_t, const Series &ser, const LsqtLayout &ly, const TileRun &rec, const TileRun &prop,
+                         char *work, double *nu, hipStream_t s) {
+    const int64_t n = h->n_rows;
+    const SellView sv{h->ptr, h->col, log2_of(h->fmt == TBK_CSR_F64 ? 1 : h->slice)};
+    VT *phi = reinterpret_cast<VT *>(work + ly.off_phi);
+    VT *next = reinterpret_cast<VT *>(work + ly.off_phi + ly.plane2);
+    VT *start = reinterpret_cast<VT *>(work + ly.off_start);
+    VT *left = reinterpret_cast<VT *>(work + ly.off_start + ly.planeb);
+    const int64_t half = 2 * n * (int64_t)R;         // phi_L follows the R planes of phi_R
+    const dim3 g((unsigned)ceil_div(n, kLsqtThreads), (unsigned)R);
+    k_permute_planes<VT><<<g, kLsqtThreads, 0, s>>>(r, h->perm, n, R, phi);
+    k_velocity_planes<VT><<<g, kLsqtThreads, 0, s>>>(sv, vx, phi, n, phi + half, nullptr, nullptr);
+    TBK_HIP(hipGetLastError());
+    for (int32_t j0 = 0; j0 < n_t; j0 += ly.B) {
+        const int32_t nb = std::min(ly.B, n_t - j0);
+        for (int32_t q = 0; q < nb; ++q) {
+            k_velocity_planes<VT><<<g, kLsqtThreads, 0, s>>>(sv, vx, phi, n, start + q * half, phi + half,
+                                                              left + q * half);
+            TBK_HIP(hipGetLastError());
+            if (j0 + q + 1 < n_t) {
+                const tbk_status st =
+                    propagate_tiled<VT>(h, ly.ev, prop, a, b, 2 * R, (int32_t)ser.re.size(), ser.re.data(),
+                                        ser.im.data(), ser.pr, ser.pi, work, s, phi, next);
+                if (st != TBK_OK) return st;
+                std::swap(phi, next);
+            }
+        }
+        // the batch's moments [q][v][m] are nu[j0 + q][v][m]; a short last batch runs its own vectors only
+        const tbk_status st = run_tiled<VT>(h, ly.pl, rec, a, b, nullptr, R * nb, M, work,
+                                            nu + (int64_t)j0 * R * M, s, start, left, true);
+        if (st != TBK_OK) return st;
+    }
+    return check_finite(nu, (int64_t)n_t * R * M, s);
 }
 
 template <class VT>
@@ -392,17 +518,21 @@ tbk_status run_vac(const tbk_ham *h, const VT *vx, double a, double b, const VT 
     const unsigned g = (unsigned)ceil_div(nv, kLsqtThreads), g2 = (unsigned)ceil_div(nv2, kLsqtThreads);
     const unsigned gp = (unsigned)ceil_div(n * Rp, kLsqtThreads);     // a thread per row and pair of vectors
 
-    // series coefficients of U(dt)
-    const double z = a * dt / kHbar;
-    std::vector<double> cre(n_cheb), cim(n_cheb);
-    for (int32_t k = 0; k < n_cheb; ++k) {
-        const double jk = (k == 0 ? 1.0 : 2.0) * ::jn(k, z);
-        // (-i)^k: 1, -i, -1, i
-        const int q = k & 3;
-        cre[k] = q == 0 ? jk : (q == 2 ? -jk : 0.0);
-        cim[k] = q == 1 ? -jk : (q == 3 ? jk : 0.0);
+    const Series ser(a, b, dt, n_cheb);
+    const std::vector<double> &cre = ser.re, &cim = ser.im;
+    const double pr = ser.pr, pi = ser.pi;
+    TileRun tiles;                  // listed once for the recurrences of all batches
+    if (pl.tile.on) {
+        tbk_status st = build_tiles(h, pl, precision, work, s, tiles);
+        if (st != TBK_OK) return st;
+        if (tiles.s > 0 && ly.ev.tile.on && n_cheb >= 2) {
+            TileRun prop;
+            st = build_tiles(h, ly.ev, precision, work, s, prop);
+            if (st != TBK_OK) return st;
+            if (prop.s > 0)
+                return run_vac_tiled<VT>(h, vx, a, b, r, R, M, n_t, ser, ly, tiles, prop, work, nu, s);
+        }
     }
-    const double pr = std::cos(b * dt / kHbar), pi = -std::sin(b * dt / kHbar);   // exp(-i b dt / hbar)
 
     const bool blk = pl.block;
     const int32_t norb = pl.norb;
@@ -468,11 +598,6 @@ tbk_status run_vac(const tbk_ham *h, const VT *vx, double a, double b, const VT 
     const int64_t nb_el = 2 * n * (int64_t)Rb;
     const unsigned gz = (unsigned)ceil_div(nb_el, kLsqtThreads);
     const unsigned gi = (unsigned)ceil_div(n * R, kLsqtThreads);
-    TileRun tiles;                  // listed once for the recurrences of all batches
-    if (pl.tile.on) {
-        tbk_status st = build_tiles(h, pl, precision, work, s, tiles);
-        if (st != TBK_OK) return st;
-    }
     for (int32_t j0 = 0; j0 < n_t; j0 += ly.B) {
         const int32_t nb = std::min(ly.B, n_t - j0);
         if (nb * R < Rb) {
@@ -495,17 +620,7 @@ tbk_status run_vac(const tbk_ham *h, const VT *vx, double a, double b, const VT 
         TBK_HIP(hipMemcpyAsync(nu + (int64_t)j0 * R * M, mub, sizeof(double) * (size_t)nb * R * M,
                                hipMemcpyDeviceToDevice, s));
     }
-    DevBuf flag;
-    TBK_HIP(flag.alloc(sizeof(int32_t), s));
-    TBK_HIP(hipMemsetAsync(flag.as<int32_t>(), 0, sizeof(int32_t), s));
-    const int64_t m = (int64_t)n_t * R * M;
-    k_all_finite<<<(unsigned)ceil_div(m, 256), 256, 0, s>>>(nu, m, flag.as<int32_t>());
-    TBK_HIP(hipGetLastError());
-    int32_t hf = 0;
-    TBK_HIP(hipMemcpyAsync(&hf, flag.as<int32_t>(), sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    TBK_HIP(hipStreamSynchronize(s));
-    TBK_CHECK(hf == 0, TBK_ERR_SPECTRUM, "a correlation moment is not finite: (a, b) does not bound the spectrum");
-    return TBK_OK;
+    return check_finite(nu, (int64_t)n_t * R * M, s);
 }
 
 }  // namespace

@@ -158,18 +158,26 @@ def test_stacked_tiles_equal_the_stacked_sweep(fmt, prec, R, dims):
         assert (tiled[k] - mk).abs().max().item() <= 1e-13 * s.n * (1 if prec == "f64" else 1e7)
 
 
-def test_vac_on_tiles_equals_the_sweep():
-    s = synth.graphene_sheet(70, 60, 0.05, 8)
-    H = G.build(s, fmt="sell_f64", slice=64)
+@pytest.mark.parametrize("prec,R,stripes,nx,ny,n_cheb", [("f64", 1, False, 70, 60, 0), ("c32", 3, True, 90, 100, 0),
+                                                          ("c32", 1, False, 160, 170, 2), ("f64", 2, True, 20, 30, 3),
+                                                          ("c32", 20, False, 33, 40, 0)])
+def test_vac_on_tiles_equals_the_sweep(prec, R, stripes, nx, ny, n_cheb):
+    """Propagation and recurrences on tiles: each value from the same operands in the
+    same order as the sweeps', so only the moments' double sums differ.  A short last
+    batch, a series of two terms, a matrix of one tile."""
+    s = synth.hbn_stripes(nx, ny, 4, 0.05, 8) if stripes else synth.graphene_sheet(nx, ny, 0.05, 8)
+    H = G.build(s, fmt="sell_f64" if prec == "f64" else "sell_f32", slice=64)
     a, b = H.scale()
     vx = tbkpm.build_velocity(H, G.to_dev(s.pos), s.box, s.periodic, 0)
-    r = tbkpm.random_phase(5, s.n, 1, "f64")
-    M, n_t = 40, 21
-    nu = tbkpm.vac_moments(H, vx, a, b, r, M, n_t, 0.1, precision="f64")
-    # nine vector blocks, the batch's start and left vectors and its moments after the sweep's workspace
-    vec = (s.n * 16 + 255) // 256 * 256
-    small = _sweep_size(H, 16, M, "f64") + 9 * vec + 2 * 16 * vec + (16 * M * 8 + 255) // 256 * 256 + 256
+    r = tbkpm.random_phase(5, s.n, R, prec)
+    M, B = 40, max(1, 16 // R)
+    n_t = B + 3
+    nu = tbkpm.vac_moments(H, vx, a, b, r, M, n_t, 0.1, n_cheb=n_cheb, precision=prec)
+    # the sweep's workspace, nine vector blocks, the batch's start and left vectors and its moments
+    elem = 16 if prec == "f64" else 8
+    pad = lambda x: (x + 255) // 256 * 256
+    vec, bvec = (pad(s.n * elem * (1 << (k - 1).bit_length())) for k in (R, R * B))
+    small = pad(_sweep_size(H, R * B, M, prec)) + 9 * vec + 2 * bvec + pad(R * B * M * 8)
     work = torch.zeros(small, dtype=torch.uint8, device=G.DEV)
-    nu2 = tbkpm.vac_moments(H, vx, a, b, r, M, n_t, 0.1, precision="f64", work=work)
-    scale = nu.abs().max().item()
-    assert (nu - nu2).abs().max().item() <= 1e-13 * max(scale, s.n)
+    nu2 = tbkpm.vac_moments(H, vx, a, b, r, M, n_t, 0.1, n_cheb=n_cheb, precision=prec, work=work)
+    assert (nu - nu2).abs().max().item() <= 1e-13 * max(nu2.abs().max().item(), s.n)
