@@ -39,18 +39,36 @@ __global__ void k_tile_rows(int64_t n, int32_t n_tiles, int32_t S, int32_t *__re
 
 // Halves the tiles whose halo does not fit (the builder orders rows in strips of
 // cells; a tile across a strip's end has two edges more than its neighbours and
-// would set the steps per launch for all of them).  One workgroup: every thread
-// counts the pieces of a run of tiles, a scan places them.  At most `most` tiles
-// result; entries past the last one hold n.
+// would set the steps per launch for all of them).  The rings k asked of every tile
+// are those with the most steps per tile, k over the number of tiles that result:
+// where only a few tiles reach S (long bonds), halving the rest costs more than
+// the rings are worth (1 M rows of up to 5 entries, four vectors: 16.0 us a step at
+// the S = 8 of half tiles, 11.2 at the 5 rings that fit).  One workgroup: every
+// thread counts the pieces of a run of tiles, a scan places them.  At most `most`
+// tiles result; entries past the last one hold n.
 __global__ __launch_bounds__(1024) void k_tile_split(const int32_t *__restrict__ first, const int32_t *__restrict__ rings,
                                                      const int32_t *__restrict__ seg, int32_t n_tiles, int32_t most,
                                                      int32_t S, int32_t n, int32_t *__restrict__ row0,
                                                      int32_t *__restrict__ tseg, TileInfo *__restrict__ info) {
     __shared__ int32_t sum[1024];
+    __shared__ int32_t reach[kTileMaxS + 1];      // tiles of just so many rings
     const int tid = threadIdx.x;
     const int per = (n_tiles + 1023) / 1024;
     const int t0 = min(tid * per, n_tiles), t1 = min(t0 + per, n_tiles);
-    auto pieces = [&](int t) { return rings[t] < S && first[t + 1] - first[t] >= 2 ? 2 : 1; };
+    if (tid <= kTileMaxS) reach[tid] = 0;
+    __syncthreads();
+    for (int t = t0; t < t1; ++t) atomicAdd(&reach[min(max(rings[t], 0), S)], 1);
+    __syncthreads();
+    int need = 1;
+    int64_t need_tiles = n_tiles;
+    for (int k = 1, less = 0; k <= S; ++k) {
+        less += reach[k - 1];
+        if (n_tiles + less <= most && k * need_tiles >= (int64_t)need * (n_tiles + less)) {
+            need = k;
+            need_tiles = n_tiles + less;
+        }
+    }
+    auto pieces = [&](int t) { return rings[t] < need && first[t + 1] - first[t] >= 2 ? 2 : 1; };
     int c = 0;
     for (int t = t0; t < t1; ++t) c += pieces(t);
     sum[tid] = c;
@@ -370,19 +388,21 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
         tp.tile_rows = n;
         tp.S = 1;
     } else {
-        // Rows per tile and rings.  Large systems: 0.65 of the capacity (0.6 in FP64) and
-        // eight (six) rings; 4 M rows, one complex-float vector, us per step: 13.1 with 0.8
-        // and 4 rings, 9.6 with 0.65 and 8, 10.2 with 0.6 and 10 (the sweep: 36.9).  Systems
-        // with fewer tiles than CUs: smaller tiles, whose larger halo costs less than idle
-        // CUs; 30,212 rows, three vectors: 1.25 us per step with 384 rows (236 workgroups),
-        // 1.6 with 1024, the sweep 4.8.
+        // Rows per tile and rings.  Large systems: 0.7 of the capacity (0.6 in FP64 and for
+        // rows of 5 and 6 entries) and up to eight (six) rings, of which k_tile_split takes
+        // what pays; 16 M row-vectors, us per step: 31.4 with 0.75 of the capacity, 29.1 with
+        // 0.7, 30.1 with 0.65, 31.0 with 0.55 and ten rings (the sweep: 148).  Systems with
+        // fewer tiles than CUs: smaller tiles, whose larger halo costs less than idle CUs;
+        // 30,212 rows, three vectors: 1.25 us per step with 384 rows (236 workgroups), 1.6
+        // with 1024, the sweep 4.8; 300,000 rows, two vectors: 2.46 with 0.4 of the capacity,
+        // 2.70 with 8/15.
         if (!f64 && work < 700000) {
             shape(kTileSmall);
-            tp.tile_rows = std::min<int64_t>(tp.cap * 8 / 15, std::max<int64_t>(256, work / 256));
+            tp.tile_rows = std::min<int64_t>(tp.cap * (W <= 4 ? 6 : 8) / 15, std::max<int64_t>(256, work / 256));
         } else {
             shape(h->has_onsite ? kTileLargeDiag : kTileLarge);
             if (f64) tp.tile_rows = std::min<int64_t>(tp.cap * 3 / 5, std::max<int64_t>(256, work / 400));
-            else tp.tile_rows = std::min<int64_t>(tp.cap * 13 / 20, std::max<int64_t>(tp.cap * 7 / 25, work / 512));
+            else tp.tile_rows = std::min<int64_t>(tp.cap * (W <= 4 ? 7 : 6) / 10, std::max<int64_t>(tp.cap * 7 / 25, work / 512));
         }
         tp.S = (f64 || tp.shape == kTileSmall) && tp.tile_rows > tp.cap * 2 / 5 ? 6 : 8;
         tp.n_first = ceil_div(n, tp.tile_rows) + (n_seg > 1 ? n_seg : 0);   // a partial tile per structure

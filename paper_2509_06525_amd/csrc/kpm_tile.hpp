@@ -110,8 +110,11 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
     const int row0 = a.row0[t], nr = a.row0[t + 1] - row0;
     const int32_t *cnt = a.cnt + (int64_t)t * a.S1;
     const int s = a.s;
-    const int n_all = a.closed ? nr : cnt[s];             // rows whose T_n is read
-    const int n_mat = a.closed ? nr : cnt[s - 1];         // rows the first step writes
+    // lane k holds the rows within k rings: read from memory at each step their latency
+    // stood between the barrier and the step (16 M row-vectors: 34.0 us a step, 30.4 so)
+    const int rings = cnt[min(tid & 63, a.S1 - 1)];
+    const int n_all = a.closed ? nr : __builtin_amdgcn_readlane(rings, s);         // rows whose T_n is read
+    const int n_mat = a.closed ? nr : __builtin_amdgcn_readlane(rings, s - 1);     // rows the first step writes
     const int64_t plane = (int64_t)v * a.rows;
     const C2 *gcur = reinterpret_cast<const C2 *>(a.cur) + plane;
     const C2 *gprev = reinterpret_cast<const C2 *>(a.prev) + plane;
@@ -184,7 +187,7 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
     auto step = [&](auto par, int m) {
         constexpr int SRC = decltype(par)::value ? CAP : 0;
         constexpr int DST = decltype(par)::value ? 0 : CAP;
-        const int lim = a.closed ? nr : cnt[s - 1 - m];
+        const int lim = a.closed ? nr : __builtin_amdgcn_readlane(rings, s - 1 - m);
         const VT cc = (m == 0 && a.first) ? c1f : c1;
         const double cr = EVO ? a.cr[m] : 0.0, ci = EVO ? a.ci[m] : 0.0;
         const char *src = reinterpret_cast<const char *>(buf + SRC);
