@@ -4,7 +4,7 @@
 //   1. k_segment_scan: per-segment coordinate range, NaN/Inf and species checks
 //   2. cell list: cell id per atom (per-segment grids, global ids), counts,
 //      exclusive scan, scatter, per-cell sort by atom index
-//   3. k_degree: neighbours within r_cut per row
+//   3. k_degree: neighbours within r_cut per row, the first few of them kept for 5.
 //   4. slice widths (max degree per slice) -> slice offsets (exclusive scan)
 //   5. k_fill: columns and FP64 hoppings of each row, padding, in-row sort by
 //      column, onsite, per-segment row Gershgorin bounds
@@ -14,6 +14,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "builder.hpp"
@@ -42,29 +43,34 @@ __global__ void k_seg_of(int64_t n, int32_t nseg, const int64_t *__restrict__ se
     seg_of[i] = lo;
 }
 
-constexpr int kScanChunk = 16;      // atoms per thread in k_segment_scan
+// Atoms per thread of k_segment_scan and rows per thread of k_fill, such that no more
+// than `blocks` blocks end in atomics on the same few words: those come one every 60 ns
+// or so (1 M atoms, k_segment_scan: 273 us with a block per 256 atoms, 50 with 512 blocks).
+int rows_per_thread(int64_t n, int blocks) {
+    return (int)std::max<int64_t>(1, ceil_div(n, (int64_t)kBlock * blocks));
+}
 
 // Per-segment coordinate ranges and input checks over the whole grid.
 // keys[(k n_seg + s) 2 + {0, 1}] = order-preserving keys of min / max of
 // coordinate k over the finite coordinates of segment s (k_init_bounds start);
 // flags[2 s] = 1 if some coordinate of s is NaN/Inf, flags[2 s + 1] = 1 if a
 // species index is outside [0, n_species) (flags start at 0).  A block covers
-// kScanChunk * kBlock consecutive atoms; a thread flushes its running range
+// chunk * kBlock consecutive atoms; a thread flushes its running range
 // with atomics when its atoms cross into another segment, and the block folds
 // the last ranges per segment before one atomic per segment and coordinate.
 __global__ __launch_bounds__(kBlock) void k_segment_scan(const double *__restrict__ pos,
                                                          const int32_t *__restrict__ species, int64_t n,
                                                          const int32_t *__restrict__ seg_of, int32_t nseg,
-                                                         int32_t n_species, int64_t *__restrict__ keys,
+                                                         int32_t n_species, int chunk, int64_t *__restrict__ keys,
                                                          int32_t *__restrict__ flags) {
-    const int64_t base = (int64_t)blockIdx.x * kBlock * kScanChunk;
+    const int64_t base = (int64_t)blockIdx.x * kBlock * chunk;
     double mn[3], mx[3];
     int32_t cur = -1;
     auto reset = [&]() {
         for (int k = 0; k < 3; ++k) { mn[k] = INFINITY; mx[k] = -INFINITY; }
     };
     reset();
-    for (int u = 0; u < kScanChunk; ++u) {
+    for (int u = 0; u < chunk; ++u) {
         const int64_t i = base + (int64_t)u * kBlock + threadIdx.x;
         if (i >= n) break;
         const int32_t sg = seg_of[i];
@@ -135,31 +141,79 @@ __global__ void k_perm(int64_t n, int32_t reorder, const int32_t *__restrict__ s
     iperm[a] = (int32_t)r;
 }
 
+// Neighbours within r_cut per row, and (nbr != NULL) the first kShortRow of them for
+// k_fill.
+constexpr int kShortRow = 6;
+
 __global__ void k_degree(CellList cl, const double *__restrict__ pos, int64_t n, double r_cut,
-                         const int32_t *__restrict__ perm, int32_t *__restrict__ deg) {
+                         const int32_t *__restrict__ perm, int32_t *__restrict__ deg, int32_t *__restrict__ nbr) {
     int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (r >= n) return;
     int32_t cnt = 0;
-    for_each_neighbor(cl, pos, perm[r], r_cut, [&](int32_t, double, double, double, double) { ++cnt; });
+    for_each_pair(cl, pos, perm[r], r_cut, [&](int32_t j, double, double, double, double) {
+        if (nbr && cnt < kShortRow) nbr[cnt * n + r] = j;
+        ++cnt;
+    });
     deg[r] = cnt;
 }
 
-// Width of each slice (largest degree among its rows) and its stored entries.
-__global__ void k_slice_width(int64_t n, int32_t slice, int64_t n_slices, const int32_t *__restrict__ deg,
-                              int64_t *__restrict__ entries) {
-    int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (s >= n_slices) return;
+// Width of each slice (largest degree among its rows) and its stored entries.  A
+// slice goes to min(slice, 64) lanes side by side: one thread per slice of 256 rows
+// read each row from a line of its own (100 M rows: 1.3 ms, 0.15 ms so).
+__global__ __launch_bounds__(kBlock) void k_slice_width(int64_t n, int32_t slice, int64_t n_slices,
+                                                        const int32_t *__restrict__ deg,
+                                                        int64_t *__restrict__ entries) {
+    const int32_t lanes = slice < 64 ? slice : 64;
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t s = t / lanes;
+    const int32_t lane = (int32_t)(t - s * lanes);
     int32_t w = 0;
-    int64_t r1 = (s + 1) * slice < n ? (s + 1) * slice : n;
-    for (int64_t r = s * slice; r < r1; ++r) w = deg[r] > w ? deg[r] : w;
-    entries[s] = (int64_t)w * slice;
+    const int64_t r1 = (s + 1) * slice < n ? (s + 1) * slice : n;
+    for (int64_t r = s * slice + lane; r < r1; r += lanes) w = max(w, deg[r]);
+    for (int d = lanes >> 1; d > 0; d >>= 1) w = max(w, __shfl_xor(w, d));
+    if (lane == 0 && s <= n_slices) entries[s] = (int64_t)w * slice;      // 0 past the last
 }
 
-__global__ void k_init_bounds(int32_t n_seg, int64_t *__restrict__ keys) {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n_seg) return;
-    keys[2 * s] = dkey(INFINITY);
-    keys[2 * s + 1] = dkey(-INFINITY);
+// n empty bounds, and `zeros` words of 0 after them.
+__global__ void k_init_bounds(int32_t n, int64_t *__restrict__ keys, int32_t zeros) {
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s < n) {
+        keys[2 * s] = dkey(INFINITY);
+        keys[2 * s + 1] = dkey(-INFINITY);
+    }
+    if (s < zeros) keys[2 * n + s] = 0;
+}
+
+// totals[0] = largest degree, totals[1] = sum of the degrees (both start at 0),
+// totals[2] = stored entries.
+__global__ __launch_bounds__(kBlock) void k_totals(const int32_t *__restrict__ deg, int64_t n,
+                                                   const int64_t *__restrict__ ptr, int64_t n_slices,
+                                                   int64_t *__restrict__ totals) {
+    int32_t mx = 0;
+    int64_t sum = 0;
+    for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
+        mx = max(mx, deg[i]);
+        sum += deg[i];
+    }
+    for (int d = 32; d > 0; d >>= 1) {
+        mx = max(mx, __shfl_xor(mx, d));
+        sum += __shfl_xor(sum, d);
+    }
+    __shared__ int32_t wmx[kBlock / 64];
+    __shared__ int64_t wsum[kBlock / 64];
+    if ((threadIdx.x & 63) == 0) {
+        wmx[threadIdx.x >> 6] = mx;
+        wsum[threadIdx.x >> 6] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < kBlock / 64; ++w) {
+        mx = max(mx, wmx[w]);
+        sum += wsum[w];
+    }
+    atomicMax((long long *)&totals[0], (long long)mx);
+    atomicAdd((unsigned long long *)&totals[1], (unsigned long long)sum);
+    if (blockIdx.x == 0) totals[2] = ptr[n_slices];
 }
 
 struct SpeciesTable {
@@ -167,77 +221,129 @@ struct SpeciesTable {
     double t_pair[kMaxSpecies * kMaxSpecies];
 };
 
-template <class V>
-__global__ void k_fill(CellList cl, const double *__restrict__ pos, const int32_t *__restrict__ species,
-                       int64_t n, int32_t slice, double r_cut, double r0, double beta, int32_t n_species,
-                       const SpeciesTable *__restrict__ tab, const int32_t *__restrict__ perm,
-                       const int32_t *__restrict__ iperm, const int64_t *__restrict__ ptr,
-                       int32_t *__restrict__ col, V *__restrict__ val, V *__restrict__ onsite,
-                       int64_t *__restrict__ bound_keys, int64_t *__restrict__ val_keys,
-                       int16_t *__restrict__ col16) {
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+// Columns, hoppings, onsite energies and Gershgorin bounds of the rows.  SHORT (no row
+// of more than kShortRow entries): the neighbours are those k_degree found, in its
+// order, and a row is sorted in registers and written once; otherwise the search runs
+// again and rows are sorted in place.  The search beside exp and the rest takes 160
+// registers, and waves per SIMD with them (100 M atoms: 19.5 ms with the search, 5.3
+// without).  A block takes `rows` rows per thread (one where there are several segments).
+template <class V, bool SHORT>
+__global__ __launch_bounds__(kBlock) void k_fill(
+    CellList cl, const double *__restrict__ pos, const int32_t *__restrict__ species, int64_t n, int32_t slice,
+    double r_cut, double r0, double beta, int32_t n_species, const SpeciesTable *__restrict__ tab,
+    const int32_t *__restrict__ perm, const int32_t *__restrict__ iperm, const int64_t *__restrict__ ptr,
+    int32_t *__restrict__ col, V *__restrict__ val, V *__restrict__ onsite, int64_t *__restrict__ bound_keys,
+    int64_t *__restrict__ val_keys, int16_t *__restrict__ col16, const int32_t *__restrict__ deg,
+    const int32_t *__restrict__ nbr, int rows) {
     double lo = INFINITY, hi = -INFINITY;
     double vlo = INFINITY, vhi = -INFINITY;   // range of the stored hoppings
     int32_t sg = -1;
-    if (r < n) {
+    for (int it = 0; it < rows; ++it) {
+        const int64_t r = ((int64_t)blockIdx.x * rows + it) * kBlock + threadIdx.x;
+        if (r >= n) break;
         const int64_t s = r / slice, lane = r - s * slice;
         const int64_t base = ptr[s] + lane;
         const int32_t w = (int32_t)((ptr[s + 1] - ptr[s]) / slice);
         const int32_t i = perm[r];
         const int32_t si = species[i];
         sg = cl.seg_of[i];
-        int32_t k = 0;
-        double asum = 0.0;
-        for_each_neighbor(cl, pos, i, r_cut, [&](int32_t j, double rij, double, double, double) {
-            double t = tab->t_pair[si * n_species + species[j]] * exp(-beta * (rij / r0 - 1.0));
-            if (k < w) {
-                col[base + (int64_t)k * slice] = iperm[j];
-                val[base + (int64_t)k * slice] = (V)t;
-            }
-            vlo = fmin(vlo, (double)(V)t);
-            vhi = fmax(vhi, (double)(V)t);
-            asum += fabs(t);
-            ++k;
-        });
-        for (int32_t q = k; q < w; ++q) {
-            col[base + (int64_t)q * slice] = (int32_t)r;
-            val[base + (int64_t)q * slice] = (V)0;
-        }
-        // Insertion sort of the row's real entries by column.
-        int32_t kk = k < w ? k : w;
-        for (int32_t a = 1; a < kk; ++a) {
-            int32_t c = col[base + (int64_t)a * slice];
-            V v = val[base + (int64_t)a * slice];
-            int32_t b = a - 1;
-            while (b >= 0 && col[base + (int64_t)b * slice] > c) {
-                col[base + (int64_t)(b + 1) * slice] = col[base + (int64_t)b * slice];
-                val[base + (int64_t)(b + 1) * slice] = val[base + (int64_t)b * slice];
-                --b;
-            }
-            col[base + (int64_t)(b + 1) * slice] = c;
-            val[base + (int64_t)(b + 1) * slice] = v;
-        }
-        if (col16) {    // 16-bit column offsets (escape -32768: read col)
-            for (int32_t q = 0; q < w; ++q) {
-                const int64_t d = (int64_t)col[base + (int64_t)q * slice] - r;
+        auto hopping = [&](int32_t j, double rij) {
+            return tab->t_pair[si * n_species + species[j]] * exp(-beta * (rij / r0 - 1.0));
+        };
+        auto put = [&](int32_t q, int32_t c, V v) {
+            col[base + (int64_t)q * slice] = c;
+            val[base + (int64_t)q * slice] = v;
+            if (col16) {    // 16-bit column offsets (escape -32768: read col)
+                const int64_t d = (int64_t)c - r;
                 col16[base + (int64_t)q * slice] = (d >= -32767 && d <= 32767) ? (int16_t)d : (int16_t)-32768;
             }
+        };
+        int32_t k = 0;
+        double asum = 0.0;
+        if constexpr (SHORT) {
+            const CellGrid &g = cl.grids[sg];
+            const double xi = pos[3 * (int64_t)i], yi = pos[3 * (int64_t)i + 1], zi = pos[3 * (int64_t)i + 2];
+            k = deg[r];
+            int32_t c[kShortRow];
+            V v[kShortRow];
+#pragma unroll
+            for (int q = 0; q < kShortRow; ++q) {
+                c[q] = INT32_MAX;
+                v[q] = (V)0;
+                if (q >= k) continue;
+                const int32_t j = nbr[q * n + r];
+                double dx, dy, dz;
+                const double r2 = pair_r2(g, pos[3 * (int64_t)j] - xi, pos[3 * (int64_t)j + 1] - yi,
+                                          pos[3 * (int64_t)j + 2] - zi, dx, dy, dz);
+                const double t = hopping(j, sqrt(r2));
+                c[q] = iperm[j];
+                v[q] = (V)t;
+                vlo = fmin(vlo, (double)(V)t);
+                vhi = fmax(vhi, (double)(V)t);
+                asum += fabs(t);
+            }
+            // ascending columns; the places without an entry stay last
+#pragma unroll
+            for (int e = 1; e < kShortRow; ++e)
+#pragma unroll
+                for (int q = e; q > 0; --q)
+                    if (c[q - 1] > c[q]) {
+                        const int32_t tc = c[q - 1];
+                        const V tv = v[q - 1];
+                        c[q - 1] = c[q];
+                        v[q - 1] = v[q];
+                        c[q] = tc;
+                        v[q] = tv;
+                    }
+#pragma unroll
+            for (int q = 0; q < kShortRow; ++q)
+                if (q < w) put(q, q < k ? c[q] : (int32_t)r, v[q]);
+            for (int32_t q = kShortRow; q < w; ++q) put(q, (int32_t)r, (V)0);
+        } else {
+            for_each_neighbor(cl, pos, i, r_cut, [&](int32_t j, double rij, double, double, double) {
+                const double t = hopping(j, rij);
+                if (k < w) {
+                    col[base + (int64_t)k * slice] = iperm[j];
+                    val[base + (int64_t)k * slice] = (V)t;
+                }
+                vlo = fmin(vlo, (double)(V)t);
+                vhi = fmax(vhi, (double)(V)t);
+                asum += fabs(t);
+                ++k;
+            });
+            // Insertion sort of the row's real entries by column.
+            const int32_t kk = k < w ? k : w;
+            for (int32_t a = 1; a < kk; ++a) {
+                const int32_t ca = col[base + (int64_t)a * slice];
+                const V va = val[base + (int64_t)a * slice];
+                int32_t b = a - 1;
+                while (b >= 0 && col[base + (int64_t)b * slice] > ca) {
+                    col[base + (int64_t)(b + 1) * slice] = col[base + (int64_t)b * slice];
+                    val[base + (int64_t)(b + 1) * slice] = val[base + (int64_t)b * slice];
+                    --b;
+                }
+                col[base + (int64_t)(b + 1) * slice] = ca;
+                val[base + (int64_t)(b + 1) * slice] = va;
+            }
+            for (int32_t q = 0; q < w; ++q)
+                put(q, q < kk ? col[base + (int64_t)q * slice] : (int32_t)r,
+                    q < kk ? val[base + (int64_t)q * slice] : (V)0);
         }
-        double eps = tab->onsite[si];
+        const double eps = tab->onsite[si];
         onsite[r] = (V)eps;
-        lo = eps - asum;
-        hi = eps + asum;
+        lo = fmin(lo, eps - asum);
+        hi = fmax(hi, eps + asum);
     }
     block_segment_bounds(lo, hi, sg, bound_keys);
     block_segment_bounds(vlo, vhi, vlo <= vhi ? 0 : -1, val_keys);
 }
 
 template <class T>
-tbk_status exclusive_scan(const T *in, T *out, int64_t n, hipStream_t s) {
+tbk_status exclusive_scan(const T *in, T *out, int64_t n, Arena &arena, hipStream_t s) {
     size_t tmp = 0;
     TBK_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp, in, out, (int)n, s));
     DevBuf t;
-    TBK_HIP(t.alloc(tmp, s));
+    TBK_HIP(t.alloc(tmp, arena));
     TBK_HIP(hipcub::DeviceScan::ExclusiveSum(t.as<void>(), tmp, in, out, (int)n, s));
     return TBK_OK;
 }
@@ -278,16 +384,16 @@ void decode_bounds(const std::vector<int64_t> &keys, int nseg, double *bounds) {
     }
 }
 
-tbk_status init_bound_keys(DevBuf &keys, int nseg, hipStream_t s) {
-    TBK_HIP(keys.alloc(sizeof(int64_t) * 2 * nseg, s));
-    k_init_bounds<<<(nseg + 255) / 256, 256, 0, s>>>(nseg, keys.as<int64_t>());
+tbk_status init_bound_keys(DevBuf &keys, int n, Arena &arena, hipStream_t s) {
+    TBK_HIP(keys.alloc(sizeof(int64_t) * 2 * n, arena));
+    k_init_bounds<<<(n + 255) / 256, 256, 0, s>>>(n, keys.as<int64_t>(), 0);
     TBK_HIP(hipGetLastError());
     return TBK_OK;
 }
 
 tbk_status CellListOwner::build(const double *pos, const int32_t *species, int32_t n_species, int64_t n,
                                 int32_t nseg, const int64_t *seg_atoms_h, const double *boxes,
-                                const int32_t periodic[3], double r_cut, hipStream_t s) {
+                                const int32_t periodic[3], double r_cut, Arena &arena, hipStream_t s) {
     TBK_CHECK(pos && boxes && periodic && seg_atoms_h, TBK_ERR_INVALID_ARG, "NULL position/box/periodic/segments");
     TBK_CHECK(n >= 1 && n < (int64_t)INT32_MAX, TBK_ERR_INVALID_ARG, "n = %lld out of [1, 2^31-1)", (long long)n);
     TBK_CHECK(nseg >= 1 && nseg <= (1 << 20), TBK_ERR_INVALID_ARG, "n_seg = %d out of [1, 2^20]", nseg);
@@ -306,8 +412,8 @@ tbk_status CellListOwner::build(const double *pos, const int32_t *species, int32
                           "periodic length %g (axis %d, segment %d) is below 2 r_cut = %g", L, k, g, 2.0 * r_cut);
             }
     n_seg = nseg;
-    TBK_HIP(seg_atoms.alloc(sizeof(int64_t) * (nseg + 1), s));
-    TBK_HIP(seg_of.alloc(sizeof(int32_t) * n, s));
+    TBK_HIP(seg_atoms.alloc(sizeof(int64_t) * (nseg + 1), arena));
+    TBK_HIP(seg_of.alloc(sizeof(int32_t) * n, arena));
     TBK_HIP(hipMemcpyAsync(seg_atoms.as<int64_t>(), seg_atoms_h, sizeof(int64_t) * (nseg + 1),
                            hipMemcpyHostToDevice, s));
     const int gseg = (int)ceil_div(n, kBlock);
@@ -315,20 +421,20 @@ tbk_status CellListOwner::build(const double *pos, const int32_t *species, int32
     TBK_HIP(hipGetLastError());
 
     // 1. ranges and validity per segment
-    DevBuf rkeys, rflags;
-    TBK_HIP(rkeys.alloc(sizeof(int64_t) * 6 * nseg, s));
-    TBK_HIP(rflags.alloc(sizeof(int32_t) * 2 * nseg, s));
-    k_init_bounds<<<(3 * nseg + 255) / 256, 256, 0, s>>>(3 * nseg, rkeys.as<int64_t>());
+    DevBuf rkeys;           // 6 nseg keys, then 2 nseg 32-bit flags
+    TBK_HIP(rkeys.alloc(sizeof(int64_t) * 7 * nseg, arena));
+    int32_t *rflags = reinterpret_cast<int32_t *>(rkeys.as<int64_t>() + 6 * (size_t)nseg);
+    k_init_bounds<<<(3 * nseg + 255) / 256, 256, 0, s>>>(3 * nseg, rkeys.as<int64_t>(), nseg);
     TBK_HIP(hipGetLastError());
-    TBK_HIP(hipMemsetAsync(rflags.as<int32_t>(), 0, sizeof(int32_t) * 2 * nseg, s));
-    k_segment_scan<<<(unsigned)ceil_div(n, (int64_t)kBlock * kScanChunk), kBlock, 0, s>>>(
-        pos, species, n, seg_of.as<int32_t>(), nseg, n_species, rkeys.as<int64_t>(), rflags.as<int32_t>());
+    const int chunk = nseg == 1 ? rows_per_thread(n, n < (1 << 22) ? 512 : 2048) : 1;
+    k_segment_scan<<<(unsigned)ceil_div(n, (int64_t)kBlock * chunk), kBlock, 0, s>>>(
+        pos, species, n, seg_of.as<int32_t>(), nseg, n_species, chunk, rkeys.as<int64_t>(), rflags);
     TBK_HIP(hipGetLastError());
-    std::vector<int64_t> hk(6 * (size_t)nseg);
-    std::vector<int32_t> hf(2 * (size_t)nseg);
-    TBK_HIP(hipMemcpyAsync(hk.data(), rkeys.as<int64_t>(), sizeof(int64_t) * 6 * nseg, hipMemcpyDeviceToHost, s));
-    TBK_HIP(hipMemcpyAsync(hf.data(), rflags.as<int32_t>(), sizeof(int32_t) * 2 * nseg, hipMemcpyDeviceToHost, s));
+    std::vector<int64_t> hk(7 * (size_t)nseg);
+    TBK_HIP(hipMemcpyAsync(hk.data(), rkeys.as<int64_t>(), sizeof(int64_t) * 7 * nseg, hipMemcpyDeviceToHost, s));
     TBK_HIP(hipStreamSynchronize(s));
+    std::vector<int32_t> hf(2 * (size_t)nseg);
+    std::memcpy(hf.data(), hk.data() + 6 * (size_t)nseg, sizeof(int32_t) * 2 * nseg);
     // hp[8 g + k] = min, hp[8 g + 3 + k] = max of coordinate k in segment g
     std::vector<double> hp(8 * (size_t)nseg);
     for (int g = 0; g < nseg; ++g) {
@@ -373,21 +479,21 @@ tbk_status CellListOwner::build(const double *pos, const int32_t *species, int32
         TBK_CHECK(off < (int64_t)INT32_MAX, TBK_ERR_UNSUPPORTED, "too many cells");
     }
     const int64_t ncell = off;
-    TBK_HIP(grids.alloc(sizeof(CellGrid) * nseg, s));
+    TBK_HIP(grids.alloc(sizeof(CellGrid) * nseg, arena));
     TBK_HIP(hipMemcpyAsync(grids.as<CellGrid>(), hg.data(), sizeof(CellGrid) * nseg, hipMemcpyHostToDevice, s));
 
     DevBuf cell, slot, count;
-    TBK_HIP(cell.alloc(sizeof(int32_t) * n, s));
-    TBK_HIP(slot.alloc(sizeof(int32_t) * n, s));
-    TBK_HIP(count.alloc(sizeof(int32_t) * (ncell + 1), s));
-    TBK_HIP(cell_start.alloc(sizeof(int32_t) * (ncell + 1), s));
-    TBK_HIP(sorted.alloc(sizeof(int32_t) * n, s));
+    TBK_HIP(cell.alloc(sizeof(int32_t) * n, arena));
+    TBK_HIP(slot.alloc(sizeof(int32_t) * n, arena));
+    TBK_HIP(count.alloc(sizeof(int32_t) * (ncell + 1), arena));
+    TBK_HIP(cell_start.alloc(sizeof(int32_t) * (ncell + 1), arena));
+    TBK_HIP(sorted.alloc(sizeof(int32_t) * n, arena));
     TBK_HIP(hipMemsetAsync(count.as<int32_t>(), 0, sizeof(int32_t) * (ncell + 1), s));
     const int gn = (int)ceil_div(n, kBlock);
     k_cell_of<<<gn, kBlock, 0, s>>>(pos, n, grids.as<CellGrid>(), seg_of.as<int32_t>(), cell.as<int32_t>(),
                                     slot.as<int32_t>(), count.as<int32_t>());
     TBK_HIP(hipGetLastError());
-    tbk_status st = exclusive_scan(count.as<int32_t>(), cell_start.as<int32_t>(), ncell + 1, s);
+    tbk_status st = exclusive_scan(count.as<int32_t>(), cell_start.as<int32_t>(), ncell + 1, arena, s);
     if (st != TBK_OK) return st;
     k_scatter<<<gn, kBlock, 0, s>>>(n, cell.as<int32_t>(), slot.as<int32_t>(), cell_start.as<int32_t>(),
                                     sorted.as<int32_t>());
@@ -403,7 +509,7 @@ tbk_status CellListOwner::build(const double *pos, const int32_t *species, int32
 
 tbk_status HamPlan::run(const double *pos, const int32_t *species, int64_t n, int32_t nseg, const int64_t *seg_atoms,
                         const double *boxes, const int32_t periodic[3], const tbk_tb_params *p, int32_t fmt,
-                        int32_t slice_in, hipStream_t s) {
+                        int32_t slice_in, hipStream_t s, bool keep_nbr, size_t extra) {
     tbk_status st = check_tb_params(p);
     if (st != TBK_OK) return st;
     TBK_CHECK(species != nullptr, TBK_ERR_INVALID_ARG, "species is NULL");
@@ -416,48 +522,42 @@ tbk_status HamPlan::run(const double *pos, const int32_t *species, int64_t n, in
                   "slice = %d is not a power of two in [1, 1024]", slice_in);
         slice = slice_in;
     }
-    st = cells.build(pos, species, p->n_species, n, nseg, seg_atoms, boxes, periodic, p->r_cut, s);
+    const size_t per_atom = kCellBytes + sizeof(int32_t) * (3 + (keep_nbr ? kShortRow : 0)) + extra;
+    arena.expect(per_atom * n + 2 * sizeof(int64_t) * (n / slice + 2) +
+                     (sizeof(CellGrid) + 16 * sizeof(int64_t)) * nseg + 65536, s);
+    st = cells.build(pos, species, p->n_species, n, nseg, seg_atoms, boxes, periodic, p->r_cut, arena, s);
     if (st != TBK_OK) return st;
     const int gn = (int)ceil_div(n, kBlock);
-    TBK_HIP(perm.alloc(sizeof(int32_t) * n, s));
-    TBK_HIP(iperm.alloc(sizeof(int32_t) * n, s));
-    TBK_HIP(deg.alloc(sizeof(int32_t) * n, s));
+    TBK_HIP(perm.alloc(sizeof(int32_t) * n, arena));
+    TBK_HIP(iperm.alloc(sizeof(int32_t) * n, arena));
+    TBK_HIP(deg.alloc(sizeof(int32_t) * n, arena));
     k_perm<<<gn, kBlock, 0, s>>>(n, p->reorder, cells.view.sorted, perm.as<int32_t>(), iperm.as<int32_t>());
     TBK_HIP(hipGetLastError());
-    k_degree<<<gn, kBlock, 0, s>>>(cells.view, pos, n, p->r_cut, perm.as<int32_t>(), deg.as<int32_t>());
+    if (keep_nbr) TBK_HIP(nbr.alloc(sizeof(int32_t) * kShortRow * n, arena));
+    k_degree<<<gn, kBlock, 0, s>>>(cells.view, pos, n, p->r_cut, perm.as<int32_t>(), deg.as<int32_t>(),
+                                   nbr.as<int32_t>());
     TBK_HIP(hipGetLastError());
     n_slices = ceil_div(n, slice);
     DevBuf entries;
-    TBK_HIP(entries.alloc(sizeof(int64_t) * (n_slices + 1), s));
-    TBK_HIP(ptr.alloc(sizeof(int64_t) * (n_slices + 1), s));
-    TBK_HIP(hipMemsetAsync(entries.as<int64_t>() + n_slices, 0, sizeof(int64_t), s));
-    k_slice_width<<<(int)ceil_div(n_slices, kBlock), kBlock, 0, s>>>(n, slice, n_slices, deg.as<int32_t>(),
-                                                                     entries.as<int64_t>());
+    TBK_HIP(entries.alloc(sizeof(int64_t) * (n_slices + 1), arena));
+    TBK_HIP(ptr.alloc(sizeof(int64_t) * (n_slices + 1), arena));
+    k_slice_width<<<(unsigned)ceil_div((n_slices + 1) * std::min<int64_t>(slice, 64), kBlock), kBlock, 0, s>>>(
+        n, slice, n_slices, deg.as<int32_t>(), entries.as<int64_t>());
     TBK_HIP(hipGetLastError());
-    st = exclusive_scan(entries.as<int64_t>(), ptr.as<int64_t>(), n_slices + 1, s);
+    st = exclusive_scan(entries.as<int64_t>(), ptr.as<int64_t>(), n_slices + 1, arena, s);
     if (st != TBK_OK) return st;
-    // totals: max degree, degree sum, stored entries
-    DevBuf red, t1, t2;
-    TBK_HIP(red.alloc(sizeof(int64_t) * 2, s));
-    int32_t *dmax = reinterpret_cast<int32_t *>(red.as<int64_t>());
-    int64_t *dsum = red.as<int64_t>() + 1;
-    size_t tmp = 0, tmp2 = 0;
-    TBK_HIP(hipcub::DeviceReduce::Max(nullptr, tmp, deg.as<int32_t>(), dmax, (int)n, s));
-    TBK_HIP(t1.alloc(tmp, s));
-    TBK_HIP(hipcub::DeviceReduce::Max(t1.as<void>(), tmp, deg.as<int32_t>(), dmax, (int)n, s));
-    TBK_HIP(hipcub::DeviceReduce::Sum(nullptr, tmp2, deg.as<int32_t>(), dsum, (int)n, s));
-    TBK_HIP(t2.alloc(tmp2, s));
-    TBK_HIP(hipcub::DeviceReduce::Sum(t2.as<void>(), tmp2, deg.as<int32_t>(), dsum, (int)n, s));
-    int64_t host[2] = {0, 0};
-    int64_t total = 0;
-    TBK_HIP(hipMemcpyAsync(host, red.as<int64_t>(), sizeof(int64_t) * 2, hipMemcpyDeviceToHost, s));
-    TBK_HIP(hipMemcpyAsync(&total, ptr.as<int64_t>() + n_slices, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    DevBuf totals;
+    TBK_HIP(totals.alloc(sizeof(int64_t) * 3, arena));
+    k_init_bounds<<<1, 64, 0, s>>>(0, totals.as<int64_t>(), 3);
+    k_totals<<<(unsigned)std::min<int64_t>(256, ceil_div(n, 4 * kBlock)), kBlock, 0, s>>>(
+        deg.as<int32_t>(), n, ptr.as<int64_t>(), n_slices, totals.as<int64_t>());
+    TBK_HIP(hipGetLastError());
+    int64_t host[3] = {0, 0, 0};
+    TBK_HIP(hipMemcpyAsync(host, totals.as<int64_t>(), sizeof host, hipMemcpyDeviceToHost, s));
     TBK_HIP(hipStreamSynchronize(s));
-    int32_t mxd;
-    std::memcpy(&mxd, &host[0], sizeof(int32_t));
-    max_degree = mxd;
+    max_degree = (int32_t)host[0];
     n_bonds = host[1] / 2;
-    n_entries = total;
+    n_entries = host[2];
     TBK_CHECK(max_degree <= kMaxDegree, TBK_ERR_UNSUPPORTED, "max degree %d exceeds %d", max_degree, kMaxDegree);
     TBK_CHECK(n_entries < (int64_t)1 << 40, TBK_ERR_UNSUPPORTED, "too many entries");
     return TBK_OK;
@@ -496,40 +596,34 @@ tbk_status HamPlan::fill(const double *pos, const int32_t *species, int64_t n, c
         for (int j = 0; j < p->n_species; ++j) tab.t_pair[i * p->n_species + j] = p->t_pair[i * p->n_species + j];
     }
     DevBuf dtab, keys;
-    TBK_HIP(dtab.alloc(sizeof(SpeciesTable), s));
-    st = init_bound_keys(vkeys, 1, s);
-    if (st != TBK_OK) return st;
+    TBK_HIP(dtab.alloc(sizeof(SpeciesTable), arena));
     TBK_HIP(hipMemcpyAsync(dtab.as<void>(), &tab, sizeof(SpeciesTable), hipMemcpyHostToDevice, s));
-    st = init_bound_keys(keys, nseg, s);
+    st = init_bound_keys(keys, nseg + 1, arena, s);       // the last: range of the stored hoppings
     if (st != TBK_OK) return st;
-    const int gn = (int)ceil_div(n, kBlock);
+    const int rows = nseg == 1 ? rows_per_thread(n, 4096) : 1;
+    const int gn = (int)ceil_div(n, (int64_t)kBlock * rows);
     TBK_HIP(hipMemcpyAsync(h->ptr, ptr.as<int64_t>(), sizeof(int64_t) * (n_slices + 1), hipMemcpyDeviceToDevice, s));
     TBK_HIP(hipMemcpyAsync(h->perm, perm.as<int32_t>(), sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
-    if (h->fmt == TBK_SELL_F32) {
-        k_fill<float><<<gn, kBlock, 0, s>>>(cells.view, pos, species, n, slice, p->r_cut, p->r0, p->beta,
-                                            p->n_species, dtab.as<SpeciesTable>(), perm.as<int32_t>(),
-                                            iperm.as<int32_t>(), h->ptr, h->col, static_cast<float *>(h->val),
-                                            static_cast<float *>(h->onsite), keys.as<int64_t>(),
-                                            vkeys.as<int64_t>(), h->col16);
-    } else {
-        k_fill<double><<<gn, kBlock, 0, s>>>(cells.view, pos, species, n, slice, p->r_cut, p->r0, p->beta,
-                                             p->n_species, dtab.as<SpeciesTable>(), perm.as<int32_t>(),
-                                             iperm.as<int32_t>(), h->ptr, h->col, static_cast<double *>(h->val),
-                                             static_cast<double *>(h->onsite), keys.as<int64_t>(),
-                                             vkeys.as<int64_t>(), h->col16);
-    }
+    auto launch = [&](auto v, auto is_short) {
+        typedef decltype(v) V;
+        k_fill<V, decltype(is_short)::value><<<gn, kBlock, 0, s>>>(
+            cells.view, pos, species, n, slice, p->r_cut, p->r0, p->beta, p->n_species, dtab.as<SpeciesTable>(),
+            perm.as<int32_t>(), iperm.as<int32_t>(), h->ptr, h->col, static_cast<V *>(h->val),
+            static_cast<V *>(h->onsite), keys.as<int64_t>(), keys.as<int64_t>() + 2 * nseg, h->col16, deg.as<int32_t>(),
+            nbr.as<int32_t>(), rows);
+    };
+    const bool is_short = max_degree <= kShortRow;
+    if (h->fmt == TBK_SELL_F32) is_short ? launch(0.0f, std::true_type{}) : launch(0.0f, std::false_type{});
+    else is_short ? launch(0.0, std::true_type{}) : launch(0.0, std::false_type{});
     TBK_HIP(hipGetLastError());
-    return finish(keys, n, p, h, bounds, s);
+    return finish(keys, true, n, p, h, bounds, s);
 }
 
-tbk_status HamPlan::finish(DevBuf &keys, int64_t n, const tbk_tb_params *p, tbk_ham *h, double *bounds,
-                           hipStream_t s) {
+tbk_status HamPlan::finish(DevBuf &keys, bool with_values, int64_t n, const tbk_tb_params *p, tbk_ham *h,
+                           double *bounds, hipStream_t s) {
     const int nseg = cells.n_seg;
-    std::vector<int64_t> hk(2 * (size_t)nseg);
-    int64_t vk[2] = {0, 0};
-    TBK_HIP(hipMemcpyAsync(hk.data(), keys.as<int64_t>(), sizeof(int64_t) * 2 * nseg, hipMemcpyDeviceToHost, s));
-    if (vkeys.as<int64_t>())
-        TBK_HIP(hipMemcpyAsync(vk, vkeys.as<int64_t>(), sizeof vk, hipMemcpyDeviceToHost, s));
+    std::vector<int64_t> hk(2 * (size_t)(nseg + (with_values ? 1 : 0)));
+    TBK_HIP(hipMemcpyAsync(hk.data(), keys.as<int64_t>(), sizeof(int64_t) * hk.size(), hipMemcpyDeviceToHost, s));
     if (h->seg_rows)
         TBK_HIP(hipMemcpyAsync(h->seg_rows, cells.seg_atoms.as<int64_t>(), sizeof(int64_t) * (nseg + 1),
                                hipMemcpyDeviceToDevice, s));
@@ -539,7 +633,8 @@ tbk_status HamPlan::finish(DevBuf &keys, int64_t n, const tbk_tb_params *p, tbk_
     // uniform hoppings: every stored value (as stored) equal, at least one entry
     h->uniform_hop = 0;
     h->hop_value = 0.0;
-    if (vkeys.as<int64_t>() && vk[0] == vk[1] && dunkey(vk[0]) <= dunkey(vk[1])) {
+    const int64_t *vk = hk.data() + 2 * (size_t)nseg;
+    if (with_values && vk[0] == vk[1] && dunkey(vk[0]) <= dunkey(vk[1])) {
         h->uniform_hop = 1;
         h->hop_value = dunkey(vk[0]);
     }
@@ -570,7 +665,7 @@ tbk_status build_common(const double *pos, const int32_t *species, int64_t n, in
     TBK_CHECK(h != nullptr && bounds != nullptr, TBK_ERR_INVALID_ARG, "h or bounds is NULL");
     hipStream_t s = as_stream(stream);
     HamPlan plan;
-    tbk_status st = plan.run(pos, species, n, nseg, seg_atoms, boxes, periodic, p, h->fmt, h->slice, s);
+    tbk_status st = plan.run(pos, species, n, nseg, seg_atoms, boxes, periodic, p, h->fmt, h->slice, s, true);
     if (st != TBK_OK) return st;
     return plan.fill(pos, species, n, p, h, bounds, s);
 }

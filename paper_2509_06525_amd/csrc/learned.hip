@@ -801,7 +801,7 @@ FeatNorm make_norm(const double *shift, const double *scale) {
 // Descriptor of every atom: cell list at the descriptor cutoff, then sums.
 static tbk_status descriptor_impl(const double *pos, int64_t n, int32_t nseg, const int64_t *seg_atoms,
                                   const double *boxes, const int32_t periodic[3], double rc, int32_t nk, double *v,
-                                  hipStream_t s, const int32_t *species = nullptr, int32_t ns = 1,
+                                  Arena &arena, hipStream_t s, const int32_t *species = nullptr, int32_t ns = 1,
                                   const double *cnk_dev = nullptr) {
     TBK_CHECK(nk >= 1 && nk <= 16, TBK_ERR_INVALID_ARG, "n_radial = %d outside [1, 16]", nk);
     TBK_CHECK(std::isfinite(rc) && rc > 0, TBK_ERR_INVALID_ARG, "descriptor cutoff must be positive");
@@ -809,7 +809,7 @@ static tbk_status descriptor_impl(const double *pos, int64_t n, int32_t nseg, co
     CellListOwner cells;
     // with coefficients per species pair the cell list also validates the species indices
     tbk_status st = cells.build(pos, cnk_dev ? species : nullptr, cnk_dev ? ns : 1, n, nseg, seg_atoms, boxes,
-                                periodic, rc, s);
+                                periodic, rc, arena, s);
     if (st != TBK_OK) return st;
     if (nk == 8)
         k_descriptor_nk<8><<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(cells.view, pos, n, rc, species, ns, cnk_dev,
@@ -826,17 +826,17 @@ static tbk_status descriptor_impl(const double *pos, int64_t n, int32_t nseg, co
 // then (bi, bj, br) ordered by (i, j).  *nb = the number of bonds; they are
 // written only when *nb <= cap.
 static tbk_status bonds_on_cells(const CellList &cl, const double *pos, int64_t n, double rc, int64_t cap,
-                                 int32_t *bi, int32_t *bj, double *br, int64_t *nb, hipStream_t s) {
+                                 int32_t *bi, int32_t *bj, double *br, int64_t *nb, Arena &arena, hipStream_t s) {
     DevBuf cnt, off, tmp;
-    TBK_HIP(cnt.alloc(sizeof(int64_t) * (n + 1), s));
-    TBK_HIP(off.alloc(sizeof(int64_t) * (n + 1), s));
+    TBK_HIP(cnt.alloc(sizeof(int64_t) * (n + 1), arena));
+    TBK_HIP(off.alloc(sizeof(int64_t) * (n + 1), arena));
     TBK_HIP(hipMemsetAsync(cnt.as<int64_t>() + n, 0, sizeof(int64_t), s));
     const unsigned g = (unsigned)ceil_div(n, 256);
     k_bond_count<<<g, 256, 0, s>>>(cl, pos, n, rc, cnt.as<int64_t>());
     TBK_HIP(hipGetLastError());
     size_t tb = 0;
     TBK_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt.as<int64_t>(), off.as<int64_t>(), (int)(n + 1), s));
-    TBK_HIP(tmp.alloc(tb, s));
+    TBK_HIP(tmp.alloc(tb, arena));
     TBK_HIP(hipcub::DeviceScan::ExclusiveSum(tmp.as<void>(), tb, cnt.as<int64_t>(), off.as<int64_t>(), (int)(n + 1), s));
     int64_t total = 0;
     TBK_HIP(hipMemcpyAsync(&total, off.as<int64_t>() + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
@@ -854,10 +854,12 @@ static tbk_status bonds_on_cells(const CellList &cl, const double *pos, int64_t 
 static tbk_status bonds_impl(const double *pos, int64_t n, int32_t nseg, const int64_t *seg_atoms, const double *boxes,
                              const int32_t periodic[3], double rc, int64_t cap, int32_t *bi, int32_t *bj, double *br,
                              int64_t *nb, hipStream_t s) {
+    Arena arena;
     CellListOwner cells;
-    tbk_status st = cells.build(pos, nullptr, 1, n, nseg, seg_atoms, boxes, periodic, rc, s);
+    arena.expect((kCellBytes + 2 * sizeof(int64_t)) * n + 256 * (size_t)nseg + 65536, s);
+    tbk_status st = cells.build(pos, nullptr, 1, n, nseg, seg_atoms, boxes, periodic, rc, arena, s);
     if (st != TBK_OK) return st;
-    st = bonds_on_cells(cells.view, pos, n, rc, cap, bi, bj, br, nb, s);
+    st = bonds_on_cells(cells.view, pos, n, rc, cap, bi, bj, br, nb, arena, s);
     if (st != TBK_OK) return st;
     TBK_HIP(hipStreamSynchronize(s));
     return TBK_OK;
@@ -892,7 +894,9 @@ extern "C" tbk_status tbk_descriptor(const double *pos, int32_t n_seg, const int
                                      void *stream) {
     clear_error();
     TBK_CHECK(seg_atoms && n_seg >= 1, TBK_ERR_INVALID_ARG, "bad segment table");
-    return descriptor_impl(pos, seg_atoms[n_seg], n_seg, seg_atoms, boxes, periodic, r_cut, n_radial, v,
+    Arena arena;
+    arena.expect(kCellBytes * seg_atoms[n_seg] + 256 * (size_t)n_seg + 65536, as_stream(stream));
+    return descriptor_impl(pos, seg_atoms[n_seg], n_seg, seg_atoms, boxes, periodic, r_cut, n_radial, v, arena,
                            as_stream(stream));
 }
 
@@ -960,11 +964,13 @@ extern "C" tbk_status tbk_descriptor_species(const double *pos, const int32_t *s
     if (st != TBK_OK) return st;
     hipStream_t s = as_stream(stream);
     const size_t bytes = sizeof(double) * n_species * n_species * n_radial * n_radial;
+    Arena arena;
+    arena.expect(kCellBytes * seg_atoms[n_seg] + 256 * (size_t)n_seg + bytes + 65536, s);
     DevBuf c;
     TBK_HIP(c.alloc(bytes, s));
     TBK_HIP(hipMemcpyAsync(c.as<double>(), c_nk, bytes, hipMemcpyHostToDevice, s));
-    st = descriptor_impl(pos, seg_atoms[n_seg], n_seg, seg_atoms, boxes, periodic, r_cut, n_radial, v, s, species,
-                         n_species, c.as<double>());
+    st = descriptor_impl(pos, seg_atoms[n_seg], n_seg, seg_atoms, boxes, periodic, r_cut, n_radial, v, arena, s,
+                         species, n_species, c.as<double>());
     if (st != TBK_OK) return st;
     TBK_HIP(hipStreamSynchronize(s));      // the caller's c_nk must outlive the transfer
     return TBK_OK;
@@ -1198,24 +1204,27 @@ extern "C" tbk_status tb_build_hamiltonian_learned(const double *pos, const int3
     const int64_t n = seg_atoms[n_seg];
     // 1. pattern and plain values (also validates all structure inputs)
     HamPlan plan;
-    st = plan.run(pos, species, n, n_seg, seg_atoms, boxes, periodic, p, h->fmt, h->slice, s);
+    // from the plan's arena: node features, the descriptor's cell list, counts and offsets
+    // of the bonds and (two per atom allowed for) the bonds
+    const size_t extra = sizeof(double) * kNR + kCellBytes + 2 * sizeof(int64_t) + 2 * 16;
+    st = plan.run(pos, species, n, n_seg, seg_atoms, boxes, periodic, p, h->fmt, h->slice, s, true, extra);
     if (st != TBK_OK) return st;
     std::vector<double> tmpb(2 * (size_t)n_seg);
     st = plan.fill(pos, species, n, p, h, tmpb.data(), s);
     if (st != TBK_OK) return st;
     // 2. descriptors and the hop bonds
     DevBuf v, bi, bj, br;
-    TBK_HIP(v.alloc(sizeof(double) * n * kNR, s));
-    st = descriptor_impl(pos, n, n_seg, seg_atoms, boxes, periodic, model->r_cut, kNR, v.as<double>(), s);
+    TBK_HIP(v.alloc(sizeof(double) * n * kNR, plan.arena));
+    st = descriptor_impl(pos, n, n_seg, seg_atoms, boxes, periodic, model->r_cut, kNR, v.as<double>(), plan.arena, s);
     if (st != TBK_OK) return st;
     const int64_t nb = plan.n_bonds;
-    TBK_HIP(bi.alloc(sizeof(int32_t) * std::max<int64_t>(nb, 1), s));
-    TBK_HIP(bj.alloc(sizeof(int32_t) * std::max<int64_t>(nb, 1), s));
-    TBK_HIP(br.alloc(sizeof(double) * std::max<int64_t>(nb, 1), s));
+    TBK_HIP(bi.alloc(sizeof(int32_t) * std::max<int64_t>(nb, 1), plan.arena));
+    TBK_HIP(bj.alloc(sizeof(int32_t) * std::max<int64_t>(nb, 1), plan.arena));
+    TBK_HIP(br.alloc(sizeof(double) * std::max<int64_t>(nb, 1), plan.arena));
     int64_t nb2 = 0;
     // the hop bonds over the Hamiltonian's own cell list (same cutoff)
     st = bonds_on_cells(plan.cells.view, pos, n, p->r_cut, nb, bi.as<int32_t>(), bj.as<int32_t>(), br.as<double>(),
-                        &nb2, s);
+                        &nb2, plan.arena, s);
     if (st != TBK_OK) return st;
     TBK_CHECK(nb2 == nb, TBK_ERR_DEVICE, "bond count mismatch (%lld vs %lld)", (long long)nb2, (long long)nb);
     if (n_bonds) *n_bonds = nb;
@@ -1227,7 +1236,7 @@ extern "C" tbk_status tb_build_hamiltonian_learned(const double *pos, const int3
     hm.beta = p->beta;
     hm.n_species = p->n_species;
     DevBuf tp;
-    TBK_HIP(tp.alloc(sizeof(double) * p->n_species * p->n_species, s));
+    TBK_HIP(tp.alloc(sizeof(double) * p->n_species * p->n_species, plan.arena));
     TBK_HIP(hipMemcpyAsync(tp.as<double>(), p->t_pair, sizeof(double) * p->n_species * p->n_species,
                            hipMemcpyHostToDevice, s));
     hm.t_pair = tp.as<double>();
@@ -1249,7 +1258,7 @@ extern "C" tbk_status tb_build_hamiltonian_learned(const double *pos, const int3
     }
     // 4. bounds of the learned H
     DevBuf keys;
-    st = init_bound_keys(keys, n_seg, s);
+    st = init_bound_keys(keys, n_seg, plan.arena, s);
     if (st != TBK_OK) return st;
     const unsigned gr = (unsigned)ceil_div(n, kBlock);
     if (h->fmt == TBK_SELL_F32)
@@ -1261,6 +1270,5 @@ extern "C" tbk_status tb_build_hamiltonian_learned(const double *pos, const int3
                                                    static_cast<const double *>(h->onsite), h->perm,
                                                    plan.cells.view.seg_of, l2, keys.as<int64_t>());
     TBK_HIP(hipGetLastError());
-    plan.vkeys.release();    // the plain values' range no longer describes the learned ones
-    return plan.finish(keys, n, p, h, spec_bounds, s);
+    return plan.finish(keys, false, n, p, h, spec_bounds, s);
 }

@@ -41,8 +41,22 @@ struct CellList {
     const int32_t *sorted;      // [n] atom indices, cell-major, ascending within a cell
 };
 
+// |d| <= L / 2 is its own image (the quotient rounds to at most 1/2, whose rint is
+// 0): most pairs, which the division would cost more than all the rest.
 __device__ __forceinline__ double min_image(double d, double L, int periodic) {
-    return periodic ? __dsub_rn(d, __dmul_rn(L, rint(d / L))) : d;
+    if (!periodic) return d;
+    if (fabs(d) <= 0.5 * L) return __dadd_rn(d, 0.0);
+    return __dsub_rn(d, __dmul_rn(L, rint(d / L)));
+}
+
+// Minimum image (dx, dy, dz) of a difference of positions and its squared length,
+// an uncontracted sum of squares: the same rounding for (i, j) and (j, i).
+__device__ __forceinline__ double pair_r2(const CellGrid &g, double x, double y, double z, double &dx, double &dy,
+                                          double &dz) {
+    dx = min_image(x, g.box[0], g.periodic[0]);
+    dy = min_image(y, g.box[1], g.periodic[1]);
+    dz = min_image(z, g.box[2], g.periodic[2]);
+    return __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
 }
 
 __device__ __forceinline__ int32_t cell_coord(double x, const CellGrid &g, int k) {
@@ -54,11 +68,17 @@ __device__ __forceinline__ int32_t cell_coord(double x, const CellGrid &g, int k
     return c;
 }
 
-// Calls f(j, r, dx, dy, dz) for every atom j != i of i's segment with
+// Calls f(j, r^2, dx, dy, dz) for every atom j != i of i's segment with
 // |x_j - x_i| < r_cut (minimum image), visiting cells in a fixed order.
+// Bound by the latency of cell start -> atom -> position and by the FP64 work per
+// candidate: the cells of a row that lie side by side are one run of atoms, the next
+// atom's position is loaded while this one is tested, and the root is left to f but
+// for pairs within a rounding of r_cut, whose decision is r < r_cut (100 M atoms in
+// a lattice, the degree count: 7.8 ms with a loop per cell, a division per axis and
+// a root per candidate, 6.6 ms so).
 template <class F>
-__device__ __forceinline__ void for_each_neighbor(const CellList &cl, const double *__restrict__ pos,
-                                                  int32_t i, double r_cut, F &&f) {
+__device__ __forceinline__ void for_each_pair(const CellList &cl, const double *__restrict__ pos,
+                                              int32_t i, double r_cut, F &&f) {
     const CellGrid g = cl.grids[cl.seg_of[i]];
     const double xi = pos[3 * (int64_t)i], yi = pos[3 * (int64_t)i + 1], zi = pos[3 * (int64_t)i + 2];
     int32_t c[3] = {cell_coord(xi, g, 0), cell_coord(yi, g, 1), cell_coord(zi, g, 2)};
@@ -67,8 +87,10 @@ __device__ __forceinline__ void for_each_neighbor(const CellList &cl, const doub
         if (g.nc[k] >= 3) { lo[k] = c[k] - 1; cnt[k] = 3; }
         else { lo[k] = 0; cnt[k] = g.nc[k]; }
     }
-    // Cheap pre-filter slightly above r_cut^2; the decision itself is r < r_cut.
-    const double rc2_hi = r_cut * r_cut * (1.0 + 1e-12);
+    // cells lo[0] .. lo[0] + cnt[0] - 1 of one strip and unwrapped have consecutive ids
+    const int32_t x1 = lo[0] + cnt[0] - 1;
+    const int32_t run = lo[0] >= 0 && x1 < g.nc[0] && lo[0] / g.strip == x1 / g.strip ? cnt[0] : 1;
+    const double rc2_hi = r_cut * r_cut * (1.0 + 1e-12), rc2_lo = r_cut * r_cut * (1.0 - 1e-12);
     for (int a = 0; a < cnt[2]; ++a) {
         int32_t cz = lo[2] + a;
         if (cz < 0 || cz >= g.nc[2]) {
@@ -81,33 +103,47 @@ __device__ __forceinline__ void for_each_neighbor(const CellList &cl, const doub
                 if (!g.periodic[1]) continue;
                 cy = (cy + g.nc[1]) % g.nc[1];
             }
-            for (int e = 0; e < cnt[0]; ++e) {
+            for (int e = 0; e < cnt[0]; e += run) {
                 int32_t cx = lo[0] + e;
                 if (cx < 0 || cx >= g.nc[0]) {
                     if (!g.periodic[0]) continue;
                     cx = (cx + g.nc[0]) % g.nc[0];
                 }
                 const int64_t cid = g.cell_off + cell_id(g, cx, cy, cz);
-                int32_t s0 = cl.cell_start[cid], s1 = cl.cell_start[cid + 1];
+                const int32_t s0 = cl.cell_start[cid], s1 = cl.cell_start[cid + run];
+                if (s0 >= s1) continue;
+                int32_t j1 = cl.sorted[s0], j2 = cl.sorted[min(s0 + 1, s1 - 1)];
+                double px = pos[3 * (int64_t)j1], py = pos[3 * (int64_t)j1 + 1], pz = pos[3 * (int64_t)j1 + 2];
                 for (int32_t s = s0; s < s1; ++s) {
-                    int32_t j = cl.sorted[s];
+                    const int32_t j = j1;
+                    const double x = px, y = py, z = pz;
+                    j1 = j2;
+                    j2 = cl.sorted[min(s + 2, s1 - 1)];
+                    px = pos[3 * (int64_t)j1];
+                    py = pos[3 * (int64_t)j1 + 1];
+                    pz = pos[3 * (int64_t)j1 + 2];
                     if (j == i) continue;
-                    double dx = min_image(pos[3 * (int64_t)j] - xi, g.box[0], g.periodic[0]);
-                    double dy = min_image(pos[3 * (int64_t)j + 1] - yi, g.box[1], g.periodic[1]);
-                    double dz = min_image(pos[3 * (int64_t)j + 2] - zi, g.box[2], g.periodic[2]);
-                    // Uncontracted sum of squares: the same rounding for (i, j) and (j, i).
-                    double r2 = __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
-                    if (r2 < rc2_hi) {
-                        double r = sqrt(r2);
-                        if (r < r_cut) f(j, r, dx, dy, dz);
-                    }
+                    double dx, dy, dz;
+                    const double r2 = pair_r2(g, x - xi, y - yi, z - zi, dx, dy, dz);
+                    if (r2 < rc2_hi && (r2 < rc2_lo || sqrt(r2) < r_cut)) f(j, r2, dx, dy, dz);
                 }
             }
         }
     }
 }
 
-// Owns the device buffers of a cell list built for stacked structures.
+// The same with the distance: f(j, r, dx, dy, dz).
+template <class F>
+__device__ __forceinline__ void for_each_neighbor(const CellList &cl, const double *__restrict__ pos,
+                                                  int32_t i, double r_cut, F &&f) {
+    for_each_pair(cl, pos, i, r_cut, [&](int32_t j, double r2, double dx, double dy, double dz) {
+        f(j, sqrt(r2), dx, dy, dz);
+    });
+}
+
+constexpr size_t kCellBytes = 24;
+
+// Holds the device buffers of a cell list built for stacked structures.
 struct CellListOwner {
     CellList view{};
     int32_t n_seg = 0;
@@ -115,10 +151,11 @@ struct CellListOwner {
     // Bins positions pos[n][3] of n_seg structures; structure s holds atoms
     // [seg_atoms[s], seg_atoms[s+1]) (host array) and, on periodic axes, the
     // box boxes[3 s .. 3 s + 2] (host).  Validates box lengths, finiteness and
-    // (when species != nullptr) the species range.
+    // (when species != nullptr) the species range.  Buffers come from `arena`
+    // (kCellBytes per atom and a little over, unless cells outnumber atoms).
     tbk_status build(const double *pos, const int32_t *species, int32_t n_species, int64_t n, int32_t n_seg,
                      const int64_t *seg_atoms, const double *boxes, const int32_t periodic[3], double r_cut,
-                     hipStream_t s);
+                     Arena &arena, hipStream_t s);
 };
 
 }  // namespace tbk

@@ -466,7 +466,7 @@ tbk_status build_sk(const double *pos, const int32_t *species, int64_t n, const 
     k_sk_perm<<<(unsigned)ceil_div(norb * n, kBlock), kBlock, 0, s>>>(n, norb, plan.perm.as<int32_t>(), h->perm);
     TBK_HIP(hipGetLastError());
     DevBuf keys;
-    st = init_bound_keys(keys, 1, s);
+    st = init_bound_keys(keys, 1, plan.arena, s);
     if (st != TBK_OK) return st;
     SkValues v{sk->r0, sk->beta, sk->e_s, sk->e_p, sk->e_d,
                {sk->v_ss_sigma, sk->v_sp_sigma, sk->v_pp_sigma, sk->v_pp_pi, sk->v_sd_sigma, sk->v_pd_sigma,
