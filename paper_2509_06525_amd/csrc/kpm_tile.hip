@@ -12,6 +12,7 @@ namespace {
 
 constexpr int kPlanThreads = 512;
 constexpr int kHaloMax = 2048;         // halo rows a tile can list
+constexpr int kLocalBond = 256;        // rows between the ends of a bond inside a strip, at most (about two lines of cells)
 constexpr int kHashSize = 4096;        // open addressing, at most kHaloMax + kPlanThreads keys
 constexpr int kTileMaxW = 6;           // entries per row
 constexpr size_t kTilePartialBudget = 64ull << 20;
@@ -37,9 +38,11 @@ __global__ void k_tile_rows(int64_t n, int32_t n_tiles, int32_t S, int32_t *__re
     }
 }
 
-// Halves the tiles whose halo does not fit (the builder orders rows in strips of
-// cells; a tile across a strip's end has two edges more than its neighbours and
-// would set the steps per launch for all of them).  The rings k asked of every tile
+// Cuts the tiles across a strip's end in two there (the builder orders rows in strips
+// of cells; such a tile is two patches of the sheet, with two edges more than its
+// neighbours, and would set the steps per launch for all of them: 96 snapshots of 1,000
+// to 50,000 atoms, 8 vectors, 15.8 ms with tiles halved anywhere, 13.1 so), and halves
+// those whose halo does not fit.  The rings k asked of every tile
 // are those with the most steps per tile, k over the number of tiles that result:
 // where only a few tiles reach S (long bonds), halving the rest costs more than
 // the rings are worth (1 M rows of up to 5 entries, four vectors: 16.0 us a step at
@@ -52,23 +55,35 @@ __global__ __launch_bounds__(1024) void k_tile_split(const int32_t *__restrict__
                                                      int32_t *__restrict__ tseg, TileInfo *__restrict__ info) {
     __shared__ int32_t sum[1024];
     __shared__ int32_t reach[kTileMaxS + 1];      // tiles of just so many rings
+    __shared__ int32_t cuts;
     const int tid = threadIdx.x;
     const int per = (n_tiles + 1023) / 1024;
     const int t0 = min(tid * per, n_tiles), t1 = min(t0 + per, n_tiles);
     if (tid <= kTileMaxS) reach[tid] = 0;
     __syncthreads();
-    for (int t = t0; t < t1; ++t) atomicAdd(&reach[min(max(rings[t], 0), S)], 1);
+    if (tid == 0) cuts = 0;
     __syncthreads();
+    for (int t = t0; t < t1; ++t) {
+        atomicAdd(&reach[rings[t] >> 8 ? S : min(rings[t] & 255, S)], 1);
+        if (rings[t] >> 8) atomicAdd(&cuts, 1);
+    }
+    __syncthreads();
+    const int base = n_tiles + cuts;
     int need = 1;
-    int64_t need_tiles = n_tiles;
+    int64_t need_tiles = base;
     for (int k = 1, less = 0; k <= S; ++k) {
         less += reach[k - 1];
-        if (n_tiles + less <= most && k * need_tiles >= (int64_t)need * (n_tiles + less)) {
+        if (base + less <= most && k * need_tiles >= (int64_t)need * (base + less)) {
             need = k;
-            need_tiles = n_tiles + less;
+            need_tiles = base + less;
         }
     }
-    auto pieces = [&](int t) { return rings[t] < need && first[t + 1] - first[t] >= 2 ? 2 : 1; };
+    // rows of tile t's first piece (all of them: one piece)
+    auto piece = [&](int t) {
+        const int len = first[t + 1] - first[t], cut = rings[t] >> 8;
+        return cut ? cut : ((rings[t] & 255) < need && len >= 2 ? len / 2 : len);
+    };
+    auto pieces = [&](int t) { return piece(t) < first[t + 1] - first[t] ? 2 : 1; };
     int c = 0;
     for (int t = t0; t < t1; ++t) c += pieces(t);
     sum[tid] = c;
@@ -83,9 +98,9 @@ __global__ __launch_bounds__(1024) void k_tile_split(const int32_t *__restrict__
     const bool split = total <= most;       // otherwise the tiles stay as they are
     int q = split ? sum[tid] - c : t0;
     for (int t = t0; t < t1; ++t) {
-        const int lo = first[t], len = first[t + 1] - lo, np = split ? pieces(t) : 1;
+        const int lo = first[t], np = split ? pieces(t) : 1;
         for (int k = 0; k < np; ++k, ++q) {
-            row0[q] = lo + (int)((int64_t)len * k / np);
+            row0[q] = lo + (k ? piece(t) : 0);
             if (seg) tseg[q] = seg[t];
         }
     }
@@ -104,7 +119,7 @@ struct TilePlanArgs {
     uint16_t *lcol1;
     void *tval, *tons;
     TileInfo *info;
-    int32_t *rings;          // PROBE: complete rings of each tile
+    int32_t *rings;          // PROBE: complete rings and cut of each tile
     int32_t log2_slice, S, W, cap;
 };
 
@@ -113,7 +128,9 @@ struct TilePlanArgs {
 // local index when first met, so a ring follows the order of the rows that reach
 // it.  The order within a ring is not reproducible, the results are: every value
 // depends on its own row's entries only, and only the tile's rows are summed.
-// PROBE: only counts the rings that fit.
+// PROBE: counts the rings that fit, and looks for the end of a strip among the rows
+// (no bond to a row within kLocalBond after crosses it): rings[t] = rings | cut << 8,
+// cut = 0 or the row of the tile that starts the next strip.
 template <class VT, bool PROBE>
 __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(TilePlanArgs a) {
     __shared__ int32_t keys[kHashSize];
@@ -122,7 +139,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(TilePlanArgs a) {
     __shared__ int32_t s_count, s_over;
     const int t = blockIdx.x, tid = threadIdx.x;
     const int row0 = a.row0[t], nr = a.row0[t + 1] - row0;
-    if (nr == 0) return;
+    if (nr == 0) {
+        if (PROBE && tid == 0) a.rings[t] = a.S;
+        return;
+    }
     const int cap_h = min(a.cap - nr, kHaloMax);
     const int64_t smask = ((int64_t)1 << a.log2_slice) - 1, stride = smask + 1;
     for (int i = tid; i < kHashSize; i += kPlanThreads) keys[i] = -1;
@@ -192,11 +212,60 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(TilePlanArgs a) {
         done = k;
         if (!PROBE && tid == 0) cnt[k] = nr + now;
     }
+    __syncthreads();
     if constexpr (PROBE) {
-        if (tid == 0) a.rings[t] = done;
+        if (nr > kHashSize) {
+            if (tid == 0) a.rings[t] = done;
+            return;
+        }
+        // place i of d: summed up to it, the rows with a bond, to a row at most kLocalBond after
+        // them, across the gap between rows i and i + 1
+        int32_t *d = keys, *part = list;
+        if (tid == 0) { s_count = 0; s_over = INT32_MAX; }
+        for (int i = tid; i < nr; i += kPlanThreads) d[i] = 0;
+        __syncthreads();
+        for (int j = tid; j < nr; j += kPlanThreads) {
+            int64_t base;
+            int w;
+            int32_t cc[kTileMaxW];
+            entries(row0 + j, base, w);
+            columns(row0 + j, base, w, cc);
+            int far = j;
+#pragma unroll
+            for (int q = 0; q < kTileMaxW; ++q) {
+                const int c = cc[q] - row0;
+                if (c <= j + kLocalBond && c < nr) far = max(far, c);
+            }
+            if (far > j) {
+                atomicAdd(&d[j], 1);
+                atomicAdd(&d[far], -1);
+            }
+        }
+        __syncthreads();
+        const int per = (nr + kPlanThreads - 1) / kPlanThreads;
+        const int i0 = min(tid * per, nr), i1 = min(i0 + per, nr);
+        int sum = 0;
+        for (int i = i0; i < i1; ++i) sum += d[i];
+        part[tid] = sum;
+        __syncthreads();
+        for (int o = 1; o < kPlanThreads; o <<= 1) {
+            const int x = tid >= o ? part[tid - o] : 0;
+            __syncthreads();
+            part[tid] += x;
+            __syncthreads();
+        }
+        int over = part[tid] - sum;
+        for (int i = i0; i < i1; ++i) {
+            over += d[i];
+            if (over != 0 || i + 1 < nr / 16 || i + 1 > nr - nr / 16 || i + 1 == nr) continue;
+            atomicAdd(&s_count, 1);
+            atomicMin(&s_over, abs(i + 1 - nr / 2) << 16 | (i + 1));
+        }
+        __syncthreads();
+        // many such gaps: rows of no order
+        if (tid == 0) a.rings[t] = done | (s_count >= 1 && s_count <= 4 ? (s_over & 0xffff) << 8 : 0);
         return;
     }
-    __syncthreads();
     if (tid == 0) {
         atomicMin(&a.info->rings, done);
         for (int k = 0; k <= done; ++k) atomicAdd(&a.info->rows[k], (unsigned long long)cnt[k]);
@@ -406,7 +475,7 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
         }
         tp.S = (f64 || tp.shape == kTileSmall) && tp.tile_rows > tp.cap * 2 / 5 ? 6 : 8;
         tp.n_first = ceil_div(n, tp.tile_rows) + (n_seg > 1 ? n_seg : 0);   // a partial tile per structure
-        tp.n_tiles = tp.n_first + tp.n_first / 8 + 8;                       // room for halved tiles
+        tp.n_tiles = tp.n_first + tp.n_first / 8 + 8 + (n_seg > 1 ? 2 * n_seg : 0);      // room for tiles cut in two
     }
     const size_t per_step = (size_t)tp.n_tiles * pl.Rv * sizeof(double);
     tp.reduce_every = (int)std::min<size_t>(kTilePartialBudget / per_step, (size_t)std::min(pl.Mr, 4096));

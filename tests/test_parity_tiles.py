@@ -128,7 +128,8 @@ def test_either_form_continues_the_other(k0, k1, R):
 
 
 @pytest.mark.parametrize("fmt,prec,R", [("sell_f32", "c32", 8), ("sell_f32", "c32", 1), ("sell_f64", "f64", 3)])
-@pytest.mark.parametrize("dims", [((5, 7), (9, 8)), ((6, 8), (40, 44), (90, 80), (31, 40))])
+@pytest.mark.parametrize("dims", [((5, 7), (9, 8)), ((6, 8), (40, 44), (90, 80), (31, 40)),
+                                  ((55, 60), (57, 150), (3, 90), (110, 50))])     # strips of a few cells
 def test_stacked_tiles_equal_the_stacked_sweep(fmt, prec, R, dims):
     """Structures of one tile and of several; each against its own run, too."""
     snaps = [synth.graphene_sheet(nx, ny, 0.04 + 0.02 * k, k) for k, (nx, ny) in enumerate(dims)]
