@@ -317,10 +317,11 @@ __global__ __launch_bounds__(kThreads) void k_reduce_l1(const double *__restrict
 }
 
 // Second level: mu[v][n] = sum over chunks of l1[n][v][c], in chunk order, for
-// the moments n0 <= n < M.
+// the moments n0 <= n < M.  Clears the flag of k_guard.
 __global__ void k_reduce_l2(const double *__restrict__ l1, int32_t R, int32_t M, int32_t n0, int32_t n_chunks,
-                            double *__restrict__ mu) {
+                            double *__restrict__ mu, int32_t *__restrict__ flag) {
     int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (idx == 0) *flag = 0;
     if (idx >= (int64_t)R * (M - n0)) return;
     const int64_t n = n0 + idx / R, v = idx % R;
     const double *p = l1 + (n * R + v) * n_chunks;
@@ -331,10 +332,12 @@ __global__ void k_reduce_l2(const double *__restrict__ l1, int32_t R, int32_t M,
 
 // flag = 1 if some |mu_n|, n0 <= n < M, exceeds mu_0 (1 + 1e-6) or is not
 // finite.  A fresh run (n0 = 0) keeps mu_0 of every vector in mu0 for the
-// runs that continue it; a continued run reads it from there.
+// runs that continue it; a continued run reads it from there.  Writes the record of
+// the run at the head of the workspace.
 __global__ void k_guard(const double *__restrict__ mu, int32_t R, int32_t M, int32_t n0, double *__restrict__ mu0,
-                        int32_t *__restrict__ flag) {
+                        int32_t *__restrict__ flag, KpmState st, KpmState *__restrict__ dst) {
     int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (idx == 0) *dst = st;
     if (idx >= (int64_t)R * (M - n0)) return;
     const int64_t v = idx / (M - n0), n = n0 + idx % (M - n0);
     const double m0 = n0 == 0 ? mu[v * M] : mu0[v];
@@ -342,20 +345,6 @@ __global__ void k_guard(const double *__restrict__ mu, int32_t R, int32_t M, int
     if (n == 0) mu0[v] = m0;
     if (!(fabs(m) <= m0 * (1.0 + 1e-6))) atomicOr(flag, 1);
 }
-
-// x[0..n) = value (a kernel rather than a memset node, so the clears stay
-// ordinary kernels under stream capture).
-__global__ void k_fill_i32(int32_t *__restrict__ x, int32_t n, int32_t value) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] = value;
-}
-
-// Record of a completed run at the head of the workspace.
-__global__ void k_store_state(KpmState st, KpmState *__restrict__ dst) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = st;
-}
-
-
 
 // rows_per_thread 4 is instantiated for one vector per row on width-3 slices
 // (the latency-bound case: 44-56 B per row); elsewhere it runs as 2.
@@ -435,16 +424,14 @@ tbk_status finish_run(const tbk_ham *h, const KpmPlan &pl, double a, double b, i
     const int n0 = pl.n_start, Rv = pl.Rv, Mr = pl.Mr;
     const int64_t nm = (int64_t)R * (M - n0);
     if (dbl) {
-        k_reduce_l2<<<(unsigned)ceil_div((int64_t)Rv * Mr, 256), 256, 0, s>>>(l1, Rv, Mr, 0, n_chunks, raw);
+        k_reduce_l2<<<(unsigned)ceil_div((int64_t)Rv * Mr, 256), 256, 0, s>>>(l1, Rv, Mr, 0, n_chunks, raw, flag);
         TBK_HIP(hipGetLastError());
         k_doubling_combine<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(raw, Mr - 1, VPT, R, M, mu);
     } else {
-        k_reduce_l2<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(l1, R, M, n0, n_chunks, mu);
+        k_reduce_l2<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(l1, R, M, n0, n_chunks, mu, flag);
     }
     TBK_HIP(hipGetLastError());
     if (pair) return TBK_OK;
-    k_fill_i32<<<1, 64, 0, s>>>(flag, 1, 0);
-    k_guard<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(mu, R, M, n0, mu0, flag);
     KpmState rec{};
     rec.magic = dbl ? 0 : kStateMagic;    // the doubling form keeps no state to continue from
     rec.n_rows = h->n_rows;
@@ -455,7 +442,7 @@ tbk_status finish_run(const tbk_ham *h, const KpmPlan &pl, double a, double b, i
     rec.next_n = M;
     rec.a = a;
     rec.b = b;
-    k_store_state<<<1, 64, 0, s>>>(rec, state);
+    k_guard<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(mu, R, M, n0, mu0, flag, rec, state);
     TBK_HIP(hipGetLastError());
     int32_t hflag = 0;
     TBK_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));

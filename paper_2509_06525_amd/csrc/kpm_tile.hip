@@ -320,62 +320,91 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(TilePlanArgs a) {
     }
 }
 
+// Elements a block turns from [row][vector] to [vector][row] or back at a time: they
+// pass through LDS, since with 32 vectors a wavefront that writes planes straight from
+// rows writes 16 bytes to each (4 M rows, 32 vectors, 200 moments: the call 49.3 ms with
+// planes written straight, 47.4 so).
+constexpr int kTurn = 2048;
+
 // Start of a run.  MODE 0: start vectors r (caller's order, or seeded phases) to
 // row order [rows][Rp] (r_int) and planes; sums of |r|^2 per tile.  MODE 1 (pair
 // form): start and left, [rows][Rp] in row order, to planes; sums of
-// Re <left|start>.  A block per tile; thread e takes elements e, e + 256, ... of
-// the tile's [row][vector] range, all of one vector.
-template <class VT, int MODE, bool DBL>
-__global__ __launch_bounds__(kThreads) void k_tile_prepare(const VT *__restrict__ r, const VT *__restrict__ left,
+// Re <left|start>.  A block per tile; thread e takes elements e, e + NT, ... of
+// the tile's [row][vector] range, all of one vector.  One tile: NT = 1024, as nothing
+// else is there to hide its latencies.
+template <class VT, int NT, int MODE, bool DBL>
+__global__ __launch_bounds__(NT) void k_tile_prepare(const VT *__restrict__ r, const VT *__restrict__ left,
                                                            const int32_t *__restrict__ perm,
                                                            const int32_t *__restrict__ row0, int64_t rows, int32_t R,
                                                            int32_t Rp, int32_t seeded, uint64_t seed,
                                                            VT *__restrict__ r_int, VT *__restrict__ plane,
                                                            VT *__restrict__ lplane, double *__restrict__ partial) {
-    __shared__ double red[kThreads];
-    const int t = blockIdx.x;
+    typedef std::conditional_t<sizeof(VT) == 4, f2v, d2v> C2;
+    constexpr int E = (NT == kThreads ? 1 : 2) * (MODE == 0 ? kTurn : kTurn / 2), NK = E / NT;
+    __shared__ double red[NT];
+    __shared__ C2 turn[MODE == 0 ? 1 : 2][E + kThreads];      // [vector][rows of the chunk + 1]
+    const int t = blockIdx.x, tid = threadIdx.x;
     const int64_t i0 = row0[t];
-    const int ne = (row0[t + 1] - row0[t]) * Rp;
-    const int v = threadIdx.x % Rp;
+    const int nr = row0[t + 1] - row0[t], ne = nr * Rp;
+    const int v = tid % Rp, rb = E / Rp;
+    const C2 *cr = reinterpret_cast<const C2 *>(r), *cl = reinterpret_cast<const C2 *>(left);
+    const bool to_planes = MODE == 1 || plane != r_int;
     double acc = 0.0;
-    for (int e = threadIdx.x; e < ne; e += kThreads) {
-        const int64_t i = i0 + e / Rp;
-        const int64_t o = 2 * (i * Rp + v), po = 2 * ((int64_t)v * rows + i);
-        if constexpr (MODE == 0) {
-            VT re = 0, im = 0;
-            if (v < R) {
-                const int64_t src = perm ? (int64_t)perm[i] : i;
+    for (int c0 = 0; c0 < ne; c0 += E) {
+        const int j0 = c0 / Rp;              // first row of the chunk
+        C2 x[NK], y[MODE == 0 ? 1 : NK];
+        int64_t src[NK];
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            const int64_t i = i0 + min(c0 + k * NT + tid, ne - 1) / Rp;
+            src[k] = MODE == 0 && perm ? (int64_t)perm[i] : i;
+        }
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            x[k].x = x[k].y = 0;
+            if (v >= R) continue;
+            if constexpr (MODE == 0) {
                 if (seeded) {
                     double c, sn;
-                    seeded_phase(seed, (uint64_t)src * (uint64_t)R + (uint64_t)v, c, sn);
-                    re = (VT)c;
-                    im = (VT)sn;
+                    seeded_phase(seed, (uint64_t)src[k] * (uint64_t)R + (uint64_t)v, c, sn);
+                    x[k].x = (VT)c;
+                    x[k].y = (VT)sn;
                 } else {
-                    re = r[2 * (src * R + v)];
-                    im = r[2 * (src * R + v) + 1];
+                    x[k] = cr[src[k] * R + v];
                 }
+            } else {
+                x[k] = cr[src[k] * Rp + v];
+                y[k] = cl[src[k] * Rp + v];
             }
-            if (r_int) {
-                r_int[o] = re;
-                r_int[o + 1] = im;
-            }
-            if (plane != r_int && v < R) {
-                plane[po] = re;
-                plane[po + 1] = im;
-            }
-            acc += (double)re * (double)re + (double)im * (double)im;
-        } else if (v < R) {
-            const VT re = r[o], im = r[o + 1], lr = left[o], li = left[o + 1];
-            plane[po] = re;
-            plane[po + 1] = im;
-            lplane[po] = lr;
-            lplane[po + 1] = li;
-            acc += (double)lr * (double)re + (double)li * (double)im;
         }
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            const int e = c0 + k * NT + tid;
+            if (e >= ne) continue;
+            const int j = e / Rp;
+            if constexpr (MODE == 0) {
+                if (r_int) reinterpret_cast<C2 *>(r_int)[i0 * Rp + e] = x[k];
+                acc += (double)x[k].x * (double)x[k].x + (double)x[k].y * (double)x[k].y;
+            } else if (v < R) {
+                turn[MODE == 0 ? 0 : 1][v * (rb + 1) + j - j0] = y[k];
+                acc += (double)y[k].x * (double)x[k].x + (double)y[k].y * (double)x[k].y;
+            }
+            if (to_planes) turn[0][v * (rb + 1) + j - j0] = x[k];
+        }
+        if (!to_planes) continue;
+        __syncthreads();
+        for (int f = tid; f < E; f += NT) {
+            const int pv = f / rb, j = f % rb;
+            if (pv >= R || j0 + j >= nr) continue;
+            const int64_t o = (int64_t)pv * rows + i0 + j0 + j;
+            reinterpret_cast<C2 *>(plane)[o] = turn[0][pv * (rb + 1) + j];
+            if constexpr (MODE == 1) reinterpret_cast<C2 *>(lplane)[o] = turn[1][pv * (rb + 1) + j];
+        }
+        __syncthreads();
     }
     red[threadIdx.x] = acc;
     __syncthreads();
-    for (int g = kThreads / 2; g >= Rp; g >>= 1) {
+    for (int g = NT / 2; g >= Rp; g >>= 1) {
         if ((int)threadIdx.x < g) red[threadIdx.x] += red[threadIdx.x + g];
         __syncthreads();
     }
@@ -411,24 +440,39 @@ __global__ __launch_bounds__(kThreads) void k_tile_overlap(const VT *__restrict_
     }
 }
 
-// [rows][Rp] <-> planes [vector][rows] for the R vectors (TO: into planes; the
-// padded columns of the row form are zero).
+// [rows][Rp] <-> planes [vector][rows] for the R vectors of up to three sets (grid y;
+// TO: into planes; the padded columns of the row form are zero).
+template <class VT> struct PlaneSets {
+    VT *x[3], *plane[3];
+};
 template <class VT, bool TO>
-__global__ __launch_bounds__(kThreads) void k_planes(VT *__restrict__ x, VT *__restrict__ plane, int64_t rows,
-                                                     int32_t R, int32_t Rp) {
-    const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (idx >= rows * Rp) return;
-    const int64_t i = idx / Rp;
-    const int v = (int)(idx % Rp);
-    const int64_t po = 2 * ((int64_t)v * rows + i);
-    if constexpr (TO) {
-        if (v < R) {
-            plane[po] = x[2 * idx];
-            plane[po + 1] = x[2 * idx + 1];
-        }
-    } else {
-        x[2 * idx] = v < R ? plane[po] : (VT)0;
-        x[2 * idx + 1] = v < R ? plane[po + 1] : (VT)0;
+__global__ __launch_bounds__(kThreads) void k_planes(PlaneSets<VT> ps, int64_t rows, int32_t R, int32_t Rp) {
+    typedef std::conditional_t<sizeof(VT) == 4, f2v, d2v> C2;
+    __shared__ C2 turn[kTurn + kThreads];
+    const int set = blockIdx.y, rb = kTurn / Rp;
+    C2 *x = reinterpret_cast<C2 *>(set == 0 ? ps.x[0] : (set == 1 ? ps.x[1] : ps.x[2]));
+    C2 *plane = reinterpret_cast<C2 *>(set == 0 ? ps.plane[0] : (set == 1 ? ps.plane[1] : ps.plane[2]));
+    const int64_t i0 = (int64_t)blockIdx.x * rb;
+    const int nr = (int)min((int64_t)rb, rows - i0);
+    // thread order of the row form (e = row * Rp + vector) and of the planes (f = vector * rb + row)
+#pragma unroll
+    for (int k = 0; k < kTurn / kThreads; ++k) {
+        const int f = k * kThreads + threadIdx.x;
+        const int j = TO ? f / Rp : f % rb, v = TO ? f % Rp : f / rb;
+        if (j >= nr) continue;
+        C2 y;
+        y.x = y.y = 0;
+        if (v < R) y = TO ? x[i0 * Rp + f] : plane[(int64_t)v * rows + i0 + j];
+        turn[v * (rb + 1) + j] = y;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kTurn / kThreads; ++k) {
+        const int f = k * kThreads + threadIdx.x;
+        const int j = TO ? f % rb : f / Rp, v = TO ? f / rb : f % Rp;
+        if (j >= nr) continue;
+        if (!TO) x[i0 * Rp + f] = turn[v * (rb + 1) + j];
+        else if (v < R) plane[(int64_t)v * rows + i0 + j] = turn[v * (rb + 1) + j];
     }
 }
 
@@ -633,7 +677,8 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
     const int n_chunks = (int)ceil_div(run.n_tiles, kReduceChunk);
     const int32_t *row0 = reinterpret_cast<const int32_t *>(work + tp.off_row0);
     const unsigned gt = (unsigned)run.n_tiles;
-    const unsigned ge = (unsigned)ceil_div(n * Rp, kThreads);
+    const bool one = run.n_tiles == 1;
+    const unsigned ge = (unsigned)ceil_div(n * Rp, kTurn);
 
     if (pair) {
         if (direct || planes) {
@@ -642,21 +687,24 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
             k_tile_overlap<VT><<<dim3(gt, R), kThreads, 0, s>>>(start, left, row0, n, Rp, part);
         } else {
             sp = plane(5);
-            k_tile_prepare<VT, 1, false><<<gt, kThreads, 0, s>>>(start, left, nullptr, row0, n, R, Rp, 0, 0, nullptr,
-                                                                  sp, rp, part);
+            if (one) k_tile_prepare<VT, 1024, 1, false><<<gt, 1024, 0, s>>>(start, left, nullptr, row0, n, R, Rp, 0, 0,
+                                                                           nullptr, sp, rp, part);
+            else k_tile_prepare<VT, kThreads, 1, false><<<gt, kThreads, 0, s>>>(start, left, nullptr, row0, n, R, Rp, 0,
+                                                                                0, nullptr, sp, rp, part);
         }
     } else if (n_start == 0) {
-        if (dbl)
-            k_tile_prepare<VT, 0, true><<<gt, kThreads, 0, s>>>(r, nullptr, h->perm, row0, n, R, Rp,
-                                                                 pl.seeded ? 1 : 0, pl.seed, r_int, rp, nullptr, part);
-        else
-            k_tile_prepare<VT, 0, false><<<gt, kThreads, 0, s>>>(r, nullptr, h->perm, row0, n, R, Rp,
-                                                                  pl.seeded ? 1 : 0, pl.seed, r_int, rp, nullptr,
-                                                                  part);
+        const int seeded = pl.seeded ? 1 : 0;
+        auto prepare = [&](auto d) {
+            constexpr bool D = decltype(d)::value;
+            if (one) k_tile_prepare<VT, 1024, 0, D><<<gt, 1024, 0, s>>>(r, nullptr, h->perm, row0, n, R, Rp, seeded,
+                                                                       pl.seed, r_int, rp, nullptr, part);
+            else k_tile_prepare<VT, kThreads, 0, D><<<gt, kThreads, 0, s>>>(r, nullptr, h->perm, row0, n, R, Rp,
+                                                                            seeded, pl.seed, r_int, rp, nullptr, part);
+        };
+        if (dbl) prepare(std::true_type{});
+        else prepare(std::false_type{});
     } else if (!direct) {
-        k_planes<VT, true><<<ge, kThreads, 0, s>>>(r_int, rp, n, R, Rp);
-        k_planes<VT, true><<<ge, kThreads, 0, s>>>(T[0], P[0][0], n, R, Rp);
-        k_planes<VT, true><<<ge, kThreads, 0, s>>>(T[1], P[0][1], n, R, Rp);
+        k_planes<VT, true><<<dim3(ge, 3), kThreads, 0, s>>>({{r_int, T[0], T[1]}, {rp, P[0][0], P[0][1]}}, n, R, Rp);
     }
     TBK_HIP(hipGetLastError());
 
@@ -716,13 +764,14 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
     reduce(batch0, pl.Mr - batch0);
     TBK_HIP(hipGetLastError());
     if (!pair && !dbl) {           // the state of the run, in row order
-        for (int q = 0; q < 2; ++q) {
-            const VT *x = q ? prev : cur;          // T_at, T_{at-1}
-            VT *y = T[(at + q) & 1];
-            if (!direct) k_planes<VT, false><<<ge, kThreads, 0, s>>>(y, const_cast<VT *>(x), n, R, Rp);
-            else if (x != y)
-                TBK_HIP(hipMemcpyAsync(y, x, sizeof(VT) * 2 * (size_t)n, hipMemcpyDeviceToDevice, s));
-        }
+        VT *y[2] = {T[at & 1], T[(at + 1) & 1]};          // of T_at, T_{at-1}
+        const VT *x[2] = {cur, prev};
+        if (!direct)
+            k_planes<VT, false><<<dim3(ge, 2), kThreads, 0, s>>>(
+                {{y[0], y[1], nullptr}, {const_cast<VT *>(x[0]), const_cast<VT *>(x[1]), nullptr}}, n, R, Rp);
+        for (int q = 0; q < 2 && direct; ++q)
+            if (x[q] != y[q])
+                TBK_HIP(hipMemcpyAsync(y[q], x[q], sizeof(VT) * 2 * (size_t)n, hipMemcpyDeviceToDevice, s));
         TBK_HIP(hipGetLastError());
     }
     return finish_run<VT>(h, pl, a, b, R, M, work, mu, s, pair, dbl, 1, l1, n_chunks, timed);
@@ -737,7 +786,7 @@ template <class VT>
 void tile_start_planes(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, const VT *r, int32_t R, char *work,
                        VT *rp, double *part, hipStream_t s) {
     const int32_t *row0 = reinterpret_cast<const int32_t *>(work + pl.tile.off_row0);
-    k_tile_prepare<VT, 0, false><<<(unsigned)run.n_tiles, kThreads, 0, s>>>(
+    k_tile_prepare<VT, kThreads, 0, false><<<(unsigned)run.n_tiles, kThreads, 0, s>>>(
         r, nullptr, h->perm, row0, h->n_rows, R, pl.Rp, 0, 0, nullptr, rp, nullptr, part);
 }
 
