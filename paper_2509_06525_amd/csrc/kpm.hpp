@@ -33,6 +33,7 @@ struct TileRun {
     int s = 0;
     int n_tiles = 0;
     bool closed = false;
+    bool uniform = false;      // every entry has the first one's value
 };
 
 struct KpmPlan {

@@ -22,6 +22,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct TileInfo {                       // what the host reads back
     int32_t rings;                      // rings complete in every tile
     int32_t n_tiles;                    // tiles after the split
+    int32_t mixed, pad;                 // 1: some entry's value is not the first one's
     unsigned long long rows[kTileMaxS + 1];   // sum over tiles of the rows within k rings
 };
 
@@ -35,6 +36,7 @@ __global__ void k_tile_rows(int64_t n, int32_t n_tiles, int32_t S, int32_t *__re
     if (t == 0) {
         info->rings = S;
         info->n_tiles = n_tiles;
+        info->mixed = 0;
     }
 }
 
@@ -122,6 +124,11 @@ struct TilePlanArgs {
     int32_t *rings;          // PROBE: complete rings and cut of each tile
     int32_t log2_slice, S, W, cap;
 };
+
+template <class VT> __device__ __forceinline__ bool same_bits(VT x, VT y) {
+    if constexpr (sizeof(VT) == 4) return __float_as_int(x) == __float_as_int(y);
+    else return __double_as_longlong(x) == __double_as_longlong(y);
+}
 
 // Lists of one tile: breadth-first over the bonds, ring by ring.  Rows outside
 // the tile go through an LDS hash table (row -> local index) and take the next
@@ -271,6 +278,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(TilePlanArgs a) {
         for (int k = 0; k <= done; ++k) atomicAdd(&a.info->rows[k], (unsigned long long)cnt[k]);
     }
     if (done == 0) return;
+    if (tid == 0) s_over = 0;
+    __syncthreads();
     const int64_t mb = (int64_t)t * a.cap;
     for (int i = tid; i < total; i += kPlanThreads) a.ext[mb + i] = list[i];
     // matrix rows of every ring but the last, in local form
@@ -317,7 +326,12 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(TilePlanArgs a) {
             else if (q & 1) a.lcol2[mb * NP + (int64_t)(q / 2) * a.cap + j] = lc[q - 1] | (lc[q] << 16);
         }
         if (ons) tons[mb + j] = ons[g];
+#pragma unroll
+        for (int q = 0; q < kTileMaxW; ++q)
+            if (q < a.W && q < w && cc[q] != g && !same_bits(v[q], val[0])) s_over = 1;
     }
+    __syncthreads();
+    if (tid == 0 && s_over) a.info->mixed = 1;
 }
 
 // Elements a block turns from [row][vector] to [vector][row] or back at a time: they
@@ -618,6 +632,7 @@ tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *wo
     TBK_HIP(hipMemcpyAsync(&hi, info, sizeof hi, hipMemcpyDeviceToHost, s));
     TBK_HIP(hipStreamSynchronize(s));
     run.n_tiles = hi.n_tiles;
+    run.uniform = hi.mixed == 0;
     if (hi.rings >= 1 && hi.rows[hi.rings] == hi.rows[0]) {
         run.closed = true;
         run.s = INT32_MAX;
@@ -638,6 +653,7 @@ TileArgs<VT> tile_args(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, 
     a.lcol2 = reinterpret_cast<const uint32_t *>(work + tp.off_lcol2);
     a.lcol1 = reinterpret_cast<const uint16_t *>(work + tp.off_lcol1);
     a.val = reinterpret_cast<const VT *>(work + tp.off_val);
+    a.hop = run.uniform ? static_cast<const VT *>(h->val) : nullptr;
     a.ons = h->has_onsite ? reinterpret_cast<const VT *>(work + tp.off_ons) : nullptr;
     a.rows = h->n_rows;
     a.n_work = run.n_tiles * R;

@@ -35,6 +35,7 @@ template <class VT> struct TileArgs {
     const uint32_t *lcol2;   // [n_tiles][W / 2][cap] pairs of LDS byte offsets
     const uint16_t *lcol1;   // [n_tiles][cap] the odd column (W odd)
     const VT *val;           // [n_tiles][W][cap]
+    const VT *hop;           // the value of every entry (val is not read then), or NULL
     const VT *ons;           // [n_tiles][cap] onsite energies, or NULL
     const int32_t *tile_seg; // structure of each tile, or NULL (one structure)
     const VT *seg_c1f, *seg_c1, *seg_shift;   // per structure (tile_seg != NULL)
@@ -93,7 +94,9 @@ template <class VT> __device__ __forceinline__ VT rounded_product(VT x, VT y) {
 constexpr int tile_cap(int NT, int K) { return NT * K - 128; }
 constexpr int kTileFlush = 8;      // steps between two writes of the moment sums
 
-template <class VT, int NT, int K, int W, bool DIAG, int FORM>
+// UNI: every entry has one value (a.hop), so rows hold columns only, and padding
+// points at a zero behind the rows.
+template <class VT, int NT, int K, int W, bool DIAG, int FORM, bool UNI>
 __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
     typedef std::conditional_t<sizeof(VT) == 4, f2v, d2v> C2;
     constexpr int CAP = tile_cap(NT, K);
@@ -101,7 +104,8 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
     constexpr int NA = DBL ? 2 : 1;
     constexpr int NW = NT / 64;
     constexpr int NP = W / 2;
-    __shared__ __align__(16) C2 buf[2 * CAP];
+    constexpr int ALT = UNI ? CAP + 1 : CAP;        // first element of the second buffer
+    __shared__ __align__(16) C2 buf[2 * ALT];
     __shared__ double red[2 * kTileFlush][NW][NA];
     const int tid = threadIdx.x;
     const int64_t l = logical_block(2);
@@ -129,7 +133,9 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
         shift = a.seg_shift[sg];
     }
 
-    VT h[K][W], dg[DIAG ? K : 1];
+    VT h[UNI ? 1 : K][W], dg[DIAG ? K : 1];
+    const VT hop = UNI ? *a.hop : (VT)0;
+    if (UNI && tid < 2) buf[CAP + tid * ALT].x = buf[CAP + tid * ALT].y = 0;
     uint32_t lc[K][NP + 1];
     C2 rr[DBL ? 1 : K];
     {
@@ -146,8 +152,10 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int j = min(k * NT + tid, n_mat - 1);
+            if constexpr (!UNI) {
 #pragma unroll
-            for (int w = 0; w < W; ++w) h[k][w] = a.val[mb * W + (int64_t)w * a.cap + j];
+                for (int w = 0; w < W; ++w) h[k][w] = a.val[mb * W + (int64_t)w * a.cap + j];
+            }
 #pragma unroll
             for (int p = 0; p < NP; ++p) lc[k][p] = a.lcol2[mb * NP + (int64_t)p * a.cap + j];
             if constexpr (W & 1) lc[k][NP] = a.lcol1[mb + j];
@@ -167,6 +175,19 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
 #pragma unroll
             for (int k = 0; k < K; ++k) dg[k] -= shift;
         }
+        if constexpr (UNI) {        // a column of the row itself is padding
+            constexpr uint32_t zero = CAP * sizeof(C2);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const uint32_t own = (uint32_t)(min(k * NT + tid, n_mat - 1) * (int)sizeof(C2));
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const uint32_t lo = lc[k][p] & 0xffffu, hi = lc[k][p] >> 16;
+                    lc[k][p] = (lo == own ? zero : lo) | (hi == own ? zero : hi) << 16;
+                }
+                if (W & 1) lc[k][NP] = lc[k][NP] == own ? zero : lc[k][NP];
+            }
+        }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int j = k * NT + tid;
@@ -178,15 +199,15 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
                 }
             }
             if (j < n_all) buf[j] = xc[k];
-            if (j < n_mat) buf[CAP + j] = xp[k];
+            if (j < n_mat) buf[ALT + j] = xp[k];
         }
     }
     __syncthreads();
 
     // one step: T of buffer SRC -> the other buffer (over T_{n-1}, in place)
     auto step = [&](auto par, int m) {
-        constexpr int SRC = decltype(par)::value ? CAP : 0;
-        constexpr int DST = decltype(par)::value ? 0 : CAP;
+        constexpr int SRC = decltype(par)::value ? ALT : 0;
+        constexpr int DST = decltype(par)::value ? 0 : ALT;
         const int lim = a.closed ? nr : __builtin_amdgcn_readlane(rings, s - 1 - m);
         const VT cc = (m == 0 && a.first) ? c1f : c1;
         const double cr = EVO ? a.cr[m] : 0.0, ci = EVO ? a.ci[m] : 0.0;
@@ -215,8 +236,9 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
                 }
 #pragma unroll
                 for (int w = 0; w < W; ++w) {
-                    yr += h[k][w] * x[w].x;
-                    yi += h[k][w] * x[w].y;
+                    const VT hw = UNI ? hop : h[UNI ? 0 : k][w];
+                    yr += hw * x[w].x;
+                    yi += hw * x[w].y;
                 }
                 if constexpr (DIAG && !EVO) {
                     yr += dg[k] * own.x;
@@ -288,7 +310,7 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
         }
     }
     if (a.out_cur) {
-        const int cur = (s & 1) ? CAP : 0, old = CAP - cur;
+        const int cur = (s & 1) ? ALT : 0, old = ALT - cur;
         C2 *oc = reinterpret_cast<C2 *>(a.out_cur) + plane + row0;
         C2 *op = reinterpret_cast<C2 *>(a.out_prev) + plane + row0;
 #pragma unroll

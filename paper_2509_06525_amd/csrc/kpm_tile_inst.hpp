@@ -10,7 +10,17 @@ namespace {
 template <class VT, int W, int SHAPE, bool DIAG, int FORM>
 void launch(unsigned grid, hipStream_t s, const TileArgs<VT> &a) {
     constexpr int NT = tile_threads(SHAPE), K = tile_slots(SHAPE, W, sizeof(VT) == 8);
-    k_tile_steps<VT, NT, K, W, DIAG, FORM><<<grid, NT, 0, s>>>(a);
+    // Every entry one value: 12 of the 74 bytes a row takes per pass of one vector, and a
+    // third of its registers (100 M rows, one vector, the call: 119 ms, 106 so).  For large
+    // pristine sheets without onsite energies alone; in the doubling form the zero behind
+    // the rows is 16 bytes too many for two workgroups in LDS.
+    if constexpr (SHAPE == kTileLarge && W == 3 && !DIAG && FORM != kTileDoubling) {
+        if (a.hop) {
+            k_tile_steps<VT, NT, K, W, DIAG, FORM, true><<<grid, NT, 0, s>>>(a);
+            return;
+        }
+    }
+    k_tile_steps<VT, NT, K, W, DIAG, FORM, false><<<grid, NT, 0, s>>>(a);
 }
 
 template <class VT, int W, int SHAPE, int FORM>

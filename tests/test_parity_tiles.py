@@ -78,6 +78,18 @@ def test_tiles_equal_the_sweep_for_every_width(sigma, fmt, prec, R, stripes):
         _check(H, R, M, prec)
 
 
+@pytest.mark.parametrize("fmt,prec,nx,ny,R", [("sell_f32", "c32", 150, 160, 8), ("sell_f32", "c32", 422, 420, 1),
+                                              ("sell_f64", "f64", 70, 71, 2)])
+@pytest.mark.parametrize("edit", [None, 0, -2])
+def test_rows_of_one_value(fmt, prec, nx, ny, R, edit):
+    """A pristine sheet's entries have one value, which is then not read per row; one entry
+    edited in place (the first, or one near the last row) has its own again."""
+    H = G.build(synth.graphene_sheet(nx, ny, 0.0, 0), fmt=fmt, slice=16)
+    if edit is not None:
+        H.tensors["val"][3 * H.n_rows + edit if edit < 0 else edit] *= 0.75
+    _check(H, R, 40, prec)
+
+
 @pytest.mark.parametrize("fmt,prec,R,M", [("sell_f32", "c32", 1, 64), ("sell_f32", "c32", 3, 65), ("sell_f64", "f64", 2, 90)])
 @pytest.mark.parametrize("nx,ny", [(20, 30), (120, 130)])
 def test_doubling_on_tiles(fmt, prec, R, M, nx, ny):
