@@ -10,7 +10,12 @@ atom*moments/s.  `roofline` rates the recurrence kernel: algorithmic bytes per
 launch (Hamiltonian values, columns and slice offsets once; per vector row one
 gather of T_n, one read of T_{n-1} and of r, one write of T_{n+1}; onsite when
 used) over its average launch time measured with HIP events on the library's
-stream, against the 8 TB/s HBM3E peak.  `cpu_baseline` times the serial FP64
+stream, against the 8 TB/s HBM3E peak.  Rows of up to six entries take several
+steps per launch from tiles held in LDS (k_tile_steps): there a "launch" is one
+step, its bytes are those of a sweep per step, and their rate, `effective_gbs`,
+may exceed the peak; `traffic` is the measured HBM bytes per step, and
+`achieved` and `frac` the rate they move at (null without a matching counter
+profile).  `cpu_baseline` times the serial FP64
 oracle (one core) on a bounded sample of the same workload.  `variants` reports,
 each under its own label, the same moments computed with the doubling
 identities and, when all stored hoppings are equal, without reading them.
@@ -96,6 +101,24 @@ def kernel_source_hash(files=KERNEL_SOURCES):
         with open(os.path.join(ROOT, "paper_2509_06525_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
+
+
+TILE_KERNEL_SOURCES = ("kpm_tile.hip", "kpm_tile.hpp", "kpm_tile_inst.hpp", "kpm.hpp", "kpm_dev.hpp")
+
+
+def on_tiles(H, cfg):
+    """Several steps per launch (k_tile_steps): one-orbital rows of up to six entries."""
+    return H.st.n_orb == 1 and 1 <= H.st.max_degree <= 6 and not (cfg is not None and cfg.persistent)
+
+
+def tile_roofline(rl, traffic=None, step_s=None):
+    """The roofline record of a recurrence on tiles, in place: `achieved` and `frac` from the
+    measured HBM bytes of a step (None without a matching profile); the rate by the bytes of
+    a sweep per step, which may exceed the peak, is `effective_gbs`."""
+    rl["effective_gbs"] = rl["achieved"]
+    rl["achieved"] = None if traffic is None else traffic / step_s / 1e9
+    rl["frac"] = None if traffic is None else rl["achieved"] / HBM_PEAK_GBS
+    return rl
 
 
 def profiled_traffic(workload, kernel, slice_, launch, prefix="k_cheb_step", files=KERNEL_SOURCES):
@@ -350,10 +373,13 @@ def bench_snapshots(args, w):
                      "traffic_source": f"profiles/k_cheb_step_seg_{args.workload}.md (stored rocprofv3 "
                                        "FETCH_SIZE, WRITE_SIZE runs, copy-calibrated; null when the kernel or "
                                        "launch shape differs)",
-                     "kernel": "k_cheb_persistent" if cfg.persistent else "k_cheb_step_seg",
+                     "kernel": "k_cheb_persistent" if cfg.persistent else (
+                         "k_tile_steps" if on_tiles(H, cfg) else "k_cheb_step_seg"),
                      "bytes_per_launch": launch_bytes, "launch_us": launch_s * 1e6,
                      "launches_timed": step_launches, "launch_us_kpm_window": kmed * 1e3 / (M - 1)},
     }
+    if on_tiles(H, cfg):
+        tile_roofline(out["roofline"])
     out["roofline"].update(stream_probe(dev))
     print(json.dumps(out), flush=True)
 
@@ -431,15 +457,18 @@ def kpm_variant(args, label, fields, H, a, b, r, M, R, Rp, elem, diag, precision
     achieved = launch_bytes / launch_s / 1e9
     N = H.st.n_rows
     log(f"{label}: kpm {med:.1f} ms ({launches} launches)")
-    return {"kpm_ms_median": med, "kpm_atom_moments_per_s": N * M * R / (med * 1e-3), "launches": launches,
-            "slice": H.st.slice, "launch": cfg.as_dict(),
-            "dos_relL2_vs_direct": float(np.linalg.norm(rho - rho_direct) / np.linalg.norm(rho_direct)),
-            "max_abs_dmu_over_N_vs_direct": float(np.abs(mu.cpu().numpy() - mu_direct).max() / N),
-            "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                         "frac": achieved / HBM_PEAK_GBS,
-                         "traffic": profiled_traffic(args.workload, label, H.st.slice, cfg.as_dict()),
-                         "kernel": f"k_cheb_step ({label})",
-                         "bytes_per_launch": launch_bytes, "launch_us": launch_s * 1e6}}
+    out = {"kpm_ms_median": med, "kpm_atom_moments_per_s": N * M * R / (med * 1e-3), "launches": launches,
+           "slice": H.st.slice, "launch": cfg.as_dict(),
+           "dos_relL2_vs_direct": float(np.linalg.norm(rho - rho_direct) / np.linalg.norm(rho_direct)),
+           "max_abs_dmu_over_N_vs_direct": float(np.abs(mu.cpu().numpy() - mu_direct).max() / N),
+           "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                        "frac": achieved / HBM_PEAK_GBS,
+                        "traffic": profiled_traffic(args.workload, label, H.st.slice, cfg.as_dict()),
+                        "kernel": f"{'k_tile_steps' if on_tiles(H, cfg) else 'k_cheb_step'} ({label})",
+                        "bytes_per_launch": launch_bytes, "launch_us": launch_s * 1e6}}
+    if on_tiles(H, cfg):
+        tile_roofline(out["roofline"])
+    return out
 
 
 def block_shape_search(H, a, b, r, geom, stream):
@@ -823,10 +852,12 @@ def bench_vac(args, w):
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
                      "kernel": "whole VAC step (k_cheb_step_atom pair form, k_evolve_term_atom, "
                                "k_apply_velocity_blk)" if sk else
-                               "whole VAC step (k_cheb_step pair form, k_evolve_term, k_apply_velocity)",
+                               "whole VAC step (k_tile_steps pair and propagator forms, k_velocity_planes)",
                      "bytes_per_step": total},
         "sigma_max": float(sig[-1].abs().max()),
     }
+    if not sk:
+        tile_roofline(out["roofline"])
     if F > 1:
         # carriers per cm^2 (spin 2, sheet area) and the mobility at a few concentrations
         area = float(s.box[0] * s.box[1])
@@ -958,6 +989,10 @@ def main():
     kpm_med = float(np.median(kpm_ms))
     launch_s = step_ms * 1e-3 / step_launches
     achieved = launch_bytes / launch_s / 1e9
+    tiles = on_tiles(Hs, launch_cfg)
+    kernel = "k_tile_steps" if tiles else "k_cheb_step"
+    traffic = profiled_traffic(args.workload, "direct", slice_, launch_cfg.as_dict(), kernel,
+                               TILE_KERNEL_SOURCES if tiles else KERNEL_SOURCES)
     mu_c = mu.cpu().numpy().copy()
     rho_c = rho.cpu().numpy()
 
@@ -976,14 +1011,16 @@ def main():
         "kpm_atom_moments_per_s": N * M * R / (kpm_med * 1e-3),
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": profiled_traffic(args.workload, "direct", slice_, launch_cfg.as_dict()),
-                     "traffic_source": f"profiles/k_cheb_step_{args.workload}.md (stored rocprofv3 FETCH_SIZE, "
+                     "traffic": traffic,
+                     "traffic_source": f"profiles/{kernel}_{args.workload}.md (stored rocprofv3 FETCH_SIZE, "
                                        "WRITE_SIZE runs, copy-calibrated; null when the kernel or launch "
                                        "shape differs)",
-                     "kernel": "k_cheb_step", "bytes_per_launch": launch_bytes,
+                     "kernel": kernel, "bytes_per_launch": launch_bytes,
                      "launch_us": launch_s * 1e6, "launches_timed": step_launches,
                      "launch_us_kpm_window": kpm_med * 1e3 / (M - 1)},
     }
+    if tiles:
+        tile_roofline(out["roofline"], traffic, launch_s)
     out["roofline"].update(stream_probe(dev))
 
     # DOS and moments against the oracle's stored full-size moments (its vector subset,
