@@ -520,9 +520,8 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
         // what pays; 16 M row-vectors, us per step: 31.4 with 0.75 of the capacity, 29.1 with
         // 0.7, 30.1 with 0.65, 31.0 with 0.55 and ten rings (the sweep: 148).  Systems with
         // fewer tiles than CUs: smaller tiles, whose larger halo costs less than idle CUs;
-        // 30,212 rows, three vectors: 1.25 us per step with 384 rows (236 workgroups), 1.6
-        // with 1024, the sweep 4.8; 300,000 rows, two vectors: 2.46 with 0.4 of the capacity,
-        // 2.70 with 8/15.
+        // 30,212 rows, three vectors: 1.18 us per step with 354 rows (256 workgroups), the
+        // sweep 4.8; 300,000 rows, two vectors: 0.4 of the capacity was 9% faster than 8/15.
         if (!f64 && work < 700000) {
             shape(kTileSmall);
             tp.tile_rows = std::min<int64_t>(tp.cap * (W <= 4 ? 6 : 8) / 15, std::max<int64_t>(256, work / 256));
@@ -532,6 +531,8 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
             else tp.tile_rows = std::min<int64_t>(tp.cap * (W <= 4 ? 7 : 6) / 10, std::max<int64_t>(tp.cap * 7 / 25, work / 512));
         }
         tp.S = (f64 || tp.shape == kTileSmall) && tp.tile_rows > tp.cap * 2 / 5 ? 6 : 8;
+        // two rings more on small tiles: 10 us of probing and lists, 0.06 us a step
+        if (tp.shape == kTileSmall && tp.S == 8 && pl.Mr > 200) tp.S = 10;
         tp.n_first = ceil_div(n, tp.tile_rows) + (n_seg > 1 ? n_seg : 0);   // a partial tile per structure
         tp.n_tiles = tp.n_first + tp.n_first / 8 + 8 + (n_seg > 1 ? 2 * n_seg : 0);      // room for tiles cut in two
     }

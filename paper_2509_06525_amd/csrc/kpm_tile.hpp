@@ -337,13 +337,15 @@ void launch_tile_steps(const TilePlan &tp, bool diag, int form, unsigned grid, h
 // with onsite energies: 26.9 us a step with ten rows, 18.5 with nine).
 //   large, large_diag: two workgroups of 512 per CU share its LDS (with onsite
 //     energies a row takes one word more);
-//   small: workgroups of 256, for complex-float systems of few tiles;
+//   small: half the rows, for complex-float systems of few tiles, where a CU has one
+//     or two workgroups and the steps wait for LDS (30,212 rows, three vectors: 1.34 us a
+//     step with 256 threads of eight rows, 1.18 so; 300,000 rows, two: 2.51 and 2.12);
 //   whole: a workgroup of 1024 takes a CU, for a matrix that is one tile.
 enum TileShape { kTileLarge = 0, kTileLargeDiag = 1, kTileSmall = 2, kTileWhole = 3 };
-constexpr int tile_threads(int shape) { return shape == kTileSmall ? 256 : (shape == kTileWhole ? 1024 : 512); }
+constexpr int tile_threads(int shape) { return shape == kTileWhole ? 1024 : 512; }
 constexpr int tile_slots(int shape, int W, bool f64) {
     const int i = W == 3 ? 0 : (W == 4 ? 1 : 2);
-    const int c32[4][3] = {{10, 8, 5}, {9, 7, 5}, {8, 7, 5}, {5, 5, 3}};
+    const int c32[4][3] = {{10, 8, 5}, {9, 7, 5}, {5, 4, 3}, {5, 5, 3}};
     const int c64[4][3] = {{5, 4, 3}, {5, 4, 3}, {0, 0, 0}, {4, 4, 3}};
     return f64 ? c64[shape][i] : c32[shape][i];
 }
