@@ -474,7 +474,7 @@ __device__ __forceinline__ void grad_tiles(const WaveWeights &w, const GradTile 
         const float diff = g[u].ok ? a[u].y - g[u].target : 0.f;
         if (q == 0) s.loss += (double)wb * (double)diff * (double)diff;
         const float dy = 2.f * wb * diff * inv_b;
-        if (q == 0) s.gb3 += dy;
+        if (q == 0) s.gb3 = add_rounded(s.gb3, dy);
         dyb[u] = rbf(dy);
         // output and second layer deltas
 #pragma unroll
