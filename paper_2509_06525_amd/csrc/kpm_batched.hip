@@ -398,7 +398,7 @@ tbk_status make_seg_plan(const tbk_ham *h, int32_t R, int32_t M, int32_t precisi
     sp.off_shift = sp.off_c1 + a256(ve * sp.n_seg);
     sp.off_flag = sp.off_shift + a256(ve * sp.n_seg);
     sp.total = sp.off_flag + 256;
-    tile_layout(h, sp.base, sp.total, R, sp.n_seg);
+    tile_layout(h, sp.base, sp.total, R, sp.n_seg, kPlanesStack);
     if (sp.base.tile.on) {
         // tiles of the tiled form: a structure that fits is one tile, others are cut evenly
         const TilePlan &tp = sp.base.tile;
@@ -628,6 +628,9 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
     int32_t *flag = reinterpret_cast<int32_t *>(w + sp.off_flag);
     double *part = reinterpret_cast<double *>(w + tp.off_part);
     const bool table = ns > 1;
+    VT *plane[kPlanesRun] = {};
+    tbk_status st = tile_planes<VT>(tp, w, kPlanesStack, plane);
+    if (st != TBK_OK) return st;
     if (table) {
         TBK_CHECK(nf <= tp.n_first, TBK_ERR_DEVICE, "tile table exceeds its workspace");
         TBK_HIP(hipMemcpyAsync(w + tp.off_first, sp.first.data(), sizeof(int32_t) * (nf + 1), hipMemcpyHostToDevice,
@@ -635,7 +638,7 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
         TBK_HIP(hipMemcpyAsync(w + tp.off_fseg, sp.fseg.data(), sizeof(int32_t) * nf, hipMemcpyHostToDevice, s));
     }
     TileRun run;
-    tbk_status st = tile_build<VT>(h, pl, table ? nf : 0, w, s, run);
+    st = tile_build<VT>(h, pl, table ? nf : 0, w, s, run);
     if (st != TBK_OK) return st;
     if (run.s == 0) return TBK_OK;
     std::vector<VT> h1f(ns), h1(ns), hs(ns);
@@ -664,8 +667,7 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
         TBK_HIP(hipMemcpyAsync(toff, range, sizeof range, hipMemcpyHostToDevice, s));
         TBK_HIP(hipStreamSynchronize(s));      // `range` lives on this stack
     }
-    auto plane = [&](int k) { return reinterpret_cast<VT *>(w + tp.off_planes + k * tp.plane_bytes); };
-    VT *rp = plane(4);
+    VT *rp = plane[4];
     tile_start_planes<VT>(h, pl, run, r, R, w, rp, part, s);
     TBK_HIP(hipGetLastError());
     ta.r = rp;
@@ -695,8 +697,8 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
         ta.cur = cur;
         ta.prev = prev;
         const bool keep = q + 1 < groups;
-        ta.out_cur = keep ? plane(2 * dst) : nullptr;
-        ta.out_prev = keep ? plane(2 * dst + 1) : nullptr;
+        ta.out_cur = keep ? plane[2 * dst] : nullptr;
+        ta.out_prev = keep ? plane[2 * dst + 1] : nullptr;
         ta.partial = part + (int64_t)(at + 1 - batch0) * ta.pstride;
         launch_tile_group<VT>(pl, diag, kTileDirect, grid, s, ta);
         cur = ta.out_cur;

@@ -498,9 +498,11 @@ void launch_steps(const TilePlan &tp, bool diag, int form, unsigned grid, hipStr
 }
 
 // Layout for rows of up to W entries from byte `base` on.
-void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int W, TilePlan &tp) {
+void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes, int W,
+                  TilePlan &tp) {
     tp = TilePlan{};
     tp.W = W;
+    tp.planes = planes;
     const int64_t n = h->n_rows, work = n * R;
     const bool f64 = pl.elem == sizeof(double);
     auto shape = [&](int sh) {
@@ -558,21 +560,21 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
     tp.off_part = take((size_t)tp.reduce_every * per_step);
     tp.off_l1 = take((size_t)pl.Mr * pl.Rv * chunks * sizeof(double));
     tp.plane_bytes = align256((size_t)n * R * 2 * pl.elem);
-    tp.off_planes = take((pl.Rp == 1 && n_seg == 1 ? 2 : 6) * tp.plane_bytes);    // T pairs, r, start
+    tp.off_planes = take(planes * tp.plane_bytes);
     tp.total = o;
 }
 
 }  // namespace
 
-void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg) {
+void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes) {
     pl.tile = TilePlan{};
     pl.tile.total = base;
     if (pl.block || h->max_degree < 1 || h->max_degree > kTileMaxW || pl.cfg.persistent) return;
     TilePlan other;
-    layout_width(h, pl, base, R, n_seg, h->max_degree <= 3 ? 3 : (h->max_degree <= 4 ? 4 : 6), pl.tile);
+    layout_width(h, pl, base, R, n_seg, planes, h->max_degree <= 3 ? 3 : (h->max_degree <= 4 ? 4 : 6), pl.tile);
     if (pl.tile.W <= 4) {
         // one size for degrees up to 4, so that a workspace serves frames of either
-        layout_width(h, pl, base, R, n_seg, pl.tile.W == 3 ? 4 : 3, other);
+        layout_width(h, pl, base, R, n_seg, planes, pl.tile.W == 3 ? 4 : 3, other);
         pl.tile.total = std::max(pl.tile.total, other.total);
     }
     // runs that the static workspace takes get the same form with it as with a caller's
@@ -683,11 +685,15 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
     const bool direct = Rp == 1;                   // the row form is the plane
     VT *r_int = reinterpret_cast<VT *>(work + pl.off_r);
     VT *T[2] = {reinterpret_cast<VT *>(work + pl.off_a), reinterpret_cast<VT *>(work + pl.off_b)};
-    auto plane = [&](int k) { return reinterpret_cast<VT *>(work + tp.off_planes + k * tp.plane_bytes); };
+    VT *plane[kPlanesRun] = {};
+    const tbk_status st = tile_planes<VT>(tp, work, direct ? kPlanesDirect : (planes ? kPlanesVac
+                                                                            : (pair ? kPlanesRun : kPlanesRun - 1)),
+                                          plane);
+    if (st != TBK_OK) return st;
     // pairs of vectors (even n, odd n); with one vector the first pair is the state's own
-    VT *P[2][2] = {{direct ? T[0] : plane(0), direct ? T[1] : plane(1)},
-                   {direct ? plane(0) : plane(2), direct ? plane(1) : plane(3)}};
-    VT *rp = direct ? r_int : plane(4), *sp = rp;
+    VT *P[2][2] = {{direct ? T[0] : plane[0], direct ? T[1] : plane[1]},
+                   {direct ? plane[0] : plane[2], direct ? plane[1] : plane[3]}};
+    VT *rp = direct ? r_int : plane[4], *sp = rp;
     double *part = reinterpret_cast<double *>(work + tp.off_part);
     double *l1 = reinterpret_cast<double *>(work + tp.off_l1);
     const int Rv = pl.Rv, Rout = dbl ? Rv : R;
@@ -703,7 +709,7 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
             sp = const_cast<VT *>(start);
             k_tile_overlap<VT><<<dim3(gt, R), kThreads, 0, s>>>(start, left, row0, n, Rp, part);
         } else {
-            sp = plane(5);
+            sp = plane[5];
             if (one) k_tile_prepare<VT, 1024, 1, false><<<gt, 1024, 0, s>>>(start, left, nullptr, row0, n, R, Rp, 0, 0,
                                                                            nullptr, sp, rp, part);
             else k_tile_prepare<VT, kThreads, 1, false><<<gt, kThreads, 0, s>>>(start, left, nullptr, row0, n, R, Rp, 0,
@@ -812,7 +818,9 @@ tbk_status propagate_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &r
                            int32_t n_cheb, const double *cre, const double *cim, double pr, double pi, char *work,
                            hipStream_t s, const VT *phi, VT *phi_out) {
     const TilePlan &tp = pl.tile;
-    auto plane = [&](int k) { return reinterpret_cast<VT *>(work + tp.off_planes + k * tp.plane_bytes); };
+    VT *plane[kPlanesRun] = {};
+    const tbk_status st = tile_planes<VT>(tp, work, kPlanesStack, plane);
+    if (st != TBK_OK) return st;
     TileArgs<VT> ta = tile_args<VT>(h, pl, run, work, R);
     ta.c1f = (VT)(1.0 / a);
     ta.c1 = (VT)(2.0 / a);
@@ -834,10 +842,10 @@ tbk_status propagate_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &r
         ta.s = len;
         ta.cur = cur;
         ta.prev = prev;
-        ta.out_cur = last ? nullptr : plane(2 * dst);
-        ta.out_prev = last ? nullptr : plane(2 * dst + 1);
-        ta.acc_in = plane(4);
-        ta.acc_out = last ? phi_out : plane(4);
+        ta.out_cur = last ? nullptr : plane[2 * dst];
+        ta.out_prev = last ? nullptr : plane[2 * dst + 1];
+        ta.acc_in = plane[4];
+        ta.acc_out = last ? phi_out : plane[4];
         for (int m = 0; m < len; ++m) {
             ta.cr[m] = cre[at + 1 + m];
             ta.ci[m] = cim[at + 1 + m];

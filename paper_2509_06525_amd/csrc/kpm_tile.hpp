@@ -368,6 +368,14 @@ tbk_status propagate_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &r
                            int32_t n_cheb, const double *cre, const double *cim, double pr, double pi, char *work,
                            hipStream_t s, const VT *phi, VT *phi_out);
 unsigned tile_grid(const TileRun &run, int32_t R);
+// The first `need` planes of the workspace; fails where the layout reserves fewer.
+template <class VT>
+tbk_status tile_planes(const TilePlan &tp, char *work, int need, VT *(&plane)[kPlanesRun]) {
+    TBK_CHECK(need <= tp.planes && need <= kPlanesRun, TBK_ERR_DEVICE, "%d planes needed, %d in the workspace", need,
+              tp.planes);
+    for (int k = 0; k < need; ++k) plane[k] = reinterpret_cast<VT *>(work + tp.off_planes + k * tp.plane_bytes);
+    return TBK_OK;
+}
 // One launch of a group of steps.
 template <class VT>
 void launch_tile_group(const KpmPlan &pl, bool diag, int form, unsigned grid, hipStream_t s, const TileArgs<VT> &a);

@@ -378,7 +378,7 @@ tbk_status make_layout(const tbk_ham *h, int32_t R, int32_t M, int32_t precision
     if (ly.pl.tile.on && 2 * R <= 64) {
         st = make_plan(h, 2 * R, 2, precision, nullptr, ly.ev);
         if (st != TBK_OK) return st;
-        tile_layout(h, ly.ev, ly.off_vec, 2 * R, 1);
+        tile_layout(h, ly.ev, ly.off_vec, 2 * R, 1, kPlanesStack);
         ly.plane2 = a256((size_t)h->n_rows * 2 * R * 2 * elem);
         ly.planeb = a256((size_t)h->n_rows * R * ly.B * 2 * elem);
         ly.off_phi = a256(ly.ev.tile.total);
