@@ -34,7 +34,7 @@ struct TileRun {
     int s = 0;
     int n_tiles = 0;
     bool closed = false;
-    bool uniform = false;      // every entry has the first one's value
+    bool uniform = false;      // every entry has the first one's value (0 in the row's own column: padding)
 };
 
 struct KpmPlan {

@@ -22,7 +22,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct TileInfo {                       // what the host reads back
     int32_t rings;                      // rings complete in every tile
     int32_t n_tiles;                    // tiles after the split
-    int32_t mixed, pad;                 // 1: some entry's value is not the first one's
+    int32_t mixed, pad;                 // 1: some entry's value is not the first one's, or not 0 in the row's own column
     unsigned long long rows[kTileMaxS + 1];   // sum over tiles of the rows within k rings
 };
 
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(TilePlanArgs a) {
         if (ons) tons[mb + j] = ons[g];
 #pragma unroll
         for (int q = 0; q < kTileMaxW; ++q)
-            if (q < a.W && q < w && cc[q] != g && !same_bits(v[q], val[0])) s_over = 1;
+            if (q < a.W && q < w && (cc[q] != g ? !same_bits(v[q], val[0]) : v[q] != 0)) s_over = 1;
     }
     __syncthreads();
     if (tid == 0 && s_over) a.info->mixed = 1;

@@ -175,7 +175,7 @@ __global__ __launch_bounds__(NT, 4) void k_tile_steps(TileArgs<VT> a) {
 #pragma unroll
             for (int k = 0; k < K; ++k) dg[k] -= shift;
         }
-        if constexpr (UNI) {        // a column of the row itself is padding
+        if constexpr (UNI) {        // a column of the row itself is padding: its value is 0 (k_tile_plan)
             constexpr uint32_t zero = CAP * sizeof(C2);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
