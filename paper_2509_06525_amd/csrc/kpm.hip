@@ -199,9 +199,10 @@ tbk_status make_plan(const tbk_ham *h, int32_t R, int32_t M, int32_t precision, 
     return TBK_OK;
 }
 
-tbk_status build_tiles(const tbk_ham *h, const KpmPlan &pl, int32_t precision, char *w, hipStream_t s, TileRun &run) {
-    return precision == TBK_PREC_F64 ? tile_build<double>(h, pl, 0, w, s, run)
-                                     : tile_build<float>(h, pl, 0, w, s, run);
+tbk_status build_tiles(const tbk_ham *h, const KpmPlan &pl, int32_t precision, char *w, hipStream_t s, TileRun &run,
+                       bool defer) {
+    return precision == TBK_PREC_F64 ? tile_build<double>(h, pl, 0, w, s, run, defer)
+                                     : tile_build<float>(h, pl, 0, w, s, run, defer);
 }
 
 tbk_status run_plan(const tbk_ham *h, const KpmPlan &pl, double a, double b, const void *r, int32_t R,
@@ -209,17 +210,25 @@ tbk_status run_plan(const tbk_ham *h, const KpmPlan &pl, double a, double b, con
                     const void *left, const TileRun *tiles) {
     if (pl.tile.on) {
         TileRun run;
+        tbk_status st = TBK_OK;
+        bool retry = false;
         if (tiles) run = *tiles;
         else {
-            const tbk_status st = build_tiles(h, pl, precision, w, s, run);
+            // only a fresh run can start again on the sweep
+            const bool defer = !left && pl.n_start == 0 && !step_timer().on;
+            st = build_tiles(h, pl, precision, w, s, run, defer);
             if (st != TBK_OK) return st;
         }
         if (run.s > 0) {
             if (precision == TBK_PREC_F64)
-                return run_tiled<double>(h, pl, run, a, b, static_cast<const double *>(r), R, M, w, mu, s,
-                                         static_cast<const double *>(start), static_cast<const double *>(left));
-            return run_tiled<float>(h, pl, run, a, b, static_cast<const float *>(r), R, M, w, mu, s,
-                                    static_cast<const float *>(start), static_cast<const float *>(left));
+                st = run_tiled<double>(h, pl, run, a, b, static_cast<const double *>(r), R, M, w, mu, s,
+                                       static_cast<const double *>(start), static_cast<const double *>(left), false,
+                                       &retry);
+            else
+                st = run_tiled<float>(h, pl, run, a, b, static_cast<const float *>(r), R, M, w, mu, s,
+                                      static_cast<const float *>(start), static_cast<const float *>(left), false,
+                                      &retry);
+            if (!retry) return st;
         }
     }
     const double *sd = static_cast<const double *>(start), *ld_ = static_cast<const double *>(left);

@@ -34,6 +34,7 @@ struct TileRun {
     int s = 0;
     int n_tiles = 0;
     bool closed = false;
+    const int32_t *unchecked = nullptr;   // device: 0 if the lists could not be made (else the host has looked)
     bool uniform = false;      // every entry has the first one's value (0 in the row's own column: padding)
 };
 
@@ -149,8 +150,11 @@ tbk_status run_plan(const tbk_ham *h, const KpmPlan &pl, double a, double b, con
                     int32_t M, int32_t precision, char *w, double *mu, hipStream_t s,
                     const void *start = nullptr, const void *left = nullptr, const TileRun *tiles = nullptr);
 
-// Lists the tiles of h in the workspace (pl.tile.on); run.s = 0 when their halos do not fit.
-tbk_status build_tiles(const tbk_ham *h, const KpmPlan &pl, int32_t precision, char *w, hipStream_t s, TileRun &run);
+// Lists the tiles of h in the workspace (pl.tile.on); run.s = 0 when their halos do not fit or
+// rows hold more than pl.tile.W entries.  defer: a matrix that is one tile is not waited
+// for; the run that follows looks at its end (run.unchecked).
+tbk_status build_tiles(const tbk_ham *h, const KpmPlan &pl, int32_t precision, char *w, hipStream_t s, TileRun &run,
+                       bool defer = false);
 
 // One run of the recurrence for vector type VT (double: c128, float: c64), L
 // threads per row and VPT vectors per thread; instantiated in kpm_inst_*.hip.

@@ -638,7 +638,7 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
         TBK_HIP(hipMemcpyAsync(w + tp.off_fseg, sp.fseg.data(), sizeof(int32_t) * nf, hipMemcpyHostToDevice, s));
     }
     TileRun run;
-    st = tile_build<VT>(h, pl, table ? nf : 0, w, s, run);
+    st = tile_build<VT>(h, pl, table ? nf : 0, w, s, run, false);
     if (st != TBK_OK) return st;
     if (run.s == 0) return TBK_OK;
     std::vector<VT> h1f(ns), h1(ns), hs(ns);

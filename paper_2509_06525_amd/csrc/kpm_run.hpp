@@ -333,11 +333,15 @@ __global__ void k_reduce_l2(const double *__restrict__ l1, int32_t R, int32_t M,
 // flag = 1 if some |mu_n|, n0 <= n < M, exceeds mu_0 (1 + 1e-6) or is not
 // finite.  A fresh run (n0 = 0) keeps mu_0 of every vector in mu0 for the
 // runs that continue it; a continued run reads it from there.  Writes the record of
-// the run at the head of the workspace.
+// the run at the head of the workspace.  tiles: flag |= 2 if *tiles is 0 (TileRun::unchecked).
 __global__ void k_guard(const double *__restrict__ mu, int32_t R, int32_t M, int32_t n0, double *__restrict__ mu0,
-                        int32_t *__restrict__ flag, KpmState st, KpmState *__restrict__ dst) {
+                        int32_t *__restrict__ flag, KpmState st, KpmState *__restrict__ dst,
+                        const int32_t *__restrict__ tiles) {
     int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (idx == 0) *dst = st;
+    if (idx == 0) {
+        *dst = st;
+        if (tiles && *tiles == 0) atomicOr(flag, 2);
+    }
     if (idx >= (int64_t)R * (M - n0)) return;
     const int64_t v = idx / (M - n0), n = n0 + idx % (M - n0);
     const double m0 = n0 == 0 ? mu[v * M] : mu0[v];
@@ -413,10 +417,11 @@ void launch_reduce(const KpmPlan &pl, int n0, int count, int R, double *part, do
 // Last part of a run: chunk sums to moments, spectrum guard and state record
 // (not in the pair form, where |mu_n| <= mu_0 holds only for left = start).
 // Sums of vector v sit at the virtual vectors of k_doubling_combine for VPT.
+// tiles: TileRun::unchecked; *retry = true if the tiles did not hold the matrix.
 template <class VT>
 tbk_status finish_run(const tbk_ham *h, const KpmPlan &pl, double a, double b, int32_t R, int32_t M, char *work,
                       double *mu, hipStream_t s, bool pair, bool dbl, int VPT, const double *l1, int n_chunks,
-                      bool timed) {
+                      bool timed, const int32_t *tiles = nullptr, bool *retry = nullptr) {
     KpmState *state = reinterpret_cast<KpmState *>(work + pl.off_state);
     double *mu0 = reinterpret_cast<double *>(work + pl.off_state + kStateMu0);
     double *raw = reinterpret_cast<double *>(work + pl.off_raw);
@@ -442,11 +447,15 @@ tbk_status finish_run(const tbk_ham *h, const KpmPlan &pl, double a, double b, i
     rec.next_n = M;
     rec.a = a;
     rec.b = b;
-    k_guard<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(mu, R, M, n0, mu0, flag, rec, state);
+    k_guard<<<(unsigned)ceil_div(nm, 256), 256, 0, s>>>(mu, R, M, n0, mu0, flag, rec, state, tiles);
     TBK_HIP(hipGetLastError());
     int32_t hflag = 0;
     TBK_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     TBK_HIP(hipStreamSynchronize(s));
+    if (hflag & 2) {
+        *retry = true;
+        return TBK_OK;
+    }
     if (timed) TBK_HIP(step_timer().collect());
     TBK_CHECK(hflag == 0, TBK_ERR_SPECTRUM,
               "a moment exceeds mu_0: the scale a = %g, shift b = %g do not bound the spectrum", a, b);

@@ -277,10 +277,17 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(TilePlanArgs a) {
         atomicMin(&a.info->rings, done);
         for (int k = 0; k <= done; ++k) atomicAdd(&a.info->rows[k], (unsigned long long)cnt[k]);
     }
-    if (done == 0) return;
+    const int64_t mb = (int64_t)t * a.cap;
+    if (done == 0) {
+        // a run that has not been told yet (TileRun::unchecked) may read these: offsets in range
+        for (int i = tid; i < nr; i += kPlanThreads) {
+            for (int q = 0; q < a.W / 2; ++q) a.lcol2[mb * (a.W / 2) + (int64_t)q * a.cap + i] = 0;
+            if (a.W & 1) a.lcol1[mb + i] = 0;
+        }
+        return;
+    }
     if (tid == 0) s_over = 0;
     __syncthreads();
-    const int64_t mb = (int64_t)t * a.cap;
     for (int i = tid; i < total; i += kPlanThreads) a.ext[mb + i] = list[i];
     // matrix rows of every ring but the last, in local form
     const int n_mat = closed ? nr + total : lo;
@@ -586,7 +593,8 @@ void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t 
 // written) and the number of steps per launch.  run.s = 0: the halos do not fit
 // (rows without locality), the sweep per step is to be used.
 template <class VT>
-tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *work, hipStream_t s, TileRun &run) {
+tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *work, hipStream_t s, TileRun &run,
+                      bool defer) {
     const TilePlan &tp = pl.tile;
     run = TileRun{};
     int32_t *first = reinterpret_cast<int32_t *>(work + tp.off_first);
@@ -625,17 +633,18 @@ tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *wo
     pa.row0 = row0;
     k_tile_plan<VT, false><<<(unsigned)(whole ? 1 : tp.n_tiles), kPlanThreads, 0, s>>>(pa);
     TBK_HIP(hipGetLastError());
-    if (whole) {
+    if (whole && defer) {       // closed, unless a row is wider than W: looked at after the run (no wait here)
         run.n_tiles = 1;
         run.closed = true;
         run.s = INT32_MAX;
+        run.unchecked = &info->rings;
         return TBK_OK;
     }
     TileInfo hi;
     TBK_HIP(hipMemcpyAsync(&hi, info, sizeof hi, hipMemcpyDeviceToHost, s));
     TBK_HIP(hipStreamSynchronize(s));
     run.n_tiles = hi.n_tiles;
-    run.uniform = hi.mixed == 0;
+    run.uniform = !whole && hi.mixed == 0;
     if (hi.rings >= 1 && hi.rows[hi.rings] == hi.rows[0]) {
         run.closed = true;
         run.s = INT32_MAX;
@@ -676,7 +685,7 @@ unsigned tile_grid(const TileRun &run, int32_t R) {
 template <class VT>
 tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, double a, double b, const VT *r,
                      int32_t R, int32_t M, char *work, double *mu, hipStream_t s, const VT *start, const VT *left,
-                     bool planes) {
+                     bool planes, bool *retry) {
     const TilePlan &tp = pl.tile;
     const bool pair = left != nullptr, dbl = pl.cfg.doubling != 0;
     const int n_start = pl.n_start;
@@ -797,7 +806,8 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
                 TBK_HIP(hipMemcpyAsync(y[q], x[q], sizeof(VT) * 2 * (size_t)n, hipMemcpyDeviceToDevice, s));
         TBK_HIP(hipGetLastError());
     }
-    return finish_run<VT>(h, pl, a, b, R, M, work, mu, s, pair, dbl, 1, l1, n_chunks, timed);
+    return finish_run<VT>(h, pl, a, b, R, M, work, mu, s, pair, dbl, 1, l1, n_chunks, timed, run.unchecked,
+                          retry);
 }
 
 template <class VT>
@@ -861,10 +871,11 @@ tbk_status propagate_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &r
 }
 
 #define TBK_TILE_INST(VT)                                                                                              \
-    template tbk_status tile_build<VT>(const tbk_ham *, const KpmPlan &, int, char *, hipStream_t, TileRun &);        \
+    template tbk_status tile_build<VT>(const tbk_ham *, const KpmPlan &, int, char *, hipStream_t, TileRun &, bool);  \
     template TileArgs<VT> tile_args<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, char *, int32_t);           \
     template tbk_status run_tiled<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, double, double, const VT *,   \
-                                      int32_t, int32_t, char *, double *, hipStream_t, const VT *, const VT *, bool);  \
+                                      int32_t, int32_t, char *, double *, hipStream_t, const VT *, const VT *, bool,   \
+                                      bool *);                                                                        \
     template tbk_status propagate_tiled<VT>(const tbk_ham *, const KpmPlan &, const TileRun &, double, double,         \
                                             int32_t, int32_t, const double *, const double *, double, double, char *,  \
                                             hipStream_t, const VT *, VT *);                                            \

@@ -351,16 +351,18 @@ constexpr int tile_slots(int shape, int W, bool f64) {
 }
 
 // Tile lists of h and the steps per launch (run.s = 0: no locality, use the sweep).
-// n_first > 0: the caller has written that many tiles' first rows and structures.
+// n_first > 0: the caller has written that many tiles' first rows and structures.  defer: as build_tiles.
 template <class VT>
-tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *work, hipStream_t s, TileRun &run);
+tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *work, hipStream_t s, TileRun &run,
+                      bool defer);
 template <class VT>
 TileArgs<VT> tile_args(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, char *work, int32_t R);
-// planes: start and left are planes [vector][rows] (pair form).
+// planes: start and left are planes [vector][rows] (pair form).  *retry = true: run.unchecked
+// tiles turned out not to hold the matrix, the sweep has to run.
 template <class VT>
 tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, double a, double b, const VT *r,
                      int32_t R, int32_t M, char *work, double *mu, hipStream_t s, const VT *start, const VT *left,
-                     bool planes = false);
+                     bool planes = false, bool *retry = nullptr);
 // phi_out = exp(-i b dt / hbar) sum_k c[k] T_k(Ht) phi for R vectors in planes
 // (n_cheb >= 2 terms, coefficients cre + i cim, phase pr + i pi); phi_out is not phi.
 template <class VT>
