@@ -21,7 +21,8 @@ struct TilePlan {
     int shape = 0;              // launch shape (tile_threads, tile_slots)
     int NT = 0, K = 0, cap = 0; // threads, rows per thread, local rows a tile can hold
     int W = 0;                  // entries per row
-    int S = 0;                  // rings listed
+    int S = 0;                  // rings the tiles are cut for
+    int L = 0;                  // rings listed
     int64_t n_first = 0, n_tiles = 0, tile_rows = 0;   // tiles before halving, most after it, rows of one
     int reduce_every = 1;       // steps whose partial sums are kept between reductions
     int planes = 0;             // planes reserved

@@ -522,7 +522,7 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
     if (n_seg == 1 && n <= tp.cap) {
         tp.n_first = tp.n_tiles = 1;
         tp.tile_rows = n;
-        tp.S = 1;
+        tp.S = tp.L = 1;
     } else {
         // Rows per tile and rings.  Large systems: 0.7 of the capacity (0.6 in FP64 and for
         // rows of 5 and 6 entries) and up to eight (six) rings, of which k_tile_split takes
@@ -540,8 +540,10 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
             else tp.tile_rows = std::min<int64_t>(tp.cap * (W <= 4 ? 7 : 6) / 10, std::max<int64_t>(tp.cap * 7 / 25, work / 512));
         }
         tp.S = (f64 || tp.shape == kTileSmall) && tp.tile_rows > tp.cap * 2 / 5 ? 6 : 8;
-        // two rings more on small tiles: 10 us of probing and lists, 0.06 us a step
-        if (tp.shape == kTileSmall && tp.S == 8 && pl.Mr > 200) tp.S = 10;
+        // Two rings more on small tiles: 5 us of lists, 0.06 us a step; no more than a run has
+        // steps.  The cut asks for S whatever the number of moments: where tiles end decides the
+        // grouping of the moments' sums, and the parts of a run split over calls add up as one run's.
+        tp.L = std::min(tp.shape == kTileSmall && tp.S == 8 && pl.Mr > 200 ? 10 : tp.S, std::max(2, pl.Mr - 1));
         tp.n_first = ceil_div(n, tp.tile_rows) + (n_seg > 1 ? n_seg : 0);   // a partial tile per structure
         tp.n_tiles = tp.n_first + tp.n_first / 8 + 8 + (n_seg > 1 ? 2 * n_seg : 0);      // room for tiles cut in two
     }
@@ -558,7 +560,7 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
     tp.off_row0 = take(sizeof(int32_t) * (tp.n_tiles + 1));
     tp.off_tseg = take(sizeof(int32_t) * tp.n_tiles);
     tp.off_info = take(sizeof(TileInfo));
-    tp.off_cnt = take(sizeof(int32_t) * tp.n_tiles * (tp.S + 1));
+    tp.off_cnt = take(sizeof(int32_t) * tp.n_tiles * (tp.L + 1));
     tp.off_ext = take(sizeof(int32_t) * rows);
     tp.off_lcol2 = take(sizeof(uint32_t) * rows * (W / 2));
     tp.off_lcol1 = take(sizeof(uint16_t) * rows * (W % 2));
@@ -606,7 +608,7 @@ tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *wo
     const bool table = n_first > 0;               // the caller has written first and fseg
     const int nf = table ? n_first : (int)tp.n_first;
     k_tile_rows<<<(unsigned)ceil_div(nf + 1 + kTileMaxS, 256), 256, 0, s>>>(
-        h->n_rows, nf, tp.S, whole ? row0 : (table ? nullptr : first), info);
+        h->n_rows, nf, tp.L, whole ? row0 : (table ? nullptr : first), info);
     TilePlanArgs pa{};
     pa.ptr = h->ptr;
     pa.col = h->col;
@@ -621,16 +623,17 @@ tbk_status tile_build(const tbk_ham *h, const KpmPlan &pl, int n_first, char *wo
     pa.info = info;
     pa.rings = reinterpret_cast<int32_t *>(work + tp.off_rings);
     pa.log2_slice = pl.log2_slice;
-    pa.S = tp.S;
     pa.W = tp.W;
     pa.cap = tp.cap;
     if (!whole) {
         pa.row0 = first;
+        pa.S = tp.S;
         k_tile_plan<VT, true><<<(unsigned)nf, kPlanThreads, 0, s>>>(pa);
         k_tile_split<<<1, 1024, 0, s>>>(first, pa.rings, table ? fseg : nullptr, nf, (int)tp.n_tiles, tp.S,
                                         (int)h->n_rows, row0, tseg, info);
     }
     pa.row0 = row0;
+    pa.S = tp.L;
     k_tile_plan<VT, false><<<(unsigned)(whole ? 1 : tp.n_tiles), kPlanThreads, 0, s>>>(pa);
     TBK_HIP(hipGetLastError());
     if (whole && defer) {       // closed, unless a row is wider than W: looked at after the run (no wait here)
@@ -672,7 +675,7 @@ TileArgs<VT> tile_args(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, 
     a.R = R;
     a.Rv = pl.cfg.doubling ? 2 * pl.Rp : pl.Rp;
     a.pstride = (int64_t)run.n_tiles * a.Rv;
-    a.S1 = tp.S + 1;
+    a.S1 = tp.L + 1;
     a.cap = tp.cap;
     a.closed = run.closed ? 1 : 0;
     return a;

@@ -376,7 +376,7 @@ tbk_status make_layout(const tbk_ham *h, int32_t R, int32_t M, int32_t precision
     ly.bvec = a256((size_t)h->n_rows * ly.pl.Rp * 2 * elem);
     ly.off_mu = ly.off_batch + 2 * ly.bvec;
     if (ly.pl.tile.on && 2 * R <= 64) {
-        st = make_plan(h, 2 * R, 2, precision, nullptr, ly.ev);
+        st = make_plan(h, 2 * R, kTileMaxS + 2, precision, nullptr, ly.ev);      // any number of terms
         if (st != TBK_OK) return st;
         tile_layout(h, ly.ev, ly.off_vec, 2 * R, 1, kPlanesStack);
         ly.plane2 = a256((size_t)h->n_rows * 2 * R * 2 * elem);
