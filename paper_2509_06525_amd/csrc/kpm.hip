@@ -195,7 +195,7 @@ tbk_status make_plan(const tbk_ham *h, int32_t R, int32_t M, int32_t precision, 
     pl.off_raw = pl.off_l1 + align256((size_t)pl.Mr * Rout * pl.n_chunks * sizeof(double));
     pl.off_flag = pl.off_raw + align256((size_t)pl.Mr * Rout * sizeof(double));
     pl.total = pl.off_flag + 256;
-    tile_layout(h, pl, pl.total, R, 1, pl.Rp == 1 ? kPlanesDirect : kPlanesRun);
+    tile_layout(h, pl, pl.total, R, 1, pl.Rp == 1 ? kPlanesDirect : kPlanesRun, true);
     return TBK_OK;
 }
 

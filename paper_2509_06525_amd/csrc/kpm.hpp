@@ -25,7 +25,7 @@ struct TilePlan {
     int L = 0;                  // rings listed
     int64_t n_first = 0, n_tiles = 0, tile_rows = 0;   // tiles before halving, most after it, rows of one
     int reduce_every = 1;       // steps whose partial sums are kept between reductions
-    int planes = 0;             // planes reserved
+    int planes = 0, Rc = 1;     // planes reserved, vectors in one
     size_t off_first = 0, off_fseg = 0, off_rings = 0, off_row0 = 0, off_tseg = 0, off_info = 0, off_cnt = 0, off_ext = 0, off_lcol2 = 0, off_lcol1 = 0,
            off_val = 0, off_ons = 0, off_part = 0, off_l1 = 0, off_planes = 0, plane_bytes = 0, total = 0;
 };
@@ -61,16 +61,18 @@ struct KpmPlan {
     TilePlan tile;              // tiled form; its workspace follows `total`
 };
 
-// Planes ([R][rows] vectors) the users of the tiled form take from its workspace (tile_planes):
-// two pairs T_n, T_{n-1}, the start vectors r, and in the pair form the left vectors.
-constexpr int kPlanesDirect = 2;       // run_tiled with one vector: r and the first pair are the row form's
-constexpr int kPlanesVac = 4;          // run_tiled on planes of the caller
-constexpr int kPlanesStack = 5;        // run_seg_tiled, propagate_tiled
-constexpr int kPlanesRun = 6;          // run_tiled
+// Planes ([vectors][rows]) that the users of the tiled form take from its workspace (tile_planes)
+// beside the sweep's r, T_a and T_b, of two pairs T_n, T_{n-1}, the start and the left vectors.
+constexpr int kPlanesDirect = 2;       // run_tiled, one vector: a pair (the row form is a plane)
+constexpr int kPlanesRun = 5;          // run_tiled: two pairs and r (the row form holds the run's state)
+constexpr int kPlanesPair = 3;         // run_tiled, pair form: half a pair, start, left (no state is kept)
+constexpr int kPlanesStack = 2;        // run_seg_tiled: a pair (no state is kept)
+constexpr int kPlanesPropagate = 5;    // propagate_tiled: two pairs and the series' sum
+constexpr int kPlanesMax = 5;
 
 // Fills pl.tile for n_seg structures and a run that takes `planes` planes; its workspace
-// starts at byte `base`.
-void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes);
+// starts at byte `base`.  sets: the run can take its vectors in sets of pl.tile.Rc.
+void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes, bool sets = false);
 
 // Leading bytes of the recurrence workspace: the record of the last completed
 // run, which a later call with n_start > 0 continues.  The vectors r, T_a, T_b

@@ -628,7 +628,7 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
     int32_t *flag = reinterpret_cast<int32_t *>(w + sp.off_flag);
     double *part = reinterpret_cast<double *>(w + tp.off_part);
     const bool table = ns > 1;
-    VT *plane[kPlanesRun] = {};
+    VT *plane[kPlanesMax] = {};
     tbk_status st = tile_planes<VT>(tp, w, kPlanesStack, plane);
     if (st != TBK_OK) return st;
     if (table) {
@@ -667,7 +667,8 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
         TBK_HIP(hipMemcpyAsync(toff, range, sizeof range, hipMemcpyHostToDevice, s));
         TBK_HIP(hipStreamSynchronize(s));      // `range` lives on this stack
     }
-    VT *rp = plane[4];
+    VT *rp = reinterpret_cast<VT *>(w + sp.off_r);      // the sweep's vectors serve as planes
+    VT *P[2][2] = {{reinterpret_cast<VT *>(w + sp.off_a), reinterpret_cast<VT *>(w + sp.off_b)}, {plane[0], plane[1]}};
     tile_start_planes<VT>(h, pl, run, r, R, w, rp, part, s);
     TBK_HIP(hipGetLastError());
     ta.r = rp;
@@ -697,8 +698,8 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
         ta.cur = cur;
         ta.prev = prev;
         const bool keep = q + 1 < groups;
-        ta.out_cur = keep ? plane[2 * dst] : nullptr;
-        ta.out_prev = keep ? plane[2 * dst + 1] : nullptr;
+        ta.out_cur = keep ? P[dst][0] : nullptr;
+        ta.out_prev = keep ? P[dst][1] : nullptr;
         ta.partial = part + (int64_t)(at + 1 - batch0) * ta.pstride;
         launch_tile_group<VT>(pl, diag, kTileDirect, grid, s, ta);
         cur = ta.out_cur;

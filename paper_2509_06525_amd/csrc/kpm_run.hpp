@@ -288,13 +288,14 @@ __global__ void k_doubling_combine(const double *__restrict__ raw, int32_t K, in
     mu[(int64_t)v * M + m] = out;
 }
 
-// First level: l1[n0 + k][v][c] = sum of partial[k][b][v] over b in chunk c.
+// First level: l1[n0 + k][v][c] = sum of partial[k][b][v] over b in chunk c (v < R of
+// the Rl vectors in a row of l1).
 // grid = (n_chunks, K).  Thread t reads vector v = t % Rp of blocks
 // b0 + t / Rp, b0 + t / Rp + 256 / Rp, ..., so a wavefront reads whole rows of
 // partial[k][b][0..Rp) (contiguous); the per-vector sums are then folded in LDS
 // over the 256 / Rp thread groups in a fixed tree.
 __global__ __launch_bounds__(kThreads) void k_reduce_l1(const double *__restrict__ partial, int64_t G, int32_t Rp,
-                                                        int32_t R, int32_t n0, int32_t n_chunks,
+                                                        int32_t R, int32_t Rl, int32_t n0, int32_t n_chunks,
                                                         double *__restrict__ l1) {
     __shared__ double red[kThreads];
     const int c = blockIdx.x;
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(kThreads) void k_reduce_l1(const double *__restrict
         if (j < g) red[threadIdx.x] += red[threadIdx.x + g * Rp];
         __syncthreads();
     }
-    if (j == 0 && v < R) l1[((int64_t)(n0 + k) * R + v) * n_chunks + c] = red[v];
+    if (j == 0 && v < R) l1[((int64_t)(n0 + k) * Rl + v) * n_chunks + c] = red[v];
 }
 
 // Second level: mu[v][n] = sum over chunks of l1[n][v][c], in chunk order, for
@@ -411,7 +412,7 @@ void launch_step(const KpmPlan &pl, bool first, bool diag, hipStream_t s, const 
 
 void launch_reduce(const KpmPlan &pl, int n0, int count, int R, double *part, double *l1, hipStream_t s) {
     dim3 grid(pl.n_chunks, count);
-    k_reduce_l1<<<grid, kThreads, 0, s>>>(part, pl.G, pl.Rp, R, n0, pl.n_chunks, l1);
+    k_reduce_l1<<<grid, kThreads, 0, s>>>(part, pl.G, pl.Rp, R, R, n0, pl.n_chunks, l1);
 }
 
 // Last part of a run: chunk sums to moments, spectrum guard and state record
@@ -513,7 +514,7 @@ tbk_status run_moments_t(const tbk_ham *h, const KpmPlan &pl, double a, double b
     const bool diag = h->has_onsite || b != 0.0;
     auto reduce = [&](int n0, int count) {
         dim3 grid(pl.n_chunks, count);
-        k_reduce_l1<<<grid, kThreads, 0, s>>>(part, pl.G, Rv, Rout, n0, pl.n_chunks, l1);
+        k_reduce_l1<<<grid, kThreads, 0, s>>>(part, pl.G, Rv, Rout, Rout, n0, pl.n_chunks, l1);
     };
 
     StepTimer &timer = step_timer();

@@ -15,7 +15,8 @@ constexpr int kHaloMax = 2048;         // halo rows a tile can list
 constexpr int kLocalBond = 256;        // rows between the ends of a bond inside a strip, at most (about two lines of cells)
 constexpr int kHashSize = 4096;        // open addressing, at most kHaloMax + kPlanThreads keys
 constexpr int kTileMaxW = 6;           // entries per row
-constexpr size_t kTilePartialBudget = 64ull << 20;
+constexpr size_t kTilePartialBudget = 64ull << 20;       // a quarter of it for runs that the static workspace takes
+constexpr size_t kPlaneBudget = 32ull << 30;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -461,13 +462,14 @@ __global__ __launch_bounds__(kThreads) void k_tile_overlap(const VT *__restrict_
     }
 }
 
-// [rows][Rp] <-> planes [vector][rows] for the R vectors of up to three sets (grid y;
-// TO: into planes; the padded columns of the row form are zero).
+// Columns v0 .. v0 + Rp - 1 of [rows][pitch] <-> planes [vector][rows] of the first R of them,
+// for up to three arrays (grid y; TO: into planes; columns past R are padding, of zeros).
 template <class VT> struct PlaneSets {
     VT *x[3], *plane[3];
 };
 template <class VT, bool TO>
-__global__ __launch_bounds__(kThreads) void k_planes(PlaneSets<VT> ps, int64_t rows, int32_t R, int32_t Rp) {
+__global__ __launch_bounds__(kThreads) void k_planes(PlaneSets<VT> ps, int64_t rows, int32_t R, int32_t Rp,
+                                                       int32_t pitch, int32_t v0) {
     typedef std::conditional_t<sizeof(VT) == 4, f2v, d2v> C2;
     __shared__ C2 turn[kTurn + kThreads];
     const int set = blockIdx.y, rb = kTurn / Rp;
@@ -475,6 +477,7 @@ __global__ __launch_bounds__(kThreads) void k_planes(PlaneSets<VT> ps, int64_t r
     C2 *plane = reinterpret_cast<C2 *>(set == 0 ? ps.plane[0] : (set == 1 ? ps.plane[1] : ps.plane[2]));
     const int64_t i0 = (int64_t)blockIdx.x * rb;
     const int nr = (int)min((int64_t)rb, rows - i0);
+    x += i0 * pitch + v0;
     // thread order of the row form (e = row * Rp + vector) and of the planes (f = vector * rb + row)
 #pragma unroll
     for (int k = 0; k < kTurn / kThreads; ++k) {
@@ -483,7 +486,7 @@ __global__ __launch_bounds__(kThreads) void k_planes(PlaneSets<VT> ps, int64_t r
         if (j >= nr) continue;
         C2 y;
         y.x = y.y = 0;
-        if (v < R) y = TO ? x[i0 * Rp + f] : plane[(int64_t)v * rows + i0 + j];
+        if (v < R) y = TO ? x[j * pitch + v] : plane[(int64_t)v * rows + i0 + j];
         turn[v * (rb + 1) + j] = y;
     }
     __syncthreads();
@@ -492,7 +495,7 @@ __global__ __launch_bounds__(kThreads) void k_planes(PlaneSets<VT> ps, int64_t r
         const int f = k * kThreads + threadIdx.x;
         const int j = TO ? f % rb : f / Rp, v = TO ? f / rb : f % Rp;
         if (j >= nr) continue;
-        if (!TO) x[i0 * Rp + f] = turn[v * (rb + 1) + j];
+        if (!TO) x[j * pitch + v] = turn[v * (rb + 1) + j];
         else if (v < R) plane[(int64_t)v * rows + i0 + j] = turn[v * (rb + 1) + j];
     }
 }
@@ -505,8 +508,8 @@ void launch_steps(const TilePlan &tp, bool diag, int form, unsigned grid, hipStr
 }
 
 // Layout for rows of up to W entries from byte `base` on.
-void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes, int W,
-                  TilePlan &tp) {
+void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes, bool sets,
+                  int W, TilePlan &tp) {
     tp = TilePlan{};
     tp.W = W;
     tp.planes = planes;
@@ -548,7 +551,8 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
         tp.n_tiles = tp.n_first + tp.n_first / 8 + 8 + (n_seg > 1 ? 2 * n_seg : 0);      // room for tiles cut in two
     }
     const size_t per_step = (size_t)tp.n_tiles * pl.Rv * sizeof(double);
-    tp.reduce_every = (int)std::min<size_t>(kTilePartialBudget / per_step, (size_t)std::min(pl.Mr, 4096));
+    tp.reduce_every = (int)std::min<size_t>(kTilePartialBudget / (base > kStaticSweepBytes || n_seg > 1 ? 1 : 4) / per_step,
+                                            (size_t)std::min(pl.Mr, 4096));
     tp.reduce_every = std::max(tp.reduce_every, kTileMaxS + 1);
     const size_t rows = (size_t)tp.n_tiles * tp.cap;
     const size_t chunks = (size_t)ceil_div(tp.n_tiles, kReduceChunk);
@@ -565,25 +569,29 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
     tp.off_lcol2 = take(sizeof(uint32_t) * rows * (W / 2));
     tp.off_lcol1 = take(sizeof(uint16_t) * rows * (W % 2));
     tp.off_val = take(pl.elem * rows * W);
-    tp.off_ons = take(pl.elem * rows);
+    tp.off_ons = take(h->has_onsite ? pl.elem * rows : 0);
     tp.off_part = take((size_t)tp.reduce_every * per_step);
     tp.off_l1 = take((size_t)pl.Mr * pl.Rv * chunks * sizeof(double));
-    tp.plane_bytes = align256((size_t)n * R * 2 * pl.elem);
+    // A plane holds all vectors, unless the planes took more than 32 GB: then as many as fit
+    // (100 M rows: eight in complex float; 40 vectors: 161 + 32 GB, where planes of all took 194).
+    tp.Rc = pl.Rp;
+    while (sets && tp.Rc > 1 && (size_t)planes * n * tp.Rc * 2 * pl.elem > kPlaneBudget) tp.Rc /= 2;
+    tp.plane_bytes = align256((size_t)n * std::min(R, tp.Rc) * 2 * pl.elem);
     tp.off_planes = take(planes * tp.plane_bytes);
     tp.total = o;
 }
 
 }  // namespace
 
-void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes) {
+void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes, bool sets) {
     pl.tile = TilePlan{};
     pl.tile.total = base;
     if (pl.block || h->max_degree < 1 || h->max_degree > kTileMaxW || pl.cfg.persistent) return;
     TilePlan other;
-    layout_width(h, pl, base, R, n_seg, planes, h->max_degree <= 3 ? 3 : (h->max_degree <= 4 ? 4 : 6), pl.tile);
+    layout_width(h, pl, base, R, n_seg, planes, sets, h->max_degree <= 3 ? 3 : (h->max_degree <= 4 ? 4 : 6), pl.tile);
     if (pl.tile.W <= 4) {
         // one size for degrees up to 4, so that a workspace serves frames of either
-        layout_width(h, pl, base, R, n_seg, planes, pl.tile.W == 3 ? 4 : 3, other);
+        layout_width(h, pl, base, R, n_seg, planes, sets, pl.tile.W == 3 ? 4 : 3, other);
         pl.tile.total = std::max(pl.tile.total, other.total);
     }
     // runs that the static workspace takes get the same form with it as with a caller's
@@ -693,18 +701,20 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
     const bool pair = left != nullptr, dbl = pl.cfg.doubling != 0;
     const int n_start = pl.n_start;
     const int64_t n = h->n_rows;
-    const int Rp = pl.Rp;
+    const int Rp = pl.Rp, Rc = tp.Rc;
     const bool direct = Rp == 1;                   // the row form is the plane
+    const bool sets = Rc < Rp;                     // planes hold Rc vectors: set after set runs
     VT *r_int = reinterpret_cast<VT *>(work + pl.off_r);
     VT *T[2] = {reinterpret_cast<VT *>(work + pl.off_a), reinterpret_cast<VT *>(work + pl.off_b)};
-    VT *plane[kPlanesRun] = {};
-    const tbk_status st = tile_planes<VT>(tp, work, direct ? kPlanesDirect : (planes ? kPlanesVac
-                                                                            : (pair ? kPlanesRun : kPlanesRun - 1)),
-                                          plane);
+    VT *plane[kPlanesMax] = {};
+    const int need = pair ? (direct || planes ? 1 : kPlanesPair) : (direct ? kPlanesDirect : kPlanesRun);
+    const tbk_status st = tile_planes<VT>(tp, work, need, plane);
     if (st != TBK_OK) return st;
-    // pairs of vectors (even n, odd n); with one vector the first pair is the state's own
-    VT *P[2][2] = {{direct ? T[0] : plane[0], direct ? T[1] : plane[1]},
-                   {direct ? plane[0] : plane[2], direct ? plane[1] : plane[3]}};
+    // pairs of vectors (even n, odd n); with one vector the first pair is the state's own, and
+    // in the pair form, which keeps none, r, T_a and T_b serve as planes
+    const bool own = direct || pair;
+    VT *P[2][2] = {{own ? T[0] : plane[0], own ? T[1] : plane[1]},
+                   {pair ? r_int : (direct ? plane[0] : plane[2]), pair ? plane[0] : (direct ? plane[1] : plane[3])}};
     VT *rp = direct ? r_int : plane[4], *sp = rp;
     double *part = reinterpret_cast<double *>(work + tp.off_part);
     double *l1 = reinterpret_cast<double *>(work + tp.off_l1);
@@ -713,7 +723,7 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
     const int32_t *row0 = reinterpret_cast<const int32_t *>(work + tp.off_row0);
     const unsigned gt = (unsigned)run.n_tiles;
     const bool one = run.n_tiles == 1;
-    const unsigned ge = (unsigned)ceil_div(n * Rp, kTurn);
+    const unsigned ge = (unsigned)ceil_div(n * Rc, kTurn);
 
     if (pair) {
         if (direct || planes) {
@@ -721,7 +731,8 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
             sp = const_cast<VT *>(start);
             k_tile_overlap<VT><<<dim3(gt, R), kThreads, 0, s>>>(start, left, row0, n, Rp, part);
         } else {
-            sp = plane[5];
+            rp = plane[1];
+            sp = plane[2];
             if (one) k_tile_prepare<VT, 1024, 1, false><<<gt, 1024, 0, s>>>(start, left, nullptr, row0, n, R, Rp, 0, 0,
                                                                            nullptr, sp, rp, part);
             else k_tile_prepare<VT, kThreads, 1, false><<<gt, kThreads, 0, s>>>(start, left, nullptr, row0, n, R, Rp, 0,
@@ -729,17 +740,16 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
         }
     } else if (n_start == 0) {
         const int seeded = pl.seeded ? 1 : 0;
+        VT *to = sets ? r_int : rp;
         auto prepare = [&](auto d) {
             constexpr bool D = decltype(d)::value;
             if (one) k_tile_prepare<VT, 1024, 0, D><<<gt, 1024, 0, s>>>(r, nullptr, h->perm, row0, n, R, Rp, seeded,
-                                                                       pl.seed, r_int, rp, nullptr, part);
+                                                                       pl.seed, r_int, to, nullptr, part);
             else k_tile_prepare<VT, kThreads, 0, D><<<gt, kThreads, 0, s>>>(r, nullptr, h->perm, row0, n, R, Rp,
-                                                                            seeded, pl.seed, r_int, rp, nullptr, part);
+                                                                            seeded, pl.seed, r_int, to, nullptr, part);
         };
         if (dbl) prepare(std::true_type{});
         else prepare(std::false_type{});
-    } else if (!direct) {
-        k_planes<VT, true><<<dim3(ge, 3), kThreads, 0, s>>>({{r_int, T[0], T[1]}, {rp, P[0][0], P[0][1]}}, n, R, Rp);
     }
     TBK_HIP(hipGetLastError());
 
@@ -749,11 +759,14 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
     ta.c1 = (VT)(2.0 / a);
     ta.shift = (VT)b;
     const bool diag = h->has_onsite || b != 0.0;
-    const unsigned grid = tile_grid(run, R);
-    auto reduce = [&](int n0, int count) {
+    const int NA = dbl ? 2 : 1;
+    // l1 rows of the moments n0 .. n0 + count - 1 from the partials of the vectors v0 .. v0 + w - 1 (Rv_c sums a tile)
+    auto reduce = [&](int n0, int count, int v0, int w, int Rv_c) {
         dim3 g(n_chunks, count);
-        k_reduce_l1<<<g, kThreads, 0, s>>>(part, run.n_tiles, Rv, Rout, n0, n_chunks, l1);
+        k_reduce_l1<<<g, kThreads, 0, s>>>(part, run.n_tiles, Rv_c, w, Rout, n0, n_chunks,
+                                           l1 + (int64_t)v0 * NA * n_chunks);
     };
+    if (sets && n_start == 0) reduce(0, 1, 0, Rout, Rv);
 
     StepTimer &timer = step_timer();
     const bool timed = timer.on && !pair;
@@ -764,46 +777,65 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
     const int steps = pl.Mr - 1 - n0;
     const int most = std::min<int64_t>(run.s, run.closed ? tp.reduce_every - 1 : kTileMaxS);
     const int groups = (int)ceil_div(steps, most);
-    // a fresh run ends in pair 0; a continued one starts there
-    int dst = n_start > 0 ? 1 : (groups - 1) & 1;
-    int batch0 = n_start;          // first row index of the pending batch of partials
-    int at = n0;                   // T_at is the newest vector
-    const VT *cur = n_start > 0 ? P[0][at & 1] : sp;
-    // T_0 of a run that ended at T_1 is r (the sweep leaves no copy of it)
-    const VT *prev = n_start > 2 ? P[0][(at + 1) & 1] : (n_start == 2 ? rp : sp);
-    for (int q = 0; q < groups; ++q) {
-        const int len = steps / groups + (q < steps % groups ? 1 : 0);
-        if (at + 1 + len - batch0 > tp.reduce_every) {
-            if (open) { TBK_HIP(timer.mark(s)); open = false; }
-            reduce(batch0, at + 1 - batch0);
-            batch0 = at + 1;
+    for (int v0 = 0; v0 < (sets ? Rp : 1); v0 += Rc) {
+        const int Rs = std::max(0, std::min(R - v0, Rc));      // vectors of the set (0: only padding)
+        const int w = sets ? Rs * NA : Rout, Rv_c = sets ? Rc * NA : Rv;
+        if (Rs > 0) {
+            if (n_start > 0 && !direct)
+                k_planes<VT, true><<<dim3(ge, 3), kThreads, 0, s>>>(
+                    {{r_int, T[0], T[1]}, {rp, P[0][0], P[0][1]}}, n, Rs, Rc, Rp, v0);
+            else if (sets)
+                k_planes<VT, true><<<dim3(ge, 1), kThreads, 0, s>>>({{r_int, nullptr, nullptr}, {rp, nullptr, nullptr}},
+                                                                    n, Rs, Rc, Rp, v0);
+            TBK_HIP(hipGetLastError());
         }
-        if (timed && !open) { TBK_HIP(timer.mark(s)); open = true; }
-        if (timed) timer.launches += len;
-        ta.first = at == 0;
-        ta.s = len;
-        ta.cur = cur;
-        ta.prev = prev;
-        const int end = at + len;
-        const bool keep = q + 1 < groups || !(pair || dbl);    // the last group's vectors: only for a run to continue
-        ta.out_cur = keep ? P[dst][end & 1] : nullptr;
-        ta.out_prev = keep ? P[dst][(end + 1) & 1] : nullptr;
-        ta.partial = part + (int64_t)(at + 1 - batch0) * ta.pstride;
-        launch_steps<VT>(tp, diag, dbl ? kTileDoubling : kTileDirect, grid, s, ta);
-        cur = ta.out_cur;
-        prev = ta.out_prev;
-        at = end;
-        dst ^= 1;
-    }
-    if (open) TBK_HIP(timer.mark(s));
-    reduce(batch0, pl.Mr - batch0);
-    TBK_HIP(hipGetLastError());
-    if (!pair && !dbl) {           // the state of the run, in row order
-        VT *y[2] = {T[at & 1], T[(at + 1) & 1]};          // of T_at, T_{at-1}
+        ta.R = Rs;
+        ta.n_work = run.n_tiles * Rs;
+        ta.Rv = Rv_c;
+        ta.pstride = (int64_t)run.n_tiles * Rv_c;
+        const unsigned grid = tile_grid(run, Rs);
+        // a fresh run ends in pair 0; a continued one starts there
+        int dst = n_start > 0 ? 1 : (groups - 1) & 1;
+        int batch0 = sets && n_start == 0 ? 1 : n_start;     // first row index of the pending batch of partials
+        int at = n0;                                         // T_at is the newest vector
+        const VT *cur = n_start > 0 ? P[0][at & 1] : sp;
+        // T_0 of a run that ended at T_1 is r (the sweep leaves no copy of it)
+        const VT *prev = n_start > 2 ? P[0][(at + 1) & 1] : (n_start == 2 ? rp : sp);
+        for (int q = 0; q < groups && Rs > 0; ++q) {
+            const int len = steps / groups + (q < steps % groups ? 1 : 0);
+            if (at + 1 + len - batch0 > tp.reduce_every) {
+                if (open) { TBK_HIP(timer.mark(s)); open = false; }
+                reduce(batch0, at + 1 - batch0, v0, w, Rv_c);
+                batch0 = at + 1;
+            }
+            if (timed && !open) { TBK_HIP(timer.mark(s)); open = true; }
+            if (timed && v0 == 0) timer.launches += len;
+            ta.first = at == 0;
+            ta.s = len;
+            ta.cur = cur;
+            ta.prev = prev;
+            const int end = at + len;
+            const bool keep = q + 1 < groups || !(pair || dbl);    // the last group's vectors: only for a run to continue
+            ta.out_cur = keep ? P[dst][end & 1] : nullptr;
+            ta.out_prev = keep ? P[dst][(end + 1) & 1] : nullptr;
+            ta.partial = part + (int64_t)(at + 1 - batch0) * ta.pstride;
+            launch_steps<VT>(tp, diag, dbl ? kTileDoubling : kTileDirect, grid, s, ta);
+            cur = ta.out_cur;
+            prev = ta.out_prev;
+            at = end;
+            dst ^= 1;
+        }
+        if (open) { TBK_HIP(timer.mark(s)); open = false; }
+        if (Rs > 0) reduce(batch0, pl.Mr - batch0, v0, w, Rv_c);
+        TBK_HIP(hipGetLastError());
+        if (pair || dbl) continue;
+        // the state of the run, in row order
+        const int last = pl.Mr - 1;
+        VT *y[2] = {T[last & 1], T[(last + 1) & 1]};          // of T_last, T_{last-1}
         const VT *x[2] = {cur, prev};
         if (!direct)
             k_planes<VT, false><<<dim3(ge, 2), kThreads, 0, s>>>(
-                {{y[0], y[1], nullptr}, {const_cast<VT *>(x[0]), const_cast<VT *>(x[1]), nullptr}}, n, R, Rp);
+                {{y[0], y[1], nullptr}, {const_cast<VT *>(x[0]), const_cast<VT *>(x[1]), nullptr}}, n, Rs, Rc, Rp, v0);
         for (int q = 0; q < 2 && direct; ++q)
             if (x[q] != y[q])
                 TBK_HIP(hipMemcpyAsync(y[q], x[q], sizeof(VT) * 2 * (size_t)n, hipMemcpyDeviceToDevice, s));
@@ -831,8 +863,8 @@ tbk_status propagate_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &r
                            int32_t n_cheb, const double *cre, const double *cim, double pr, double pi, char *work,
                            hipStream_t s, const VT *phi, VT *phi_out) {
     const TilePlan &tp = pl.tile;
-    VT *plane[kPlanesRun] = {};
-    const tbk_status st = tile_planes<VT>(tp, work, kPlanesStack, plane);
+    VT *plane[kPlanesMax] = {};
+    const tbk_status st = tile_planes<VT>(tp, work, kPlanesPropagate, plane);
     if (st != TBK_OK) return st;
     TileArgs<VT> ta = tile_args<VT>(h, pl, run, work, R);
     ta.c1f = (VT)(1.0 / a);

@@ -372,8 +372,8 @@ tbk_status propagate_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &r
 unsigned tile_grid(const TileRun &run, int32_t R);
 // The first `need` planes of the workspace; fails where the layout reserves fewer.
 template <class VT>
-tbk_status tile_planes(const TilePlan &tp, char *work, int need, VT *(&plane)[kPlanesRun]) {
-    TBK_CHECK(need <= tp.planes && need <= kPlanesRun, TBK_ERR_DEVICE, "%d planes needed, %d in the workspace", need,
+tbk_status tile_planes(const TilePlan &tp, char *work, int need, VT *(&plane)[kPlanesMax]) {
+    TBK_CHECK(need <= tp.planes && need <= kPlanesMax, TBK_ERR_DEVICE, "%d planes needed, %d in the workspace", need,
               tp.planes);
     for (int k = 0; k < need; ++k) plane[k] = reinterpret_cast<VT *>(work + tp.off_planes + k * tp.plane_bytes);
     return TBK_OK;

@@ -370,6 +370,7 @@ tbk_status make_layout(const tbk_ham *h, int32_t R, int32_t M, int32_t precision
     const size_t elem = precision == TBK_PREC_C32 ? sizeof(float) : sizeof(double);
     auto a256 = [](size_t x) { return (x + 255) & ~(size_t)255; };
     ly.vec = a256((size_t)h->n_rows * pad_vectors(R) * 2 * elem);
+    if (ly.pl.tile.on) tile_layout(h, ly.pl, ly.pl.total, R * ly.B, 1, kPlanesPair);
     ly.pl.tile.on = ly.pl.tile.on && tiled;
     ly.off_vec = a256(ly.pl.tile.on ? ly.pl.tile.total : ly.pl.total);
     ly.off_batch = ly.off_vec + 9 * ly.vec;
@@ -378,7 +379,7 @@ tbk_status make_layout(const tbk_ham *h, int32_t R, int32_t M, int32_t precision
     if (ly.pl.tile.on && 2 * R <= 64) {
         st = make_plan(h, 2 * R, kTileMaxS + 2, precision, nullptr, ly.ev);      // any number of terms
         if (st != TBK_OK) return st;
-        tile_layout(h, ly.ev, ly.off_vec, 2 * R, 1, kPlanesStack);
+        tile_layout(h, ly.ev, ly.off_vec, 2 * R, 1, kPlanesPropagate);
         ly.plane2 = a256((size_t)h->n_rows * 2 * R * 2 * elem);
         ly.planeb = a256((size_t)h->n_rows * R * ly.B * 2 * elem);
         ly.off_phi = a256(ly.ev.tile.total);

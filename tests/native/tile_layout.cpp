@@ -37,7 +37,8 @@ int main() {
                                 }
                                 const TilePlan &t = pl.tile;
                                 if (!t.on) continue;
-                                const long long vec = (long long)n * R * 2 * (long long)pl.elem;
+                                const int in_plane = R < t.Rc ? R : t.Rc;
+                                const long long vec = (long long)n * in_plane * 2 * (long long)pl.elem;
                                 std::printf("%lld %d %d %d %d %d %d %zu %zu %zu %d %d %lld %d\n", (long long)n, d, R, f64,
                                             onsite, M, segs, pl.total, t.off_planes, t.total, t.planes, taken,
                                             vec, t.plane_bytes >= (size_t)vec);

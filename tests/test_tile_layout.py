@@ -25,8 +25,8 @@ def layouts(tmp_path_factory):
 
 
 def test_planes_lie_inside_the_workspace(layouts):
-    """kpm_moments (two planes with one vector, six otherwise) and stacks of one structure
-    and of several (five, whatever the vectors)."""
+    """kpm_moments (a pair of planes with one vector, five planes otherwise) and stacks of one
+    structure and of several (a pair beside the sweep's vectors, whatever their number)."""
     seen = set()
     for n, d, R, f64, onsite, M, segs, sweep, off_planes, total, planes, taken, vec, whole in layouts:
         assert taken <= planes and whole
@@ -34,3 +34,20 @@ def test_planes_lie_inside_the_workspace(layouts):
         assert off_planes + taken * vec <= total
         seen.add((segs, R))
     assert {(1, 1), (1, 3), (0, 1), (7, 64)} <= seen
+
+
+def test_a_larger_number_of_moments_never_needs_less(layouts):
+    """One buffer sized for the largest M serves every call of a run split over calls."""
+    last = {}
+    for n, d, R, f64, onsite, M, segs, sweep, off_planes, total, *_ in layouts:
+        key = (n, d, R, f64, onsite, segs)
+        assert last.get(key, (0, 0))[0] < M and last.get(key, (0, 0))[1] <= total
+        last[key] = (M, total)
+
+
+def test_planes_are_bounded_whatever_the_vectors(layouts):
+    """100 M rows: the sweep's workspace, the lists and 32 GB of planes at most."""
+    for n, d, R, f64, onsite, M, segs, sweep, off_planes, total, planes, taken, vec, whole in layouts:
+        if n == 100000000 and segs == 0 and R > 1:
+            assert total - off_planes <= (32 << 30) + 4096
+            assert off_planes - sweep <= n * 160 + (64 << 20) + M * R * 64 * 1024
