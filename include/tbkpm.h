@@ -264,11 +264,14 @@ tbk_status kpm_default_config(const tbk_ham *h, int32_t R, int32_t precision, tb
 /* Bytes of device workspace kpm_moments needs for (h, R, M, precision) with the
  * default launch shape (kpm_workspace_size) or a given one (cfg may be NULL).
  * This includes the lists and vectors of the steps on tiles; a buffer that is
- * large enough for the sweep alone is accepted too, and the sweep then runs. */
+ * large enough for the sweep alone (kpm_least_workspace_size) is accepted too, and
+ * the sweep then runs: the same vectors, moments that differ in the last bits. */
 tbk_status kpm_workspace_size(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
                               int64_t *bytes);
 tbk_status kpm_workspace_size_config(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
                                      const tbk_kpm_config *cfg, int64_t *bytes);
+tbk_status kpm_least_workspace_size(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
+                                    const tbk_kpm_config *cfg, int64_t *bytes);
 
 /*
  * Scale of the Chebyshev expansion (Sec. 2.4: the expansion needs the spectrum
@@ -377,8 +380,9 @@ tbk_status tbk_random_phase(uint64_t seed, int64_t n, int32_t R, int32_t precisi
  * a[s] > 0, b[s] (host double [n_seg]) and mu is device double
  * [n_seg][R][M], mu[s][v][n] = Re <r_v|T_n>_s over the rows of s.  r is
  * [n_rows][R] in the caller's stacked atom order.  The workspace size depends
- * on the structures' sizes and is queried with kpm_workspace_size_batched
- * (which reads h->seg_rows and synchronises `stream`).  Launch shapes as in
+ * on the structures' sizes and is queried with kpm_workspace_size_batched, the
+ * smallest accepted (of the sweep) with kpm_least_workspace_size_batched
+ * (both read h->seg_rows and synchronise `stream`).  Launch shapes as in
  * kpm_moments_config (xcd_remap and rows_per_thread are not used here); with
  * cfg->persistent = 1 all M - 1 steps run in one cooperative launch (DEVICE if a
  * team barrier times out; UNSUPPORTED with more structures than co-resident
@@ -387,6 +391,8 @@ tbk_status tbk_random_phase(uint64_t seed, int64_t n, int32_t R, int32_t precisi
  */
 tbk_status kpm_workspace_size_batched(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
                                       const tbk_kpm_config *cfg, int64_t *bytes, void *stream);
+tbk_status kpm_least_workspace_size_batched(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
+                                            const tbk_kpm_config *cfg, int64_t *bytes, void *stream);
 tbk_status kpm_moments_batched(const tbk_ham *h, const double *a, const double *b, const void *r,
                                int32_t R, int32_t M, int32_t precision, const tbk_kpm_config *cfg,
                                void *work, int64_t work_bytes, double *mu, void *stream);
@@ -826,9 +832,11 @@ int32_t lsqt_chebyshev_terms(double a, double dt);
  * (B = the time batch, below), six [n_rows][R_pad] vectors and, when B > 1, the
  * batch's start and left vectors and moments, and the lists and vectors of the
  * form that propagates and steps on tiles.  A buffer large enough without the
- * latter is accepted; the sweeps then run. */
+ * latter (lsqt_least_workspace_size) is accepted; the sweeps then run. */
 tbk_status lsqt_workspace_size(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
                                int32_t time_batch, const tbk_kpm_config *cfg, int64_t *bytes);
+tbk_status lsqt_least_workspace_size(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
+                                     int32_t time_batch, const tbk_kpm_config *cfg, int64_t *bytes);
 
 /*
  * Correlation moments of Eq. (3) with the random-phase trace of Sec. 2.4:

@@ -400,6 +400,17 @@ extern "C" tbk_status kpm_workspace_size_config(const tbk_ham *h, int32_t R, int
     return TBK_OK;
 }
 
+extern "C" tbk_status kpm_least_workspace_size(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
+                                               const tbk_kpm_config *cfg, int64_t *bytes) {
+    clear_error();
+    TBK_CHECK(bytes != nullptr, TBK_ERR_INVALID_ARG, "bytes is NULL");
+    KpmPlan pl;
+    tbk_status st = make_plan(h, R, M, precision, cfg, pl);
+    if (st != TBK_OK) return st;
+    *bytes = (int64_t)pl.total;
+    return TBK_OK;
+}
+
 extern "C" tbk_status kpm_moments(const tbk_ham *h, const double *a, const double *b, const void *r,
                                   int32_t R, int32_t M, int32_t precision, int32_t n_start, void *work,
                                   int64_t work_bytes, double *mu, void *stream) {

@@ -787,6 +787,17 @@ extern "C" tbk_status kpm_workspace_size_batched(const tbk_ham *h, int32_t R, in
     return TBK_OK;
 }
 
+extern "C" tbk_status kpm_least_workspace_size_batched(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
+                                                       const tbk_kpm_config *cfg, int64_t *bytes, void *stream) {
+    clear_error();
+    TBK_CHECK(bytes != nullptr, TBK_ERR_INVALID_ARG, "bytes is NULL");
+    SegPlan sp;
+    tbk_status st = make_seg_plan(h, R, M, precision, cfg, as_stream(stream), sp);
+    if (st != TBK_OK) return st;
+    *bytes = (int64_t)sp.total;
+    return TBK_OK;
+}
+
 extern "C" tbk_status kpm_moments_batched(const tbk_ham *h, const double *a, const double *b, const void *r,
                                           int32_t R, int32_t M, int32_t precision, const tbk_kpm_config *cfg,
                                           void *work, int64_t work_bytes, double *mu, void *stream) {

@@ -690,6 +690,17 @@ extern "C" tbk_status lsqt_workspace_size(const tbk_ham *h, int32_t R, int32_t M
     return TBK_OK;
 }
 
+extern "C" tbk_status lsqt_least_workspace_size(const tbk_ham *h, int32_t R, int32_t M, int32_t precision,
+                                                int32_t time_batch, const tbk_kpm_config *cfg, int64_t *bytes) {
+    clear_error();
+    TBK_CHECK(bytes != nullptr, TBK_ERR_INVALID_ARG, "bytes is NULL");
+    LsqtLayout ly;
+    tbk_status st = make_layout(h, R, M, precision, time_batch, cfg, false, ly);
+    if (st != TBK_OK) return st;
+    *bytes = (int64_t)ly.total;
+    return TBK_OK;
+}
+
 extern "C" tbk_status lsqt_vac_moments(const tbk_ham *h, const void *vx, double a, double b, const void *r,
                                        int32_t R, int32_t M, int32_t n_t, double dt, int32_t n_cheb,
                                        int32_t precision, int32_t time_batch, const tbk_kpm_config *cfg,

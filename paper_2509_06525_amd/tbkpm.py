@@ -56,16 +56,17 @@ ABI_SYMBOLS = ("tbk_last_error", "tbk_abi_version",
                "tbk_hamiltonian_size", "tb_build_hamiltonian",
                "tbk_hamiltonian_size_batched", "tb_build_hamiltonian_batched",
                "tbk_hamiltonian_size_sk", "tb_build_hamiltonian_sk",
-               "kpm_default_config", "kpm_workspace_size", "kpm_workspace_size_config",
+               "kpm_default_config", "kpm_workspace_size", "kpm_workspace_size_config", "kpm_least_workspace_size",
                "kpm_scale", "kpm_moments", "kpm_moments_config", "kpm_moments_seeded", "tbk_random_phase",
                "kpm_mean_moments", "kpm_step_timer", "kpm_step_timer_read", "tbk_bandwidth_probe",
                "tbk_bandwidth_probe_words", "kpm_moments_noalloc",
-               "kpm_workspace_size_batched", "kpm_moments_batched",
+               "kpm_workspace_size_batched", "kpm_least_workspace_size_batched", "kpm_moments_batched",
                "kpm_dos", "kpm_dos_batched", "tbk_autotune", "tbk_autotune_form",
                "tbk_descriptor", "tbk_bonds", "tbk_bond_features", "tbk_feature_moments",
                "tbk_coordination_target", "tbk_mlp_forward", "tbk_mlp_workspace_size",
                "tbk_mlp_loss_grad", "tbk_adamw_step", "tbk_mlp_train", "tb_build_hamiltonian_learned",
-               "tb_build_velocity", "lsqt_chebyshev_terms", "lsqt_workspace_size", "lsqt_vac_moments",
+               "tb_build_velocity", "lsqt_chebyshev_terms", "lsqt_workspace_size", "lsqt_least_workspace_size",
+               "lsqt_vac_moments",
                "lsqt_sigma", "kpm_integrated_dos", "lsqt_mobility", "tb_build_hamiltonian_sk_learned",
                "tbk_node_features", "tbk_descriptor_species", "tbk_bond_features_species")
 
@@ -186,6 +187,8 @@ def lib():
     L.kpm_workspace_size_config.restype = ctypes.c_int
     L.kpm_workspace_size_config.argtypes = [ctypes.POINTER(HamStruct), i32, i32, i32,
                                             ctypes.POINTER(KpmConfig), ctypes.POINTER(i64)]
+    L.kpm_least_workspace_size.restype = ctypes.c_int
+    L.kpm_least_workspace_size.argtypes = L.kpm_workspace_size_config.argtypes
     L.kpm_moments_config.restype = ctypes.c_int
     L.kpm_moments_config.argtypes = [ctypes.POINTER(HamStruct), ctypes.POINTER(f64), ctypes.POINTER(f64),
                                      vp, i32, i32, i32, ctypes.POINTER(KpmConfig), i32, vp, i64, vp, vp]
@@ -207,6 +210,8 @@ def lib():
     L.kpm_workspace_size_batched.restype = ctypes.c_int
     L.kpm_workspace_size_batched.argtypes = [ctypes.POINTER(HamStruct), i32, i32, i32, ctypes.POINTER(KpmConfig),
                                              ctypes.POINTER(i64), vp]
+    L.kpm_least_workspace_size_batched.restype = ctypes.c_int
+    L.kpm_least_workspace_size_batched.argtypes = L.kpm_workspace_size_batched.argtypes
     L.kpm_moments_batched.restype = ctypes.c_int
     L.kpm_moments_batched.argtypes = [ctypes.POINTER(HamStruct), ctypes.POINTER(f64), ctypes.POINTER(f64), vp,
                                       i32, i32, i32, ctypes.POINTER(KpmConfig), vp, i64, vp, vp]
@@ -260,6 +265,8 @@ def lib():
     L.lsqt_workspace_size.restype = ctypes.c_int
     L.lsqt_workspace_size.argtypes = [ctypes.POINTER(HamStruct), i32, i32, i32, i32, ctypes.POINTER(KpmConfig),
                                       ctypes.POINTER(i64)]
+    L.lsqt_least_workspace_size.restype = ctypes.c_int
+    L.lsqt_least_workspace_size.argtypes = L.lsqt_workspace_size.argtypes
     L.lsqt_vac_moments.restype = ctypes.c_int
     L.lsqt_vac_moments.argtypes = [ctypes.POINTER(HamStruct), vp, f64, f64, vp, i32, i32, i32, f64, i32, i32,
                                    i32, ctypes.POINTER(KpmConfig), vp, i64, vp, vp]
@@ -543,11 +550,30 @@ def workspace_size(H, R, M, precision, config=None):
     return out.value
 
 
-def alloc_workspace(H, R, M, precision, device=None, config=None):
-    nbytes = workspace_size(H, R, M, precision, config)
-    dev = device if device is not None else H.tensors["ptr"].device
+def least_workspace_size(H, R, M, precision, config=None):
+    """Bytes of the smallest workspace kpm_moments takes (one step per launch then)."""
+    out = ctypes.c_int64(0)
+    _check(lib().kpm_least_workspace_size(ctypes.byref(H.st), int(R), int(M), PRECISIONS[precision],
+                                          _cfg_ref(config), ctypes.byref(out)))
+    return out.value
+
+
+def _alloc_work(nbytes, least, device):
+    """nbytes of workspace, or least() where the device has no room for them."""
     # torch's caching allocator returns 512-byte aligned blocks
-    return torch.empty(nbytes, dtype=torch.uint8, device=dev)
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        small = least()
+        if small >= nbytes:
+            raise
+    return torch.empty(small, dtype=torch.uint8, device=device)
+
+
+def alloc_workspace(H, R, M, precision, device=None, config=None):
+    dev = device if device is not None else H.tensors["ptr"].device
+    return _alloc_work(workspace_size(H, R, M, precision, config),
+                       lambda: least_workspace_size(H, R, M, precision, config), dev)
 
 
 def kpm_scale(bounds, margin=1.01):
@@ -763,6 +789,14 @@ def workspace_size_batched(H, R, M, precision, config=None, stream=None):
     return out.value
 
 
+def least_workspace_size_batched(H, R, M, precision, config=None, stream=None):
+    """Bytes of the smallest workspace kpm_moments_batched takes (one step per launch then)."""
+    out = ctypes.c_int64(0)
+    _check(lib().kpm_least_workspace_size_batched(ctypes.byref(H.st), int(R), int(M), PRECISIONS[precision],
+                                                  _cfg_ref(config), ctypes.byref(out), _stream(stream)))
+    return out.value
+
+
 def kpm_moments_batched(H, a, b, r, M, precision=None, work=None, mu=None, stream=None, config=None):
     """mu[s][v][n] (float64, device) for every structure s of a stacked Hamiltonian."""
     L = lib()
@@ -775,8 +809,8 @@ def kpm_moments_batched(H, a, b, r, M, precision=None, work=None, mu=None, strea
     R = r.shape[1]
     ns = H.n_seg
     if work is None:
-        work = torch.empty(workspace_size_batched(H, R, M, precision, config, stream), dtype=torch.uint8,
-                           device=r.device)
+        work = _alloc_work(workspace_size_batched(H, R, M, precision, config, stream),
+                           lambda: least_workspace_size_batched(H, R, M, precision, config, stream), r.device)
     if mu is None:
         mu = torch.empty((ns, R, M), dtype=torch.float64, device=r.device)
     av = (ctypes.c_double * ns)(*[float(v) for v in a])
@@ -1012,6 +1046,15 @@ def vac_time_batch(R, time_batch=0):
     return int(time_batch) if time_batch > 0 else max(1, 16 // int(R))
 
 
+def vac_workspace_size(H, R, M, precision, config=None, time_batch=0, least=False):
+    """Bytes of workspace for vac_moments; least: of the smallest it takes (one step per launch then)."""
+    size = lib().lsqt_least_workspace_size if least else lib().lsqt_workspace_size
+    out = ctypes.c_int64(0)
+    _check(size(ctypes.byref(H.st), int(R), int(M), PRECISIONS[precision], int(time_batch), _cfg_ref(config),
+                ctypes.byref(out)))
+    return out.value
+
+
 def vac_moments(H, vx, a, b, r, M, n_t, dt, n_cheb=0, precision=None, config=None, work=None, stream=None,
                 time_batch=0):
     """nu [n_t][R][M] (float64, device): Re <phi_L(t_j)| T_m(Ht) V |phi_R(t_j)> for start vectors r [N, R].
@@ -1026,10 +1069,8 @@ def vac_moments(H, vx, a, b, r, M, n_t, dt, n_cheb=0, precision=None, config=Non
         r = r.reshape(-1, 1)
     R = r.shape[1]
     if work is None:
-        nbytes = ctypes.c_int64(0)
-        _check(L.lsqt_workspace_size(ctypes.byref(H.st), R, int(M), PRECISIONS[precision], int(time_batch),
-                                     _cfg_ref(config), ctypes.byref(nbytes)))
-        work = torch.empty(nbytes.value, dtype=torch.uint8, device=r.device)
+        work = _alloc_work(vac_workspace_size(H, R, M, precision, config, time_batch),
+                           lambda: vac_workspace_size(H, R, M, precision, config, time_batch, least=True), r.device)
     nu = torch.empty((int(n_t), R, int(M)), dtype=torch.float64, device=r.device)
     _check(L.lsqt_vac_moments(ctypes.byref(H.st), _ptr(vx), float(a), float(b), _ptr(r), R, int(M), int(n_t),
                               float(dt), int(n_cheb), PRECISIONS[precision], int(time_batch), _cfg_ref(config),
