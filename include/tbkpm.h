@@ -337,7 +337,8 @@ tbk_status kpm_moments_config(const tbk_ham *h, const double *a, const double *b
  * kpm_moments_config without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  The workspace is a static device array of
- * the library, 384 MiB on each GPU it runs on, held until the process ends; this
+ * the library, 336 MiB on each GPU this entry point is used on (none elsewhere:
+ * the runtime loads it with the first call), held until the process ends; this
  * call makes no allocation (no hipMalloc, hipFree or allocating library
  * routine).  Every call on one GPU shares that GPU's array, which keeps the
  * last call's contents: n_start > 0 continues the run the last call on this

@@ -3,7 +3,6 @@
 // instances of kpm_run.hpp, checkpoint/resume of a run, and the C entry points.
 #include <algorithm>
 #include <cmath>
-#include <mutex>
 
 #include "common.hpp"
 #include "kpm.hpp"
@@ -21,30 +20,6 @@ int log2_exact(int x) {
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
-// Workspace of kpm_moments_noalloc: one array per GPU, part of the loaded code
-// object (no allocation call), shared by every call on that GPU.  Host code
-// uses the device address hipGetSymbolAddress returns for the current device,
-// never the array's name (a host-side stand-in).
-constexpr int kScratchDevices = 64;
-static __device__ __align__(256) char scratch[kStaticBytes];
-std::mutex g_scratch_mu;
-void *g_scratch_ptr[kScratchDevices] = {};
-
-tbk_status scratch_address(void **out) {
-    int dev = -1;
-    TBK_HIP(hipGetDevice(&dev));
-    TBK_CHECK(dev >= 0 && dev < kScratchDevices, TBK_ERR_UNSUPPORTED, "device %d: no workspace slot", dev);
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    if (!g_scratch_ptr[dev]) {
-        void *p = nullptr;
-        TBK_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-        TBK_CHECK(p != nullptr, TBK_ERR_DEVICE, "no device address for the static workspace");
-        g_scratch_ptr[dev] = p;
-    }
-    *out = g_scratch_ptr[dev];
-    return TBK_OK;
-}
 
 }  // namespace
 
@@ -453,9 +428,10 @@ extern "C" tbk_status kpm_moments_noalloc(const tbk_ham *h, const double *a, con
               "takes (use kpm_moments_config with a caller-allocated workspace)",
               (long long)pl.total, (long long)kStaticSweepBytes);
     void *work = nullptr;
-    st = scratch_address(&work);
+    st = static_workspace(&work);
     if (st != TBK_OK) return st;
     st = check_moment_args(h, pl, a, b, r, work, (int64_t)kStaticBytes, mu);
+    TBK_CHECK(!pl.tile.on || pl.tile.total <= kStaticBytes, TBK_ERR_DEVICE, "the tiles exceed the static workspace");
     if (st != TBK_OK) return st;
     TBK_CHECK(pl.cfg.persistent == 0, TBK_ERR_INVALID_ARG, "the persistent launch is for kpm_moments_batched");
     st = check_resume(h, pl, a[0], b[0], R, M, precision, work, as_stream(stream));

@@ -12,7 +12,10 @@ constexpr int kReduceChunk = 2048;                 // partials per first-level r
 constexpr size_t kPartialBudget = 256ull << 20;    // bytes of block partials kept between reductions
 
 constexpr size_t kStaticSweepBytes = 64ull << 20;   // kpm_moments_noalloc takes runs whose sweep fits in this
-constexpr size_t kStaticBytes = 384ull << 20;       // its static workspace (the tiled form's lists and planes too)
+// Its static workspace holds what those runs take on tiles (332 MiB at most, for 2.7 M rows of
+// 5 or 6 entries and one vector: 64 of the sweep, 227 of lists, 41 of planes), so that they
+// run in the form they run in with a caller's workspace, with the same sums.
+constexpr size_t kStaticBytes = 336ull << 20;
 constexpr int kTileMaxS = 16;                      // most steps per launch of the tiled form (with a halo)
 
 // Layout of the tiled form (kpm_tile.hpp) behind a plan's sweep workspace.
@@ -137,6 +140,9 @@ template <class VT> struct StepPtrs {
 template <class VT>
 tbk_status launch_step_block(const KpmPlan &pl, bool first, bool diag, hipStream_t s, const StepPtrs<VT> &p,
                              const StepScalars<VT> &a);
+
+// Address of the kStaticBytes static workspace of the current device.
+tbk_status static_workspace(void **out);
 
 int pad_vectors(int R);
 tbk_kpm_config default_config(const tbk_ham *h, int32_t R, int32_t precision);

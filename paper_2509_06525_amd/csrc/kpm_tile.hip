@@ -594,9 +594,7 @@ void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t 
         layout_width(h, pl, base, R, n_seg, planes, sets, pl.tile.W == 3 ? 4 : 3, other);
         pl.tile.total = std::max(pl.tile.total, other.total);
     }
-    // runs that the static workspace takes get the same form with it as with a caller's
-    pl.tile.on = base > kStaticSweepBytes || pl.tile.total <= kStaticBytes;
-    if (!pl.tile.on) pl.tile.total = base;
+    pl.tile.on = true;
 }
 
 // Tile lists of h (or of its structures, whose row0 table the caller has

@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 @pytest.fixture(scope="module")
-def layouts(tmp_path_factory):
+def program(tmp_path_factory):
     if not os.path.exists(tbkpm.LIB_PATH):
         build.build()
     exe = str(tmp_path_factory.mktemp("native") / "tile_layout")
@@ -20,7 +20,12 @@ def layouts(tmp_path_factory):
                     os.path.join(rocm, "include"), os.path.join(HERE, "native", "tile_layout.cpp"), tbkpm.LIB_PATH,
                     "-Wl,-rpath," + os.path.dirname(tbkpm.LIB_PATH), "-L", os.path.join(rocm, "lib"), "-lamdhip64",
                     "-Wl,-rpath," + os.path.join(rocm, "lib"), "-o", exe], check=True)
-    out = subprocess.run([exe], check=True, capture_output=True, text=True).stdout
+    return exe
+
+
+@pytest.fixture(scope="module")
+def layouts(program):
+    out = subprocess.run([program], check=True, capture_output=True, text=True).stdout
     return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
 
 
@@ -51,3 +56,12 @@ def test_planes_are_bounded_whatever_the_vectors(layouts):
         if n == 100000000 and segs == 0 and R > 1:
             assert total - off_planes <= (32 << 30) + 4096
             assert off_planes - sweep <= n * 160 + (64 << 20) + M * R * 64 * 1024
+
+
+def test_the_static_workspace_is_what_its_runs_take(program):
+    """Every run whose sweep kpm_moments_noalloc takes fits its array on tiles, too (the
+    same form, so the same sums, as with a caller's workspace), with a few MiB to spare."""
+    out = subprocess.run([program, "static"], check=True, capture_output=True, text=True).stdout
+    runs, off, most, static = (int(x) for x in out.split())
+    assert runs > 100000 and off == 0
+    assert static - (8 << 20) < most <= static
