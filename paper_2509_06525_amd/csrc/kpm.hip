@@ -171,6 +171,10 @@ tbk_status make_plan(const tbk_ham *h, int32_t R, int32_t M, int32_t precision, 
     pl.off_flag = pl.off_raw + align256((size_t)pl.Mr * Rout * sizeof(double));
     pl.total = pl.off_flag + 256;
     tile_layout(h, pl, pl.total, R, 1, pl.Rp == 1 ? kPlanesDirect : kPlanesRun, true);
+    if (pl.tile.on && pl.cfg.doubling && !tile_pays(pl.tile, pl.Mr - 1)) {
+        pl.tile.on = false;
+        pl.tile.total = pl.total;
+    }
     return TBK_OK;
 }
 

@@ -73,6 +73,11 @@ constexpr int kPlanesStack = 2;        // run_seg_tiled: a pair (no state is kep
 constexpr int kPlanesPropagate = 5;    // propagate_tiled: two pairs and the series' sum
 constexpr int kPlanesMax = 5;
 
+// Whether `steps` steps on tiles make up for listing them.  Asked for runs that cannot be
+// continued alone (stacks, the doubling form): the parts of a run split over calls have to
+// group their sums as one run does, however few steps a part has.
+bool tile_pays(const TilePlan &tp, int steps);
+
 // Fills pl.tile for n_seg structures and a run that takes `planes` planes; its workspace
 // starts at byte `base`.  sets: the run can take its vectors in sets of pl.tile.Rc.
 void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes, bool sets = false);

@@ -399,6 +399,10 @@ tbk_status make_seg_plan(const tbk_ham *h, int32_t R, int32_t M, int32_t precisi
     sp.off_flag = sp.off_shift + a256(ve * sp.n_seg);
     sp.total = sp.off_flag + 256;
     tile_layout(h, sp.base, sp.total, R, sp.n_seg, kPlanesStack);
+    if (sp.base.tile.on && !tile_pays(sp.base.tile, M - 1)) {
+        sp.base.tile.on = false;
+        sp.base.tile.total = sp.total;
+    }
     if (sp.base.tile.on) {
         // tiles of the tiled form: a structure that fits is one tile, others are cut evenly
         const TilePlan &tp = sp.base.tile;

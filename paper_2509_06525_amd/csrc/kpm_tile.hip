@@ -583,6 +583,16 @@ void layout_width(const tbk_ham *h, const KpmPlan &pl, size_t base, int32_t R, i
 
 }  // namespace
 
+// The probe, the lists and the wait between them against the sweep's steps, us per call on
+// tiles and swept: 2,304 rows, 4 steps of doubling 81, 84; 30,212 rows, three vectors, 16 and
+// 31 steps 161, 124 and 186, 205; a stack of 20,180 rows, eight vectors, 23 and 31 steps 230,
+// 204 and 237, 236; 250,000 rows in FP64, four vectors, 8 and 12 steps 214, 181 and 223, 235; 16 M
+// rows, 10 and 12 steps 1479, 1378 and 1519, 1628; a stack of 867,364 rows, eight vectors, 7
+// and 11 steps 409, 429 and 502, 604.
+bool tile_pays(const TilePlan &tp, int steps) {
+    return steps >= (tp.shape == kTileWhole ? 4 : (tp.shape == kTileSmall ? 28 : 10));
+}
+
 void tile_layout(const tbk_ham *h, KpmPlan &pl, size_t base, int32_t R, int32_t n_seg, int planes, bool sets) {
     pl.tile = TilePlan{};
     pl.tile.total = base;

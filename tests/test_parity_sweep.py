@@ -29,14 +29,15 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(autouse=True)
 def smallest_workspace(monkeypatch):
     """Every workspace the binding or a test asks for is the sweep's, below that of the tiles
-    (the persistent launch, which is not offered tiles, has one size)."""
+    (the persistent launch and doubling runs of few moments, which are not offered tiles, have
+    one size)."""
     asked = []
 
     def least_of(full, least):
         def size(H, R, M, precision, config=None, *args, **kw):
             n = least(H, R, M, precision, config, *args, **kw)
-            persistent = config is not None and config.persistent
-            assert persistent or n < full(H, R, M, precision, config, *args, **kw)
+            swept = config is not None and (config.persistent or (config.doubling and M < 8))
+            assert swept or n < full(H, R, M, precision, config, *args, **kw)
             asked.append(n)
             return n
         return size
