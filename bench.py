@@ -18,7 +18,9 @@ may exceed the peak; `traffic` is the measured HBM bytes per step, and
 profile).  `cpu_baseline` times the serial FP64
 oracle (one core) on a bounded sample of the same workload.  `variants` reports,
 each under its own label, the same moments computed with the doubling
-identities and, when all stored hoppings are equal, without reading them.
+identities and, when all stored hoppings are equal and the sweep runs, without
+reading them.  `tuning` is the tuner's choice for the sweep; a run on tiles takes
+its slice height only.
 """
 import argparse
 import hashlib
@@ -106,9 +108,10 @@ def kernel_source_hash(files=KERNEL_SOURCES):
 TILE_KERNEL_SOURCES = ("kpm_tile.hip", "kpm_tile.hpp", "kpm_tile_inst.hpp", "kpm.hpp", "kpm_dev.hpp")
 
 
-def on_tiles(H, cfg):
-    """Several steps per launch (k_tile_steps): one-orbital rows of up to six entries."""
-    return H.st.n_orb == 1 and 1 <= H.st.max_degree <= 6 and not (cfg is not None and cfg.persistent)
+def on_tiles():
+    """Whether the last recurrence took several steps per launch (k_tile_steps)."""
+    from paper_2509_06525_amd import tbkpm
+    return tbkpm.last_form()[0] > 0
 
 
 def tile_roofline(rl, traffic=None, step_s=None):
@@ -352,6 +355,7 @@ def bench_snapshots(args, w):
         Rp *= 2
     launch_bytes = st.n_entries * 8 + st.n_ptr * 8 + N * Rp * 8 * 4
     launch_s = step_ms * 1e-3 / step_launches if step_launches else kmed * 1e-3 / (M - 1)
+    tiles = on_tiles()
     achieved = launch_bytes / launch_s / 1e9
     comparison = None if args.no_train else learned_vs_plain(dev, gpos, gsp, seg, boxes, per, params, mean, std,
                                                              r, M, stream)
@@ -374,11 +378,11 @@ def bench_snapshots(args, w):
                                        "FETCH_SIZE, WRITE_SIZE runs, copy-calibrated; null when the kernel or "
                                        "launch shape differs)",
                      "kernel": "k_cheb_persistent" if cfg.persistent else (
-                         "k_tile_steps" if on_tiles(H, cfg) else "k_cheb_step_seg"),
+                         "k_tile_steps" if tiles else "k_cheb_step_seg"),
                      "bytes_per_launch": launch_bytes, "launch_us": launch_s * 1e6,
                      "launches_timed": step_launches, "launch_us_kpm_window": kmed * 1e3 / (M - 1)},
     }
-    if on_tiles(H, cfg):
+    if tiles:
         tile_roofline(out["roofline"])
     out["roofline"].update(stream_probe(dev))
     print(json.dumps(out), flush=True)
@@ -448,6 +452,7 @@ def kpm_variant(args, label, fields, H, a, b, r, M, R, Rp, elem, diag, precision
         torch.cuda.synchronize()
         ms.append(e0.elapsed_time(e1))
     med = float(np.median(ms))
+    tiles = on_tiles()
     rho = tbkpm.kpm_dos(tbkpm.mean_moments(mu, stream=stream), a, b, E, stream=stream).cpu().numpy()
     dbl = bool(cfg.doubling)
     launches = M // 2 if dbl else M - 1
@@ -464,9 +469,9 @@ def kpm_variant(args, label, fields, H, a, b, r, M, R, Rp, elem, diag, precision
            "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": achieved / HBM_PEAK_GBS,
                         "traffic": profiled_traffic(args.workload, label, H.st.slice, cfg.as_dict()),
-                        "kernel": f"{'k_tile_steps' if on_tiles(H, cfg) else 'k_cheb_step'} ({label})",
+                        "kernel": f"{'k_tile_steps' if tiles else 'k_cheb_step'} ({label})",
                         "bytes_per_launch": launch_bytes, "launch_us": launch_s * 1e6}}
-    if on_tiles(H, cfg):
+    if tiles:
         tile_roofline(out["roofline"])
     return out
 
@@ -837,6 +842,7 @@ def bench_vac(args, w):
     vel = hb + nr * Rp * 8 * 2
     total = F * (rec + n_t * ((n_cheb - 1) * prop + vel))
     achieved = total / sec / 1e9
+    tiles = on_tiles()
     out = {
         "metric": "VAC atom*moments*timesteps/s" if not sk else "VAC orbital*moments*timesteps/s",
         "value": F * nr * M * R * n_t / sec,
@@ -852,11 +858,12 @@ def bench_vac(args, w):
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
                      "kernel": "whole VAC step (k_cheb_step_atom pair form, k_evolve_term_atom, "
                                "k_apply_velocity_blk)" if sk else
-                               "whole VAC step (k_tile_steps pair and propagator forms, k_velocity_planes)",
+                               "whole VAC step (k_tile_steps pair and propagator forms, k_velocity_planes)" if tiles else
+                               "whole VAC step (k_cheb_step pair form, k_evolve_term, k_apply_velocity)",
                      "bytes_per_step": total},
         "sigma_max": float(sig[-1].abs().max()),
     }
-    if not sk:
+    if tiles:
         tile_roofline(out["roofline"])
     if F > 1:
         # carriers per cm^2 (spin 2, sheet area) and the mobility at a few concentrations
@@ -989,7 +996,7 @@ def main():
     kpm_med = float(np.median(kpm_ms))
     launch_s = step_ms * 1e-3 / step_launches
     achieved = launch_bytes / launch_s / 1e9
-    tiles = on_tiles(Hs, launch_cfg)
+    tiles = on_tiles()
     kernel = "k_tile_steps" if tiles else "k_cheb_step"
     traffic = profiled_traffic(args.workload, "direct", slice_, launch_cfg.as_dict(), kernel,
                                TILE_KERNEL_SOURCES if tiles else KERNEL_SOURCES)
@@ -1005,7 +1012,7 @@ def main():
                    "format": fmt, "slice": slice_, "precision": w["precision"],
                    "a_eV": aa, "b_eV": bb},
         "kpm_ms_median": kpm_med,
-        "tuning": None if tune is None else {"slice": tune.slice, "launch": tune.config.as_dict(),
+        "tuning": None if tune is None else {"form": "sweep", "slice": tune.slice, "launch": tune.config.as_dict(),
                                              "tuned_ms_per_step": tune.ms_per_step,
                                              "candidates": tune.candidates},
         "kpm_atom_moments_per_s": N * M * R / (kpm_med * 1e-3),
@@ -1046,7 +1053,7 @@ def main():
         pass
     elif not args.no_doubling and M >= 2:
         variants.append(("doubling", {"doubling": 1}))
-    if Hs.st.uniform_hop and not args.no_variants:
+    if Hs.st.uniform_hop and not args.no_variants and not tiles:       # on tiles found by itself, not asked for
         variants.append(("uniform_values", {"uniform_values": 1}))
         if not args.no_doubling and M >= 2:
             variants.append(("doubling_uniform_values", {"doubling": 1, "uniform_values": 1}))

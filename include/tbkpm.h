@@ -416,6 +416,16 @@ tbk_status kpm_step_timer(int32_t enable);
 tbk_status kpm_step_timer_read(double *ms, int64_t *launches);
 
 /*
+ * How the calling thread's last recurrence stepped (of a kpm_moments*,
+ * kpm_moments_batched or lsqt_vac_moments call, or the tuner's; a measurement aid:
+ * which form runs depends on the matrix and on the workspace):
+ *   tiles   tiles held in LDS, 0: the sweep;
+ *   steps   most steps of one launch (sweep: 1; persistent launch: M - 1).
+ * 0 and 0 before the first.  Errors: INVALID_ARG (NULL).
+ */
+tbk_status kpm_last_form(int32_t *tiles, int32_t *steps);
+
+/*
  * Bandwidth probes (measurement aid: the HBM ceilings a bandwidth-bound step
  * such as the recurrence of Sec. 2.4 is rated beside):
  *   mode 1: copy `bytes` from src to dst (device, 16-byte aligned, no overlap);

@@ -28,6 +28,11 @@ StepTimer &step_timer() {
     return t;
 }
 
+RunForm &run_form() {
+    static thread_local RunForm f;
+    return f;
+}
+
 hipError_t StepTimer::mark(hipStream_t s) {
     if (used == ev.size()) {
         hipEvent_t e;
@@ -210,6 +215,7 @@ tbk_status run_plan(const tbk_ham *h, const KpmPlan &pl, double a, double b, con
             if (!retry) return st;
         }
     }
+    run_form() = {0, 1};
     const double *sd = static_cast<const double *>(start), *ld_ = static_cast<const double *>(left);
     const float *sf = static_cast<const float *>(start), *lf = static_cast<const float *>(left);
     if (precision == TBK_PREC_F64) {
@@ -350,6 +356,14 @@ extern "C" tbk_status kpm_step_timer_read(double *ms, int64_t *launches) {
     *launches = t.launches;
     t.ms = 0.0;
     t.launches = 0;
+    return TBK_OK;
+}
+
+extern "C" tbk_status kpm_last_form(int32_t *tiles, int32_t *steps) {
+    clear_error();
+    TBK_CHECK(tiles && steps, TBK_ERR_INVALID_ARG, "NULL argument");
+    *tiles = run_form().tiles;
+    *steps = run_form().steps;
     return TBK_OK;
 }
 

@@ -110,6 +110,12 @@ struct StepTimer {
 };
 StepTimer &step_timer();
 
+// What kpm_last_form reports, one per host thread.
+struct RunForm {
+    int32_t tiles = 0, steps = 0;
+};
+RunForm &run_form();
+
 // Per-launch scalars of a step (pointers go as separate restrict parameters).
 template <class VT> struct StepScalars {
     int64_t n_rows;

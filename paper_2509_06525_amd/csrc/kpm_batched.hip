@@ -686,6 +686,7 @@ tbk_status run_seg_tiled(const tbk_ham *h, const SegPlan &sp, const double *a, c
     if (timer.on) timer.used = 0;
     const int steps = M - 1;
     const int groups = (int)ceil_div(steps, std::min<int64_t>(run.s, run.closed ? tp.reduce_every - 1 : kTileMaxS));
+    run_form() = {run.n_tiles, (int32_t)ceil_div(steps, groups)};
     int batch0 = 0, at = 0, dst = 0;
     const VT *cur = rp, *prev = rp;
     for (int q = 0; q < groups; ++q) {
@@ -737,6 +738,7 @@ tbk_status dispatch_seg(const tbk_ham *h, const SegPlan &sp, const double *a, co
                 : run_seg_tiled<float>(h, sp, a, b, static_cast<const float *>(r), R, M, w, mu, s, &done);
         if (st != TBK_OK || done) return st;
     }
+    run_form() = {0, sp.persistent ? M - 1 : 1};
     if (precision == TBK_PREC_F64) {
         const double *rr = static_cast<const double *>(r);
         switch (L) {

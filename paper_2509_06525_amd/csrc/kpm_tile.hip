@@ -785,6 +785,7 @@ tbk_status run_tiled(const tbk_ham *h, const KpmPlan &pl, const TileRun &run, do
     const int steps = pl.Mr - 1 - n0;
     const int most = std::min<int64_t>(run.s, run.closed ? tp.reduce_every - 1 : kTileMaxS);
     const int groups = (int)ceil_div(steps, most);
+    run_form() = {run.n_tiles, (int32_t)ceil_div(steps, groups)};
     for (int v0 = 0; v0 < (sets ? Rp : 1); v0 += Rc) {
         const int Rs = std::max(0, std::min(R - v0, Rc));      // vectors of the set (0: only padding)
         const int w = sets ? Rs * NA : Rout, Rv_c = sets ? Rc * NA : Rv;

@@ -58,7 +58,7 @@ ABI_SYMBOLS = ("tbk_last_error", "tbk_abi_version",
                "tbk_hamiltonian_size_sk", "tb_build_hamiltonian_sk",
                "kpm_default_config", "kpm_workspace_size", "kpm_workspace_size_config", "kpm_least_workspace_size",
                "kpm_scale", "kpm_moments", "kpm_moments_config", "kpm_moments_seeded", "tbk_random_phase",
-               "kpm_mean_moments", "kpm_step_timer", "kpm_step_timer_read", "tbk_bandwidth_probe",
+               "kpm_mean_moments", "kpm_step_timer", "kpm_step_timer_read", "kpm_last_form", "tbk_bandwidth_probe",
                "tbk_bandwidth_probe_words", "kpm_moments_noalloc",
                "kpm_workspace_size_batched", "kpm_least_workspace_size_batched", "kpm_moments_batched",
                "kpm_dos", "kpm_dos_batched", "tbk_autotune", "tbk_autotune_form",
@@ -180,6 +180,8 @@ def lib():
     L.tbk_bandwidth_probe_words.argtypes = []
     L.kpm_step_timer.restype = ctypes.c_int
     L.kpm_step_timer.argtypes = [i32]
+    L.kpm_last_form.restype = ctypes.c_int
+    L.kpm_last_form.argtypes = [ctypes.POINTER(i32), ctypes.POINTER(i32)]
     L.kpm_step_timer_read.restype = ctypes.c_int
     L.kpm_step_timer_read.argtypes = [ctypes.POINTER(f64), ctypes.POINTER(i64)]
     L.kpm_mean_moments.restype = ctypes.c_int
@@ -635,6 +637,13 @@ def step_timer_read():
     ms, n = ctypes.c_double(0.0), ctypes.c_int64(0)
     _check(lib().kpm_step_timer_read(ctypes.byref(ms), ctypes.byref(n)))
     return ms.value, n.value
+
+
+def last_form():
+    """(tiles, most steps of one launch) of this thread's last recurrence; no tiles: the sweep."""
+    tiles, steps = ctypes.c_int32(0), ctypes.c_int32(0)
+    _check(lib().kpm_last_form(ctypes.byref(tiles), ctypes.byref(steps)))
+    return tiles.value, steps.value
 
 
 def kpm_moments_noalloc(H, a, b, r, M, precision=None, mu=None, stream=None, config=None, n_start=0, R=None):

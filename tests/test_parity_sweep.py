@@ -46,4 +46,4 @@ def smallest_workspace(monkeypatch):
     monkeypatch.setattr(tbkpm, "workspace_size_batched",
                         least_of(tbkpm.workspace_size_batched, tbkpm.least_workspace_size_batched))
     yield
-    assert asked
+    assert asked and tbkpm.last_form()[0] == 0
