@@ -461,7 +461,8 @@ typedef struct {
  * the LSQT step, Sec. 2.4; only their speed depends on the choice): builds
  * H for each candidate slice, times `steps` recurrence steps of every
  * candidate shape on the GPU (HIP events on `stream`), returns the fastest.
- * Only speed depends on the choice.  Results are cached per device and
+ * Only speed depends on the choice.  The steps timed are the sweep's: a run on
+ * tiles (tbk_kpm_config) takes the slice height alone.  Results are cached per device and
  * problem class (size bucket, R, precision, format, degree, onsite) in
  * memory, and in the file named by the environment variable
  * TBKPM_AUTOTUNE_CACHE when set; TBKPM_AUTOTUNE=0 returns the defaults

@@ -199,11 +199,12 @@ tbk_status run_plan(const tbk_ham *h, const KpmPlan &pl, double a, double b, con
         if (tiles) run = *tiles;
         else {
             // only a fresh run can start again on the sweep
-            const bool defer = !left && pl.n_start == 0 && !step_timer().on;
+            const bool defer = !left && pl.n_start == 0;
             st = build_tiles(h, pl, precision, w, s, run, defer);
             if (st != TBK_OK) return st;
         }
         if (run.s > 0) {
+            const int64_t counted = step_timer().launches;
             if (precision == TBK_PREC_F64)
                 st = run_tiled<double>(h, pl, run, a, b, static_cast<const double *>(r), R, M, w, mu, s,
                                        static_cast<const double *>(start), static_cast<const double *>(left), false,
@@ -213,6 +214,7 @@ tbk_status run_plan(const tbk_ham *h, const KpmPlan &pl, double a, double b, con
                                       static_cast<const float *>(start), static_cast<const float *>(left), false,
                                       &retry);
             if (!retry) return st;
+            step_timer().launches = counted;
         }
     }
     run_form() = {0, 1};

@@ -30,7 +30,7 @@ namespace tbk {
 // Pointers and scalars of one launch of k_tile_steps.
 template <class VT> struct TileArgs {
     const int32_t *row0;     // [n_tiles + 1] first row of each tile
-    const int32_t *cnt;      // [n_tiles][S + 1] rows within k rings
+    const int32_t *cnt;      // [n_tiles][S1] rows within k rings
     const int32_t *ext;      // [n_tiles][cap] halo rows (local index nr + e)
     const uint32_t *lcol2;   // [n_tiles][W / 2][cap] pairs of LDS byte offsets
     const uint16_t *lcol1;   // [n_tiles][cap] the odd column (W odd)
@@ -47,7 +47,7 @@ template <class VT> struct TileArgs {
     int64_t rows;            // plane pitch
     int32_t n_work;          // n_tiles * R
     int32_t R, Rv;
-    int32_t S1, cap;
+    int32_t S1, cap;         // rings listed + 1, slots of a tile
     int32_t s;               // steps of this launch
     int32_t first;           // 1: T_n is T_0 (step 0 is T_1 = Ht T_0)
     int32_t closed;          // 1: no tile has a halo, so s is not limited by rings
