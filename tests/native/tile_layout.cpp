@@ -34,7 +34,7 @@ static int largest_static() {
                                 if (make_plan(&h, R, M, prec, &cfg, pl) != TBK_OK) return 1;
                                 if (pl.total > kStaticSweepBytes) continue;
                                 ++runs;
-                                off += !pl.tile.on;
+                                off += !pl.tile.on && !doubling;      // few moments in the doubling form are swept
                                 most = std::max(most, pl.tile.total);
                             }
     std::printf("%ld %ld %zu %zu\n", runs, off, most, (size_t)kStaticBytes);
